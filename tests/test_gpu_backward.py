@@ -96,6 +96,14 @@ def test_attn_bwd_options(causal):
     _check(w, seed=37, causal=causal)
 
 
+@pytest.mark.parametrize("B,H,per_head", [(20, 9, False), (150, 1, True), (17, 2, True)])
+def test_attn_bwd_many_heads(B, H, per_head):
+    """Sums over many heads: more and fewer than the row lanes and their unrolled loads."""
+    w = small_workload("f32", B=B, H=H, n=5, d=32, M=8, L=8, per_head=per_head)
+    say(f"backward many heads B={B} H={H} per_head={per_head}")
+    _check(w, seed=41, causal=False)
+
+
 def test_attn_bwd_rejects_bad_arguments():
     import torch
     w = small_workload("f32", B=1, H=1, n=8, d=64, M=16, L=8)
