@@ -12,6 +12,7 @@
 #include <mutex>
 #include <string>
 
+#include "luna_grad.hpp"
 #include "luna_kernels.hpp"
 
 namespace {
@@ -74,10 +75,10 @@ struct Layout {
   // gradients, intra-chunk P and R (causal), feature gradients, dV in fp32 (bf16
   // calls), per-workgroup parameter partials, their fp64 sums and moment prefixes
   size_t vx = 0, y = 0, sx = 0, dsx = 0, pm = 0, rm = 0, dphiq = 0, dphik = 0, dvtmp = 0;
-  size_t xq = 0, xk = 0, wx = 0, uq = 0, uk = 0, duq = 0, duk = 0, dwh = 0;  // feature-map backward
+  size_t duq = 0, duk = 0, dwp = 0;  // feature-map backward
   size_t bpart = 0, sum = 0, pre = 0;
   size_t dstats = 0;  // distillation: per query row the softmax max and sum and the kernel row sum
-  int chunk = 0, nch = 1, groups = 0, part_floats = 0;
+  int chunk = 0, nch = 1, groups = 0, dw_groups = 0, part_floats = 0;
   int splits = 1, tokens_per_split = 0, tile_tokens = 256, tiles = 1, fused = 0;
   int parts = 1, split = 0;  // causal: workgroups per head, first token of part 1
   size_t state = 0;          // causal with 2 parts: state pieces of the first `split` tokens
@@ -178,27 +179,22 @@ void plan_splits(const Problem& pb, int64_t heads, Layout* lay) {
 // parameter gradients).
 constexpr int kOpDistill = 100, kOpDistillGrads = 101;
 
-// Buffers of the feature-map backward (enqueue_phi_backward): [x | 1] of the queries
-// and keys, [W | b], the projections and their gradients, per-(batch, head) [dW | db],
-// the per-workgroup parameter partials, their fp64 sums and moment prefixes.
+// Buffers of the feature-map backward (enqueue_phi_backward): the projections'
+// gradients, per-workgroup [dW | db] and moments, the moments' fp64 sums and prefixes.
 void plan_phi_backward(const Problem& pb, Layout* lay, size_t* off) {
   const int d = (int)pb.d, L = pb.p->L, M = pb.p->M, P = param_sets(pb);
-  const int64_t heads = pb.B * pb.H;
+  const int64_t heads = pb.B * pb.H, rows_per_set = pb.n * (heads / P);
   const size_t rows = (size_t)heads * (size_t)pb.n;
   auto take = [&](size_t& at, size_t bytes) {
     at = *off;
     *off = align256(*off + bytes);
   };
-  take(lay->xq, rows * (d + 1) * 4);
-  take(lay->xk, rows * (d + 1) * 4);
-  take(lay->wx, (size_t)P * M * (d + 1) * 4);
-  take(lay->uq, rows * M * 4);
-  take(lay->uk, rows * M * 4);
   take(lay->duq, rows * M * 4);
   take(lay->duk, rows * M * 4);
-  take(lay->dwh, (size_t)heads * M * (d + 1) * 4);
-  lay->groups = luna::bwd_phi_groups(2 * pb.n * (heads / P) * M);
+  lay->groups = luna::map_bwd_groups(rows_per_set, P);
+  lay->dw_groups = luna::map_dw_groups(rows_per_set, P);
   lay->part_floats = (int)luna::bwd_part_floats(d, L, M);
+  take(lay->dwp, (size_t)P * lay->dw_groups * M * (d + 1) * 4);
   take(lay->bpart, (size_t)P * lay->groups * lay->part_floats * 4);
   take(lay->sum, (size_t)P * lay->part_floats * 8);
   take(lay->pre, (size_t)P * L * (luna::bwd_nseg_cap(L) + 1) * 2 * 8);
@@ -571,91 +567,48 @@ luna_status plan_features(luna_dtype phi_dtype, luna_dtype dtype, int64_t B, int
 }
 
 // Through the feature map, from dphi(Q) and dphi(K) in the workspace (fp32, [head][n][D]):
-// u = [x | 1] [W | b]^T (GEMM), du from dphi on the tables, [dW | db] = du^T [x | 1]
-// and the channel-MLP gradients into grads (when given), dx = du [W | b] into dQ, dK
-// (when given).  Used by the backward pass and by the distillation loss.
+// dx into dQ, dK (when given), [dW | db] and the channel-MLP gradients into grads (when
+// given).  Used by the backward pass and by the distillation loss.
 luna_status enqueue_phi_backward(const Problem& pb, uint8_t* w, const Layout& lay, const void* Q, const void* K,
                                  void* dQ, void* dK, const luna_phi_grads* grads, hipStream_t s) {
   const luna_phi_params* p = pb.p;
-  const luna::Dt dt = pb.dt == LUNA_BF16 ? luna::Dt::BF16 : luna::Dt::F32;
-  const int64_t B = pb.B, H = pb.H, n = pb.n;
-  const int M = p->M, L = p->L, dd = (int)pb.d, E = dd + 1;
-  const int heads = (int)(B * H);
-  const int64_t nE = n * E;
-  float* dphiq = reinterpret_cast<float*>(w + lay.dphiq);
-  float* dphik = reinterpret_cast<float*>(w + lay.dphik);
+  const int M = p->M, L = p->L, dd = (int)pb.d, P = param_sets(pb);
   hipError_t e;
 #define LUNA_TRY(expr, what) \
   if ((e = (expr)) != hipSuccess) return hip_fail(e, what)
-  const int P = param_sets(pb);
-  const int Hh = (int)H, Bb = (int)B;
-  float* xq = reinterpret_cast<float*>(w + lay.xq);
-  float* xk = reinterpret_cast<float*>(w + lay.xk);
-  float* wx = reinterpret_cast<float*>(w + lay.wx);
-  float* uq = reinterpret_cast<float*>(w + lay.uq);
-  float* uk = reinterpret_cast<float*>(w + lay.uk);
-  float* duq = reinterpret_cast<float*>(w + lay.duq);
-  float* duk = reinterpret_cast<float*>(w + lay.duk);
-  float* dwh = reinterpret_cast<float*>(w + lay.dwh);
-  LUNA_TRY(luna::launch_bwd_pack(dt, Q, xq, (int64_t)heads * n, dd, s), "pack kernel launch");
-  LUNA_TRY(luna::launch_bwd_pack(dt, K, xk, (int64_t)heads * n, dd, s), "pack kernel launch");
-  LUNA_TRY(luna::launch_bwd_packw(dt, p->W, p->b, wx, P * M, dd, s), "pack kernel launch");
-  // products over (batch, head) pairs: the batch index is the GEMM's head, the head its
-  // chunk, so that per-head parameters are addressed by stride
-  const int64_t wsc = p->per_head ? (int64_t)M * E : 0;
-  auto gemm_bh = [&](const float* A, int64_t ah, int64_t ac, int64_t ai, int64_t ak, const float* Bm, int64_t bh,
-                     int64_t bc, int64_t bk, int64_t bj, float* Cm, int64_t ch, int64_t c2, int64_t ci, int64_t cj, int Mm,
-                     int Nn, int Kk, int acc) {
-    luna::BwdGemm g{};
-    g.A = A; g.sAh = ah; g.sAc = ac; g.sAi = ai; g.sAk = ak;
-    g.B = Bm; g.sBh = bh; g.sBc = bc; g.sBk = bk; g.sBj = bj;
-    g.C = Cm; g.sCh = ch; g.sCc = c2; g.sCi = ci; g.sCj = cj;
-    g.M = Mm; g.N = Nn; g.K = Kk;
-    g.heads = Bb; g.chunks = Hh; g.chunk = (int)n; g.seq = (int)n;
-    g.accumulate = acc;
-    return luna::launch_bwd_gemm(g, s);
-  };
-  const int64_t nM = n * M, ME = (int64_t)M * E;
-  for (int side = 0; side < 2; ++side) {
-    const float* x = side ? xk : xq;
-    float* u = side ? uk : uq;
-    LUNA_TRY(gemm_bh(x, Hh * nE, nE, E, 1, wx, 0, wsc, 1, E, u, Hh * nM, nM, M, 1, (int)n, M, E, 0), "projection GEMM");
-  }
-  luna::BwdPhi ph{};
-  ph.uq = uq;
-  ph.uk = uk;
-  ph.dphiq = dphiq;
-  ph.dphik = dphik;
-  ph.duq = duq;
-  ph.duk = duk;
-  ph.tables = w + lay.tables;
-  ph.partial = reinterpret_cast<float*>(w + lay.bpart);
-  ph.n = n;
-  ph.heads = B * H;
-  ph.H = Hh;
-  ph.M = M;
-  ph.per_head = p->per_head;
-  ph.part_floats = lay.part_floats;
-  LUNA_TRY(luna::launch_bwd_phi(L, ph, lay.groups, P, s), "feature-map backward kernel launch");
-  for (int side = 0; side < 2; ++side) {
-    float* x = side ? xk : xq;
-    const float* du = side ? duk : duq;
-    if (grads)  // [dW | db] per (batch, head), both sides added
-      LUNA_TRY(gemm_bh(du, Hh * nM, nM, 1, M, x, Hh * nE, nE, E, 1, dwh, Hh * ME, ME, E, 1, M, E, (int)n, side),
-               "weight-gradient GEMM");
-    // dx = du [W | b] into x's rows (x is not read again), then its first d columns
-    void* dx = side ? dK : dQ;
-    if (dx == nullptr) continue;
-    LUNA_TRY(gemm_bh(du, Hh * nM, nM, M, 1, wx, 0, wsc, E, 1, x, Hh * nE, nE, E, 1, (int)n, E, M, 0), "dx GEMM");
-    LUNA_TRY(luna::launch_bwd_cols(dt, x, dx, (int64_t)heads * n, dd, s), "dx convert");
-  }
+  luna::MapBwd a{};
+  a.xq = Q;
+  a.xk = K;
+  a.dphiq = reinterpret_cast<const float*>(w + lay.dphiq);
+  a.dphik = reinterpret_cast<const float*>(w + lay.dphik);
+  a.dxq = dQ;
+  a.dxk = dK;
   if (grads) {
-    LUNA_TRY(luna::launch_bwd_dw(dwh, grads->W, grads->b, Bb, Hh, M, dd, p->per_head, s), "weight-gradient sum");
+    a.duq = reinterpret_cast<float*>(w + lay.duq);
+    a.duk = reinterpret_cast<float*>(w + lay.duk);
+  }
+  a.W = p->W;
+  a.b = p->b;
+  a.tables = w + lay.tables;
+  a.partial = reinterpret_cast<float*>(w + lay.bpart);
+  a.dw_partial = reinterpret_cast<float*>(w + lay.dwp);
+  a.n = pb.n;
+  a.heads = pb.B * pb.H;
+  a.H = (int)pb.H;
+  a.M = M;
+  a.per_head = p->per_head;
+  a.groups = lay.groups;
+  a.dw_groups = lay.dw_groups;
+  a.part_floats = lay.part_floats;
+  LUNA_TRY(luna::launch_map_bwd(pb.dt == LUNA_BF16 ? luna::Dt::BF16 : luna::Dt::F32, dd, L, a, P, s),
+           "feature-map backward kernel launch");
+  if (grads) {
+    LUNA_TRY(luna::launch_bwd_dw(a.dw_partial, grads->W, grads->b, lay.dw_groups, M, dd, P, s), "weight-gradient sum");
     const int units = (p->shared_channels ? 1 : L) * p->hidden;
     const int used = 2 * (units + 1) * L;
     double* sum = reinterpret_cast<double*>(w + lay.sum);
     double* pre = reinterpret_cast<double*>(w + lay.pre);
-    LUNA_TRY(luna::launch_bwd_reduce(ph.partial, sum, lay.groups, lay.part_floats, used, P, s), "reduce kernel launch");
+    LUNA_TRY(luna::launch_bwd_reduce(a.partial, sum, lay.groups, lay.part_floats, used, P, s), "reduce kernel launch");
     LUNA_TRY(luna::launch_bwd_prefix(sum, pre, w + lay.tables, M, dd, L, lay.part_floats, luna::bwd_nseg_cap(L), P, s),
              "prefix kernel launch");
     luna::BwdMlp m{};

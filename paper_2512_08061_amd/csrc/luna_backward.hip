@@ -30,13 +30,10 @@
 //                       the non-causal form, split into chunks only for parallelism,
 //                       their total);
 //   bwd_g_kernel        [num | den - eps] -> G = [dnum | dden];
-//   bwd_packw_kernel    [W | b] in fp32: u = [x | 1] [W | b]^T, dx = du [W | b] (first d
-//                       columns), [dW | db] = du^T [x | 1] are GEMMs;
-//   bwd_phi_kernel      dphi -> du, one thread per (row, projection): the slopes of the
-//                       piecewise-linear channel functions, zero where the output ReLU
-//                       is off, and per workgroup the (segment, channel) moments sum dy
-//                       and sum dy u of the channel outputs' gradients;
-//   bwd_dw_kernel       [dW | db] summed over the (batch, head) products;
+//   (luna_map_backward.hip: dphi -> du -> dx, [dW | db] per workgroup and the
+//                       (segment, channel) moments sum dy and sum dy u of the channel
+//                       outputs' gradients)
+//   bwd_dw_kernel       [dW | db] summed over workgroups (fp64);
 //   bwd_reduce_kernel   the partials summed over workgroups (fp64);
 //   bwd_prefix_kernel   exclusive prefix sums of the moments over segments, per channel;
 //   bwd_mlp_kernel      the channel-MLP parameter gradients from the moments: unit k
@@ -53,6 +50,7 @@
 #include <algorithm>
 
 #include "luna_device.hpp"
+#include "luna_grad.hpp"
 #include "luna_kernels.hpp"
 
 namespace luna {
@@ -256,106 +254,6 @@ __global__ __launch_bounds__(256) void fwd_export_kernel(const float* __restrict
 }
 
 // ---------------------------------------------------------------------------
-// [W | b] in fp32, per parameter set: the projection u = [x | 1] [W | b]^T
-// ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void bwd_packw_kernel(const T* __restrict__ W, const float* __restrict__ b,
-                                                        float* __restrict__ Wx, int rows, int d) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= rows * (d + 1)) return;
-  const int r = i / (d + 1), c = i - r * (d + 1);
-  Wx[i] = c < d ? (float)W[(size_t)r * d + c] : b[r];
-}
-
-// ---------------------------------------------------------------------------
-// feature-map backward: one thread per (row, projection).  From u and dphi of the
-// row, on u's segment: y'_l = s'_l u + t'_l (the table's slope and intercept, scaled by
-// 1/sqrt(M)), g_l = dphi_l where the output ReLU passes (y' > 0, or always without
-// it), du = sum_l g_l s'_l, and into the (segment, channel) moments dy_l = g_l / sqrt(M)
-// and dy_l u (LDS, one copy per workgroup, written out as partials).
-// ---------------------------------------------------------------------------
-template <int L>
-__global__ __launch_bounds__(256) void bwd_phi_kernel(BwdPhi a) {
-  constexpr int NSEG = nseg_cap(L, kFmSegBytes);
-  __shared__ PwlLds<L, NSEG> tab;
-  // per (channel, segment): sum dy and sum dy u, channel-major so that the lanes of
-  // one atomic instruction (one channel, random segments) spread over the banks
-  __shared__ float m0[L][NSEG], m1[L][NSEG];
-  const int set = blockIdx.y, tid = threadIdx.x;
-  const int M = a.M, D = M * L;
-  pwl_load(tab, a.tables + (size_t)set * kTableBytes);
-  for (int i = tid; i < NSEG * L; i += blockDim.x) {
-    m0[i / NSEG][i % NSEG] = 0.0f;
-    m1[i / NSEG][i % NSEG] = 0.0f;
-  }
-  __syncthreads();
-  const int steps = __builtin_amdgcn_readfirstlane(tab.steps);
-  const float floor = tab.floor;
-  const float rsm = 1.0f / sqrtf((float)M);
-  const int64_t heads_in_set = a.per_head ? a.heads / a.H : a.heads;
-  const int64_t per_side = heads_in_set * a.n * M;  // elements (row, projection) of one side
-  const int64_t total = 2 * per_side;
-  // NB elements per thread and round, their loads issued before any is used
-  constexpr int NB = 4;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t e0 = blockIdx.x * (int64_t)blockDim.x + tid; e0 < total; e0 += NB * stride) {
-    float u[NB], gv[NB][L];
-    int64_t ui[NB];
-    int side[NB];
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      const int64_t e = min(e0 + b * stride, total - 1);  // (clamped: loads stay in range)
-      side[b] = e >= per_side;
-      const int64_t el = e - side[b] * per_side;
-      const int64_t hs = el / (a.n * M);
-      const int64_t rest = el - hs * a.n * M;  // t M + i
-      const int i = (int)(rest % M);
-      const int64_t head = a.per_head ? hs * a.H + set : hs;
-      ui[b] = head * a.n * M + rest;
-      u[b] = (side[b] ? a.uk : a.uq)[ui[b]];
-      const float* g = (side[b] ? a.dphik : a.dphiq) + head * a.n * D + (rest - i) / M * D + (int64_t)i * L;
-      if constexpr (L % 4 == 0) {
-#pragma unroll
-        for (int q = 0; q < L / 4; ++q) {
-          const float4 v = reinterpret_cast<const float4*>(g)[q];
-          gv[b][4 * q] = v.x; gv[b][4 * q + 1] = v.y; gv[b][4 * q + 2] = v.z; gv[b][4 * q + 3] = v.w;
-        }
-      } else {
-#pragma unroll
-        for (int l = 0; l < L; ++l) gv[b][l] = g[l];
-      }
-    }
-    int sg[NB];
-    pwl_search(tab, steps, u, sg);
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      if (e0 + b * stride >= total) break;
-      const float2* row = reinterpret_cast<const float2*>(seg_ptr(tab, sg[b]));
-      float du = 0.0f;
-#pragma unroll
-      for (int l = 0; l < L; ++l) {
-        const float2 st = row[l];
-        const float gl = fmaf(st.x, u[b], st.y) > floor ? gv[b][l] : 0.0f;  // floor: 0 (output ReLU) or -inf
-        du = fmaf(gl, st.x, du);
-        if (gl != 0.0f) {  // (channels cut by the output ReLU add nothing)
-          const float dy = gl * rsm;
-          atomicAdd(&m0[l][sg[b]], dy);
-          atomicAdd(&m1[l][sg[b]], dy * u[b]);
-        }
-      }
-      (side[b] ? a.duk : a.duq)[ui[b]] = du;
-    }
-  }
-  __syncthreads();
-  float* part = a.partial + ((size_t)set * gridDim.x + blockIdx.x) * a.part_floats;
-  const int nm = tab.zero_seg * L;  // real segments x channels
-  for (int i = tid; i < nm; i += blockDim.x) {  // partials as [segment][channel][2]
-    part[2 * i] = m0[i % L][i / L];
-    part[2 * i + 1] = m1[i % L][i / L];
-  }
-}
-
-// ---------------------------------------------------------------------------
 // column sums in fp64: workgroups of 64 columns x 16 row lanes.  A thread takes every
 // 16th row of its column (eight loads in flight), the 16 lanes of a column meet in LDS
 // in a fixed order.  These sums are bound by the latency of their loads: one thread
@@ -390,33 +288,19 @@ __device__ __forceinline__ double column_sum(int rows, F at) {
 }
 
 // ---------------------------------------------------------------------------
-// [dW | db] per parameter set from the per-(batch, head) products dU^T [X | 1]
+// [dW | db] per parameter set from the workgroups' sums [set][groups][M][d + 1]
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kSumCols * kSumLanes) void bwd_dw_kernel(const float* __restrict__ dwh,
+__global__ __launch_bounds__(kSumCols * kSumLanes) void bwd_dw_kernel(const float* __restrict__ partial,
                                                                       float* __restrict__ dW, float* __restrict__ db,
-                                                                      int B, int H, int M, int d, int per_head) {
+                                                                      int groups, int M, int d) {
   const int E = d + 1, cols = M * E, set = blockIdx.y;
   const int rest = blockIdx.x * kSumCols + threadIdx.x % kSumCols;  // (i, c)
-  const int at = min(rest, cols - 1);
-  const int rows = per_head ? B : B * H;  // row r: head r, or head `set` of batch r
-  const double s = column_sum(rows, [&](int r) {
-    return dwh[((size_t)r * (per_head ? H : 1) + (per_head ? set : 0)) * cols + at];
-  });
+  const float* p = partial + (size_t)set * groups * cols + min(rest, cols - 1);
+  const double s = column_sum(groups, [&](int r) { return p[(size_t)r * cols]; });
   if (threadIdx.x >= kSumCols || rest >= cols) return;
   const int i = rest / E, c = rest - i * E;
   if (c < d) dW[((size_t)set * M + i) * d + c] = (float)s;
   else db[(size_t)set * M + i] = (float)s;
-}
-
-// dX rows [rows][d + 1] (fp32, the last column unused) -> [rows][d] in the call's dtype
-template <typename T>
-__global__ __launch_bounds__(256) void bwd_cols_kernel(const float* __restrict__ src, T* __restrict__ dst, int64_t rows,
-                                                       int d) {
-  const int64_t n = rows * d;
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t r = i / d;
-    dst[i] = (T)src[i + r];  // row r starts at r (d + 1)
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -616,10 +500,6 @@ hipError_t launch_bwd_g(Dt dt, float* Y, const void* dO, int64_t rows, int d, fl
   return hipGetLastError();
 }
 
-int bwd_phi_groups(int64_t rows_per_set) {
-  return (int)std::max<int64_t>(1, std::min<int64_t>((rows_per_set + 1023) / 1024, 512));
-}
-
 bool bwd_supported(int d, int L, int M) {
   const bool lok = L == 1 || L == 2 || L == 4 || L == 8 || L == 16;
   return lok && M >= 1 && M <= 256 && M * L <= 256 && d >= 1 && d <= 128;
@@ -627,37 +507,10 @@ bool bwd_supported(int d, int L, int M) {
 
 size_t bwd_part_floats(int, int L, int) { return 2 * (size_t)nseg_cap(L, kFmSegBytes) * L; }
 
-hipError_t launch_bwd_packw(Dt dt, const void* W, const float* b, float* Wx, int rows, int d, hipStream_t s) {
-  const dim3 grid((unsigned)((rows * (d + 1) + 255) / 256)), block(256);
-  if (dt == Dt::BF16) hipLaunchKernelGGL(bwd_packw_kernel<__bf16>, grid, block, 0, s, (const __bf16*)W, b, Wx, rows, d);
-  else hipLaunchKernelGGL(bwd_packw_kernel<float>, grid, block, 0, s, (const float*)W, b, Wx, rows, d);
-  return hipGetLastError();
-}
-
-hipError_t launch_bwd_phi(int L, const BwdPhi& a, int groups, int sets, hipStream_t s) {
-  const dim3 grid((unsigned)groups, (unsigned)sets);
-  switch (L) {
-    case 1: hipLaunchKernelGGL(bwd_phi_kernel<1>, grid, dim3(256), 0, s, a); break;
-    case 2: hipLaunchKernelGGL(bwd_phi_kernel<2>, grid, dim3(256), 0, s, a); break;
-    case 4: hipLaunchKernelGGL(bwd_phi_kernel<4>, grid, dim3(256), 0, s, a); break;
-    case 8: hipLaunchKernelGGL(bwd_phi_kernel<8>, grid, dim3(256), 0, s, a); break;
-    case 16: hipLaunchKernelGGL(bwd_phi_kernel<16>, grid, dim3(256), 0, s, a); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
-hipError_t launch_bwd_dw(const float* dwh, float* dW, float* db, int B, int H, int M, int d, int per_head,
+hipError_t launch_bwd_dw(const float* partial, float* dW, float* db, int groups, int M, int d, int sets,
                          hipStream_t s) {
-  const dim3 grid((unsigned)((M * (d + 1) + kSumCols - 1) / kSumCols), (unsigned)(per_head ? H : 1));
-  hipLaunchKernelGGL(bwd_dw_kernel, grid, dim3(kSumCols * kSumLanes), 0, s, dwh, dW, db, B, H, M, d, per_head);
-  return hipGetLastError();
-}
-
-hipError_t launch_bwd_cols(Dt dt, const float* src, void* dst, int64_t rows, int d, hipStream_t s) {
-  const dim3 grid((unsigned)std::min<int64_t>((rows * d + 255) / 256, 65536)), block(256);
-  if (dt == Dt::BF16) hipLaunchKernelGGL(bwd_cols_kernel<__bf16>, grid, block, 0, s, src, (__bf16*)dst, rows, d);
-  else hipLaunchKernelGGL(bwd_cols_kernel<float>, grid, block, 0, s, src, (float*)dst, rows, d);
+  const dim3 grid((unsigned)((M * (d + 1) + kSumCols - 1) / kSumCols), (unsigned)sets);
+  hipLaunchKernelGGL(bwd_dw_kernel, grid, dim3(kSumCols * kSumLanes), 0, s, partial, dW, db, groups, M, d);
   return hipGetLastError();
 }
 

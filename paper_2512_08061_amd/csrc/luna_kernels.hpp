@@ -192,74 +192,6 @@ struct StepArgs {
 };
 constexpr int kStepMaxD = 256;  // features the step kernel holds per column
 
-// Backward pass (luna_backward.hip).  Batched C (+)= A B over (head, chunk) with
-// strided fp32 operands: element (i, k) of A at A + h sAh + c sAc + i sAi + k sAk, and
-// so on.  Dimensions marked *_chunk are token dimensions of a chunk of `chunk`
-// tokens of a `seq`-token sequence (shorter in a ragged last chunk).  lower: entries
-// above the diagonal (j > i) of the product are stored as 0.
-struct BwdGemm {
-  const float* A;
-  const float* B;
-  float* C;
-  int M, N, K;
-  int64_t sAh, sAc, sAi, sAk;
-  int64_t sBh, sBc, sBk, sBj;
-  int64_t sCh, sCc, sCi, sCj;
-  int heads, chunks, chunk, seq;
-  int m_chunk, n_chunk, k_chunk;
-  int lower, accumulate;
-};
-
-// Feature-map backward over the rows of Q and K of every head, one thread per
-// (row, projection): du from dphi and u, and the (segment, channel) moments.
-struct BwdPhi {
-  const float* uq;     // [heads][n][M] projections u = x W^T + b
-  const float* uk;
-  const float* dphiq;  // [heads][n][M*L]
-  const float* dphik;
-  float* duq;          // [heads][n][M]
-  float* duk;
-  const uint8_t* tables;
-  float* partial;      // [P][groups][part_floats]: (segment, channel) moments
-  int64_t n, heads;
-  int H, M, per_head;
-  int part_floats;
-};
-
-// Channel-MLP parameter gradients from the reduced partials.
-struct BwdMlp {
-  const double* sum;   // [P][part_floats] (fp64)
-  const double* pre;   // [P][L][nseg_cap + 1][2]: exclusive prefix sums of the moments
-  const uint8_t* tables;
-  const float* fc1_w;
-  const float* fc1_b;
-  const float* fc2_w;
-  float* dfc1_w;
-  float* dfc1_b;
-  float* dfc2_w;
-  float* dfc2_b;
-  int L, hidden, C1, part_floats, nseg_cap;
-};
-
-bool bwd_supported(int d, int L, int M);
-size_t bwd_part_floats(int d, int L, int M);
-int bwd_phi_groups(int64_t rows_per_set);
-int bwd_nseg_cap(int L);
-hipError_t launch_bwd_pack(Dt dt, const void* V, float* Vx, int64_t rows, int d, hipStream_t s);
-hipError_t launch_bwd_convert(Dt dt, const float* src, void* dst, int64_t n, hipStream_t s);
-hipError_t launch_bwd_gemm(const BwdGemm& g, hipStream_t s);
-hipError_t launch_bwd_scan(float* X, int heads, int chunks, int64_t elems, int mode, hipStream_t s);
-hipError_t launch_bwd_g(Dt dt, float* Y, const void* dO, int64_t rows, int d, float eps, hipStream_t s);
-hipError_t launch_bwd_packw(Dt dt, const void* W, const float* b, float* Wx, int rows, int d, hipStream_t s);
-hipError_t launch_bwd_phi(int L, const BwdPhi& a, int groups, int sets, hipStream_t s);
-hipError_t launch_bwd_dw(const float* dwh, float* dW, float* db, int B, int H, int M, int d, int per_head,
-                         hipStream_t s);
-hipError_t launch_bwd_cols(Dt dt, const float* src, void* dst, int64_t rows, int d, hipStream_t s);
-hipError_t launch_bwd_reduce(const float* partial, double* sum, int groups, int part_floats, int used, int sets,
-                             hipStream_t s);
-hipError_t launch_bwd_prefix(const double* sum, double* pre, const uint8_t* tables, int M, int d, int L,
-                             int part_floats, int nseg_cap, int sets, hipStream_t s);
-hipError_t launch_bwd_mlp(const BwdMlp& a, int sets, hipStream_t s);
 // Feature-map variants (random Fourier cos and sin/cos, Performer, channel MLPs with a
 // smooth activation, an envelope, channel RMS and Bank+Coef), evaluated directly.
 constexpr int kVarMlp = 0, kVarCos = 1, kVarSinCos = 2, kVarPerformer = 3;
@@ -313,11 +245,6 @@ struct DistillArgs {
 };
 bool distill_supported(Dt dt, int d, int D);
 hipError_t launch_distill(Dt dt, int d, int D, const DistillArgs& a, bool grads, hipStream_t s);
-
-// forward pass of the shapes without a fused kernel (fp32 GEMMs and scans as above)
-hipError_t launch_fwd_out(Dt dt, const float* Y, void* out, int64_t rows, int d, float eps, hipStream_t s);
-hipError_t launch_fwd_export(const float* X, int64_t head_stride, float* S, float* z, int heads, int D, int d,
-                             int accumulate, hipStream_t s);
 
 // Launchers; each returns hipSuccess or the launch error.  `ok` reports whether
 // a kernel exists for the (dtype, d, L, M) combination.

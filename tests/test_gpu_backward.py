@@ -104,6 +104,17 @@ def test_attn_bwd_many_heads(B, H, per_head):
     _check(w, seed=41, causal=False)
 
 
+@pytest.mark.parametrize("dtype,d,M,L,hidden,n", [
+    ("f32", 32, 5, 2, 64, 45), ("bf16", 64, 7, 8, 64, 33), ("bf16", 128, 20, 4, 64, 31), ("f32", 64, 33, 1, 64, 47),
+    ("bf16", 32, 16, 16, 16, 17), ("f32", 128, 8, 16, 16, 15), ("bf16", 128, 8, 16, 16, 16), ("f32", 128, 1, 1, 8, 49)])
+def test_attn_bwd_map_tiles(dtype, d, M, L, hidden, n):
+    """Projection counts off the 4-, 8-, 16- and 32-projection blocks of the feature-map
+    gradients (two row tiles to a block up to 8), and rows off their 16- and 32-row tiles."""
+    w = small_workload(dtype, B=2, H=2, n=n, d=d, M=M, L=L, hidden=hidden)
+    say(f"backward map tiles {w.name}")
+    _check(w, seed=43 + n, causal=False)
+
+
 def test_attn_bwd_rejects_bad_arguments():
     import torch
     w = small_workload("f32", B=1, H=1, n=8, d=64, M=16, L=8)
