@@ -12,6 +12,7 @@
 #include <mutex>
 #include <string>
 
+#include "luna_features.hpp"
 #include "luna_grad.hpp"
 #include "luna_kernels.hpp"
 
@@ -84,6 +85,7 @@ struct Layout {
   size_t state = 0;          // causal with 2 parts: state pieces of the first `split` tokens
   int pieces = 0, piece_chunks = 0;
   int staged = 0, sa = 0, sb = 0;  // staged causal scan: chunks of the first scanned part and of the state-only part
+  int feat = 0;     // non-causal attention from given features in their own type
   int generic = 0;  // forward in fp32 GEMMs and scans (shapes without a fused kernel)
   int given = 0;    // causal: features mapped beforehand (bf16, in phiq / phik), then the scan kernel
 };
@@ -438,35 +440,74 @@ luna_status enqueue_f32_attention(luna::Dt vdt, int64_t heads64, int64_t n, int 
   return LUNA_OK;
 }
 
-// The forward pass in fp32: features of the keys (and queries) by the feature-map
-// kernel, then enqueue_f32_attention.  Q == nullptr: the state only.
-luna_status enqueue_f32_forward(const Problem& pb, uint8_t* w, const Layout& lay, const void* Q, const void* K,
-                                const void* V, bool causal, hipStream_t s) {
-  const luna::Dt dt = pb.dt == LUNA_BF16 ? luna::Dt::BF16 : luna::Dt::F32;
-  const int L = pb.p->L, D = pb.p->M * L, dd = (int)pb.d;
-  float* phiq = reinterpret_cast<float*>(w + lay.phiq);
-  float* phik = reinterpret_cast<float*>(w + lay.phik);
+// Features of the keys (and queries) in fp32 into the workspace.  Q == nullptr: keys only.
+luna_status enqueue_f32_features(const Problem& pb, uint8_t* w, const Layout& lay, const void* Q, const void* K,
+                                 hipStream_t s) {
   luna::FeatureMapArgs f{};  // queries and keys in one launch
   f.phi = phi_args(pb, w, lay);
   f.rows_per_head = pb.n;
   f.H = (int)pb.H;
   f.heads = pb.B * pb.H;
   f.X = K;
-  f.out = phik;
+  f.out = w + lay.phik;
   if (Q) {
     f.X2 = Q;
-    f.out2 = phiq;
+    f.out2 = w + lay.phiq;
   }
-  const hipError_t e = luna::launch_featuremap(dt, luna::Dt::F32, dd, L, f, s);
-  if (e != hipSuccess) return hip_fail(e, "feature-map kernel launch");
+  const hipError_t e = luna::launch_featuremap(pb.dt == LUNA_BF16 ? luna::Dt::BF16 : luna::Dt::F32, luna::Dt::F32,
+                                               (int)pb.d, pb.p->L, f, s);
+  return e == hipSuccess ? LUNA_OK : hip_fail(e, "feature-map kernel launch");
+}
+
+// The non-causal attention from features in memory (eq. (9) of Section 3.1): statistics
+// per piece, their total, and with queries the readout.
+luna_status enqueue_feat_attention(luna::Dt fdt, luna::Dt vdt, int64_t heads, int64_t n, int d, int D, uint8_t* w,
+                                   const Layout& lay, const void* phiq, const void* phik, const void* V, float eps,
+                                   void* out, luna::FeatArgs* args, hipStream_t s) {
+  luna::FeatArgs& a = *args;
+  a.phiq = phiq;
+  a.phik = phik;
+  a.v = V;
+  a.out = out;
+  a.state = reinterpret_cast<float*>(w + lay.sx);
+  a.heads = heads;
+  a.n = n;
+  a.D = D;
+  a.piece = lay.chunk;
+  a.pieces = lay.nch;
+  a.eps = eps;
+  hipError_t e = luna::launch_feat_state(fdt, vdt, d, a, s);
+  if (e != hipSuccess) return hip_fail(e, "state kernel launch");
+  if ((e = luna::launch_feat_total(d, a, s)) != hipSuccess) return hip_fail(e, "state sum launch");
+  if (!phiq) return LUNA_OK;
+  e = luna::launch_feat_readout(fdt, vdt, d, a, s);
+  return e == hipSuccess ? LUNA_OK : hip_fail(e, "readout kernel launch");
+}
+
+// The forward pass in fp32: features of the keys (and queries) by the feature-map
+// kernel, then enqueue_f32_attention.  Q == nullptr: the state only.
+luna_status enqueue_f32_forward(const Problem& pb, uint8_t* w, const Layout& lay, const void* Q, const void* K,
+                                const void* V, bool causal, hipStream_t s) {
+  const luna::Dt dt = pb.dt == LUNA_BF16 ? luna::Dt::BF16 : luna::Dt::F32;
+  const int D = pb.p->M * pb.p->L, dd = (int)pb.d;
+  float* phiq = reinterpret_cast<float*>(w + lay.phiq);
+  float* phik = reinterpret_cast<float*>(w + lay.phik);
+  const luna_status st = enqueue_f32_features(pb, w, lay, Q, K, s);
+  if (st != LUNA_OK) return st;
   return enqueue_f32_attention(dt, pb.B * pb.H, pb.n, dd, D, w, lay, Q ? phiq : nullptr, phik, V, causal, s);
 }
 
 // The generic forward: the fp32 forward, then out = num / den in the call's dtype.
 luna_status enqueue_generic_attn(const Problem& pb, uint8_t* w, const Layout& lay, const void* Q, const void* K,
                                  const void* V, float eps, void* out, bool causal, hipStream_t s) {
-  luna_status st = enqueue_f32_forward(pb, w, lay, Q, K, V, causal, s);
-  if (st != LUNA_OK) return st;
+  luna_status st;
+  if (!causal) {
+    if ((st = enqueue_f32_features(pb, w, lay, Q, K, s)) != LUNA_OK) return st;
+    luna::FeatArgs a{};
+    return enqueue_feat_attention(luna::Dt::F32, pb.dt == LUNA_BF16 ? luna::Dt::BF16 : luna::Dt::F32, pb.B * pb.H, pb.n,
+                                  (int)pb.d, pb.p->M * pb.p->L, w, lay, w + lay.phiq, w + lay.phik, V, eps, out, &a, s);
+  }
+  if ((st = enqueue_f32_forward(pb, w, lay, Q, K, V, causal, s)) != LUNA_OK) return st;
   const hipError_t e = luna::launch_fwd_out(pb.dt == LUNA_BF16 ? luna::Dt::BF16 : luna::Dt::F32,
                                             reinterpret_cast<const float*>(w + lay.y), out, pb.B * pb.H * pb.n,
                                             (int)pb.d, eps, s);
@@ -557,6 +598,15 @@ luna_status plan_features(luna_dtype phi_dtype, luna_dtype dtype, int64_t B, int
   if (causal && phi_dtype == LUNA_BF16 && dtype == LUNA_BF16 && luna::causal_given_supported(luna::Dt::BF16, (int)d, (int)D)) {
     lay->given = 1;
     plan_causal_parts(heads, n, luna::causal_given_state_floats((int)d, (int)D), lay, &off, false);
+  } else if (!causal && luna::feat_supported((int)d, (int)D)) {
+    // the features in their own type: statistics of 512-token pieces only
+    lay->feat = 1;
+    lay->chunk = 512;
+    const int64_t pieces = (n + lay->chunk - 1) / lay->chunk;
+    if (pieces > 65535) return fail(LUNA_ERR_UNSUPPORTED, "n must be <= 65535 * 512");
+    lay->nch = (int)pieces;
+    lay->sx = off;
+    off = align256(off + (size_t)heads * lay->nch * (size_t)D * (size_t)(d + 1) * 4);
   } else {
     lay->generic = 1;
     luna_status st = plan_f32_buffers(heads, n, (int)d, (int)D, causal != 0, true, phi_dtype == LUNA_BF16, lay, &off);
@@ -769,6 +819,11 @@ luna_status luna_attn_fwd_features(const void* phiQ, const void* phiK, luna_dtyp
     return e == hipSuccess ? LUNA_OK : hip_fail(e, "causal attention kernel launch");
   }
   const int64_t heads = B * H;
+  if (lay.feat) {
+    luna::FeatArgs a{};
+    return enqueue_feat_attention(phi_dtype == LUNA_BF16 ? luna::Dt::BF16 : luna::Dt::F32, vdt, heads, n, (int)d, (int)D,
+                                  w, lay, phiQ, phiK, V, eps, out, &a, s);
+  }
   const float* fq = static_cast<const float*>(phiQ);
   const float* fk = static_cast<const float*>(phiK);
   if (phi_dtype == LUNA_BF16) {  // fp32 copies of the features
@@ -973,12 +1028,12 @@ luna_status luna_attn_state(const void* K, const void* V, luna_dtype dtype, int6
   if ((st = enqueue_prepare(pb, w, lay, s)) != LUNA_OK) return st;
   const luna::Dt dt = dtype == LUNA_BF16 ? luna::Dt::BF16 : luna::Dt::F32;
   if (lay.generic) {
-    if ((st = enqueue_f32_forward(pb, w, lay, nullptr, K, V, false, s)) != LUNA_OK) return st;
-    // every piece holds the total after the scan: export the first
-    const int D = p->M * p->L;
-    const hipError_t e = luna::launch_fwd_export(reinterpret_cast<const float*>(w + lay.sx),
-                                                 (int64_t)lay.nch * D * (d + 1), S, z, (int)(B * H), D, (int)d,
-                                                 accumulate, s);
+    if ((st = enqueue_f32_features(pb, w, lay, nullptr, K, s)) != LUNA_OK) return st;
+    luna::FeatArgs a{};
+    st = enqueue_feat_attention(luna::Dt::F32, dt, B * H, n, (int)d, p->M * p->L, w, lay, nullptr, w + lay.phik, V, 0.0f,
+                                nullptr, &a, s);
+    if (st != LUNA_OK) return st;
+    const hipError_t e = luna::launch_feat_export((int)d, a, S, z, accumulate, s);
     return e == hipSuccess ? LUNA_OK : hip_fail(e, "state export kernel launch");
   }
   if (lay.pieces == 0) {

@@ -44,9 +44,8 @@
 //
 // The same pack, GEMM and scan kernels carry the forward pass of the shapes that have
 // no fused kernel (any d, L and M the feature-map kernel takes: one channel per
-// projection with M up to 256, fp32 at d = 128, ...), in fp32 throughout, with two more:
+// projection with M up to 256, fp32 at d = 128, ...), in fp32 throughout, with one more:
 //   fwd_out_kernel      [num | den - eps] -> out = num / den in the call's dtype;
-//   fwd_export_kernel   the total [S | z] of a head into (or added to) the caller's S, z.
 #include <algorithm>
 
 #include "luna_device.hpp"
@@ -236,21 +235,6 @@ __global__ __launch_bounds__(256) void fwd_out_kernel(const float* __restrict__ 
   const float* y = Y + r * (d + 1);
   const float inv = 1.0f / (y[d] + eps);
   for (int c = lane; c < d; c += kWave) out[r * d + c] = (T)(y[c] * inv);
-}
-
-// [S | z] of each head ([D][d + 1], fp32) -> S [D][d] and z [D], set or added
-__global__ __launch_bounds__(256) void fwd_export_kernel(const float* __restrict__ X, int64_t head_stride,
-                                                         float* __restrict__ S, float* __restrict__ z, int heads,
-                                                         int D, int d, int accumulate) {
-  const int64_t per = (int64_t)D * (d + 1);
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < (int64_t)heads * per;
-       i += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t h = i / per, rest = i - h * per;
-    const int f = (int)(rest / (d + 1)), c = (int)(rest - (int64_t)f * (d + 1));
-    const float v = X[h * head_stride + rest];
-    float* dst = c < d ? &S[(h * D + f) * d + c] : &z[h * D + f];
-    *dst = accumulate ? *dst + v : v;
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -539,14 +523,6 @@ hipError_t launch_fwd_out(Dt dt, const float* Y, void* out, int64_t rows, int d,
   const dim3 grid((unsigned)((rows + 3) / 4)), block(256);
   if (dt == Dt::BF16) hipLaunchKernelGGL(fwd_out_kernel<__bf16>, grid, block, 0, s, Y, (__bf16*)out, rows, d, eps);
   else hipLaunchKernelGGL(fwd_out_kernel<float>, grid, block, 0, s, Y, (float*)out, rows, d, eps);
-  return hipGetLastError();
-}
-
-hipError_t launch_fwd_export(const float* X, int64_t head_stride, float* S, float* z, int heads, int D, int d,
-                             int accumulate, hipStream_t s) {
-  const int64_t total = (int64_t)heads * D * (d + 1);
-  const dim3 grid((unsigned)std::min<int64_t>((total + 255) / 256, 65536)), block(256);
-  hipLaunchKernelGGL(fwd_export_kernel, grid, block, 0, s, X, head_stride, S, z, heads, D, d, accumulate);
   return hipGetLastError();
 }
 

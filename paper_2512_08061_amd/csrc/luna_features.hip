@@ -1,0 +1,364 @@
+// luna_features.hip -- kernel attention, eq. (9) of Section 3.1, from features in memory:
+//
+//   feat_state_kernel    S = phi(K)^T V and z = phi(K)^T 1 per piece of a head's tokens
+//   feat_total_kernel    the pieces of a head summed
+//   feat_readout_kernel  out = phi(Q) S / (phi(Q) z + eps)
+//   feat_export_kernel   the statistics in the caller's layout
+//
+// The sums are fp32 whatever the types: two bf16 operands multiply exactly, a bf16 and
+// an fp32 one as three bf16 products, two fp32 ones on the fp32 matrix cores.  Features
+// and values are read in their own types, and z and the denominators are formed beside
+// the products, so nothing is widened or packed in memory first.  (Widening the features,
+// packing [V | 1], fp32 products on padded tiles and a scan took 440 us for 64 heads of
+// 4096 tokens with 128 bf16 features and d = 64; these kernels take 30 + 5 + 30 us.)
+#include <algorithm>
+
+#include "luna_device.hpp"
+#include "luna_features.hpp"
+#include "luna_split.hpp"
+
+namespace luna {
+
+namespace {
+
+// Rows k < rows of a [.][cols] array, columns cols .. cols_pad (16-byte pieces; cols a
+// multiple of the piece) read as 0.
+template <typename T>
+__device__ __forceinline__ uint4 piece16(const T* base, int k, int q, int rows, int cols) {
+  constexpr int V = Vec16<T>::N;
+  return k < rows && q * V < cols ? *reinterpret_cast<const uint4*>(base + (int64_t)k * cols + q * V)
+                                  : make_uint4(0, 0, 0, 0);
+}
+
+// ---------------------------------------------------------------------------
+// Per piece: S = phi(K)^T V, z.  Workgroups of four waves stage 32 tokens of features
+// and values in LDS (the next 32 in registers meanwhile) and read both transposed, the
+// tokens being the k dimension; wave w forms the 16-feature blocks w, w + 4, ... and all
+// value columns.  Bound by the read of the features and values: pieces are short enough
+// that a few hundred workgroups share the device.
+// ---------------------------------------------------------------------------
+constexpr int kFsTok = 32;
+
+template <typename TF, typename T, int DH, int FBW>
+__global__ __launch_bounds__(256) void feat_state_kernel(FeatArgs a) {
+  constexpr int CB = DH / 16, VF = Vec16<TF>::N, VT = Vec16<T>::N;
+  constexpr int DPM = 64 * FBW;                                  // features at most
+  constexpr int LDP = DPM + 16 / (int)sizeof(TF), LDV = DH + 16 / (int)sizeof(T);
+  constexpr int NP = kFsTok * DPM / VF / 256, NV = (kFsTok * DH / VT + 255) / 256;
+  __shared__ __attribute__((aligned(16))) TF ps[kFsTok * LDP];
+  __shared__ __attribute__((aligned(16))) T vs[kFsTok * LDV];
+  const int64_t head = blockIdx.x / a.pieces;
+  const int piece = (int)(blockIdx.x - head * a.pieces);
+  const int64_t first = (int64_t)piece * a.piece;
+  const int rows = (int)min((int64_t)a.piece, a.n - first);
+  const int D = a.D, tid = threadIdx.x, lane = tid % kWave, wave = wave_id();
+  const int g = lane / 16, r = lane % 16;
+  const TF* phi = reinterpret_cast<const TF*>(a.phik) + (head * a.n + first) * D;
+  const T* V = reinterpret_cast<const T*>(a.v) + (head * a.n + first) * DH;
+  const bool vec = D % VF == 0;  // (uniform) feature rows are whole 16-byte pieces
+  f32x4 acc[FBW][CB];
+  float z[FBW];
+#pragma unroll
+  for (int f = 0; f < FBW; ++f) {
+    z[f] = 0.0f;
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) acc[f][cb] = zero4();
+  }
+  uint4 pr[NP], vr[NV];
+  auto load = [&](int t0) {
+    if (vec)
+#pragma unroll
+      for (int i = 0; i < NP; ++i) {
+        const int c = tid + 256 * i;
+        pr[i] = piece16(phi + (int64_t)t0 * D, c / (DPM / VF), c % (DPM / VF), rows - t0, D);
+      }
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int c = tid + 256 * i;
+      vr[i] = piece16(V + (int64_t)t0 * DH, c / (DH / VT), c % (DH / VT), min(rows - t0, kFsTok), DH);
+    }
+  };
+  load(0);
+  for (int t0 = 0; t0 < rows; t0 += kFsTok) {
+    if (t0) __syncthreads();  // every wave is done with the tile
+    if (vec) {
+#pragma unroll
+      for (int i = 0; i < NP; ++i) {
+        const int c = tid + 256 * i;
+        *reinterpret_cast<uint4*>(ps + c / (DPM / VF) * LDP + c % (DPM / VF) * VF) = pr[i];
+      }
+    } else {
+      for (int i = tid; i < kFsTok * DPM; i += 256) {
+        const int k = i / DPM, f = i % DPM;
+        ps[k * LDP + f] = t0 + k < rows && f < D ? phi[(int64_t)(t0 + k) * D + f] : (TF)0.0f;
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int c = tid + 256 * i;
+      if (c < kFsTok * DH / VT) *reinterpret_cast<uint4*>(vs + c / (DH / VT) * LDV + c % (DH / VT) * VT) = vr[i];
+    }
+    __syncthreads();
+    if (t0 + kFsTok < rows) load(t0 + kFsTok);
+    Operand<TF, T> af[FBW];
+#pragma unroll
+    for (int f = 0; f < FBW; ++f) {
+      const int fb = wave + 4 * f;
+      Frag<TF> x;
+      load_tr4(x, 0, ps, LDP, 8 * g, 16 * fb, lane);
+      load_tr4(x, 4, ps, LDP, 8 * g + 4, 16 * fb, lane);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) z[f] += x.get(e);
+      set_operand(af[f], x);
+    }
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) {
+      Frag<T> y;
+      load_tr4(y, 0, vs, LDV, 8 * g, 16 * cb, lane);
+      load_tr4(y, 4, vs, LDV, 8 * g + 4, 16 * cb, lane);
+      Operand<T, TF> bf;
+      set_operand(bf, y);
+#pragma unroll
+      for (int f = 0; f < FBW; ++f)
+        if (f == 0 || 16 * (wave + 4 * f) < D) mma(acc[f][cb], af[f], bf);  // (uniform)
+    }
+  }
+  float* S = a.state + blockIdx.x * (int64_t)D * (DH + 1);
+#pragma unroll
+  for (int f = 0; f < FBW; ++f) {
+    z[f] += __shfl_xor(z[f], 16, kWave);
+    z[f] += __shfl_xor(z[f], 32, kWave);
+    const int f0 = 16 * (wave + 4 * f);
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (f0 + 4 * g + j < D) S[(f0 + 4 * g + j) * DH + 16 * cb + r] = acc[f][cb][j];
+    if (g == 0 && f0 + r < D) S[D * DH + f0 + r] = z[f];
+  }
+}
+
+// ---------------------------------------------------------------------------
+// the pieces of every head summed into its first, in order
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void feat_total_kernel(float* state, int64_t heads, int pieces, int64_t elems) {
+  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (i >= heads * elems) return;
+  const int64_t h = i / elems, e = i - h * elems;
+  float* p = state + h * pieces * elems + e;
+  float s = 0.0f;
+  int c = 0;
+  for (; c + 8 <= pieces; c += 8) {
+    float v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = p[(c + k) * elems];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) s += v[k];
+  }
+  for (; c < pieces; ++c) s += p[c * elems];
+  *p = s;
+}
+
+// ---------------------------------------------------------------------------
+// Readout, transposed: [num | den]^T = [S | z]^T phi(Q)^T, so that a lane reads 8
+// consecutive features of one query straight into a B operand and ends with 4
+// consecutive outputs of it.  [S | z]^T waits in LDS as A fragments (z as one block of 16
+// equal rows: every lane then holds its query's den), up to four value blocks per
+// workgroup; a fragment read serves NTL tiles of 16 queries.  Bound by the read of phi(Q).
+// ---------------------------------------------------------------------------
+constexpr int kFrThreads = 512;
+
+template <typename TF>
+constexpr int readout_tiles() { return sizeof(TF) == 2 ? 2 : 1; }
+
+template <typename TF, typename T, int DH, int KB>
+__global__ __launch_bounds__(kFrThreads) void feat_readout_kernel(FeatArgs a) {
+  constexpr int CB = DH / 16, CBW = CB < 4 ? CB : 4, NTL = readout_tiles<TF>();
+  using AOp = Operand<float, TF>;
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  AOp* frags = reinterpret_cast<AOp*>(lds);  // [kb][CBW + 1][lane]
+  const int64_t per_head = (a.n + a.tokens - 1) / a.tokens;
+  const int64_t head = blockIdx.x / per_head;
+  const int64_t first = (blockIdx.x - head * per_head) * a.tokens;
+  const int64_t last = min(a.n, first + a.tokens);
+  const int c0 = blockIdx.y * CBW * 16;
+  const int D = a.D, tid = threadIdx.x, lane = tid % kWave, wave = wave_id();
+  const int g = lane / 16, r = lane % 16;
+  const int kbs = (D + 31) / 32;
+  const float* S = a.state + head * a.pieces * (int64_t)D * (DH + 1);
+  for (int i = tid; i < kbs * (CBW + 1) * kWave; i += kFrThreads) {
+    const int ln = i % kWave, blk = i / kWave % (CBW + 1), kb = i / (kWave * (CBW + 1));
+    const int k0 = 32 * kb + 8 * (ln / 16), c = c0 + 16 * blk + ln % 16;
+    Frag<float> f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int k = k0 + e;
+      f.v[e] = k < D ? (blk < CBW ? S[k * DH + c] : S[D * DH + k]) : 0.0f;
+    }
+    set_operand(frags[i], f);
+  }
+  __syncthreads();
+  const TF* phi = reinterpret_cast<const TF*>(a.phiq) + head * a.n * D;
+  T* out = reinterpret_cast<T*>(a.out) + head * a.n * DH;
+  const bool vec = D % Vec16<TF>::N == 0 && D % 8 == 0;  // (uniform)
+  for (int64_t t0 = first + wave * 16 * NTL; t0 < last; t0 += (kFrThreads / kWave) * 16 * NTL) {
+    Frag<TF> q[NTL][KB];
+#pragma unroll
+    for (int i = 0; i < NTL; ++i) {
+      const int64_t t = t0 + 16 * i + r;
+      const TF* row = phi + t * D;
+#pragma unroll
+      for (int kb = 0; kb < KB; ++kb) {
+        const int k0 = 32 * kb + 8 * g;
+        q[i][kb].zero();
+        if (vec) {
+          if (t < last && k0 < D) load8(q[i][kb], row + k0);
+        } else if (t < last) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            if (k0 + e < D) q[i][kb].v[e] = row[k0 + e];
+        }
+      }
+    }
+    f32x4 acc[NTL][CBW + 1];
+#pragma unroll
+    for (int i = 0; i < NTL; ++i)
+#pragma unroll
+      for (int b = 0; b <= CBW; ++b) acc[i][b] = zero4();
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) {
+      if (kb > 0 && kb >= kbs) break;  // (uniform)
+#pragma unroll
+      for (int b = 0; b <= CBW; ++b) {
+        const AOp& f = frags[(kb * (CBW + 1) + b) * kWave + lane];
+#pragma unroll
+        for (int i = 0; i < NTL; ++i) mma(acc[i][b], f, q[i][kb]);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < NTL; ++i) {
+      const int64_t t = t0 + 16 * i + r;
+      if (t >= last) continue;
+      const float inv = 1.0f / (acc[i][CBW][0] + a.eps);
+      T* o = out + t * DH + c0 + 4 * g;
+#pragma unroll
+      for (int b = 0; b < CBW; ++b)
+        store4(o + 16 * b, acc[i][b][0] * inv, acc[i][b][1] * inv, acc[i][b][2] * inv, acc[i][b][3] * inv);
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// statistics into (or added to) the caller's S and z
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void feat_export_kernel(const float* __restrict__ state, int64_t head_stride,
+                                                          float* __restrict__ S, float* __restrict__ z, int64_t heads,
+                                                          int D, int d, int accumulate) {
+  const int64_t per = (int64_t)D * (d + 1);
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < heads * per;
+       i += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t h = i / per, e = i - h * per;
+    const float v = state[h * head_stride + e];
+    float* dst = e < (int64_t)D * d ? S + h * D * d + e : z + h * D + (e - (int64_t)D * d);
+    *dst = accumulate ? *dst + v : v;
+  }
+}
+
+template <typename TF, typename T, int DH>
+hipError_t state_launch(const FeatArgs& a, hipStream_t s) {
+  const dim3 grid((unsigned)(a.heads * a.pieces)), block(256);
+  if (a.D <= 64) hipLaunchKernelGGL((feat_state_kernel<TF, T, DH, 1>), grid, block, 0, s, a);
+  else if (a.D <= 128) hipLaunchKernelGGL((feat_state_kernel<TF, T, DH, 2>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((feat_state_kernel<TF, T, DH, 4>), grid, block, 0, s, a);
+  return hipGetLastError();
+}
+
+template <auto Kernel>
+hipError_t readout_launch_k(dim3 grid, size_t lds, const FeatArgs& a, hipStream_t s) {
+  if (lds > (64u << 10)) {
+    static const hipError_t set = hipFuncSetAttribute(reinterpret_cast<const void*>(Kernel),
+                                                      hipFuncAttributeMaxDynamicSharedMemorySize, 160 << 10);
+    if (set != hipSuccess) return set;
+  }
+  hipLaunchKernelGGL(Kernel, grid, dim3(kFrThreads), lds, s, a);
+  return hipGetLastError();
+}
+
+template <typename TF, typename T, int DH>
+hipError_t readout_launch(const FeatArgs& args, hipStream_t s) {
+  constexpr int CB = DH / 16, CBW = CB < 4 ? CB : 4;
+  FeatArgs a = args;
+  // 256 tokens per pass of a workgroup's waves; more passes, up to four, as long as about
+  // two workgroups per CU remain (the fragments are set up once per workgroup)
+  const int64_t passes = a.heads * a.n / (512 * 256);
+  a.tokens = 256 * (int)std::max<int64_t>(1, std::min<int64_t>(4, passes));
+  const int64_t blocks = a.heads * ((a.n + a.tokens - 1) / a.tokens);
+  if (blocks > 0x7fffffff) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)blocks, (unsigned)(CB / CBW));
+  const size_t lds = (size_t)((a.D + 31) / 32) * (CBW + 1) * kWave * sizeof(Operand<float, TF>);
+  if (a.D <= 64) return readout_launch_k<feat_readout_kernel<TF, T, DH, 2>>(grid, lds, a, s);
+  if (a.D <= 128) return readout_launch_k<feat_readout_kernel<TF, T, DH, 4>>(grid, lds, a, s);
+  return readout_launch_k<feat_readout_kernel<TF, T, DH, 8>>(grid, lds, a, s);
+}
+
+// f(type tags) for the feature and value types, F::operator()<TF, T, DH>
+template <typename F>
+hipError_t by_type(Dt fdt, Dt vdt, int d, F f) {
+  auto by_d = [&](auto tf, auto t) {
+    using TF = decltype(tf);
+    using T = decltype(t);
+    switch (d) {
+      case 32: return f.template operator()<TF, T, 32>();
+      case 64: return f.template operator()<TF, T, 64>();
+      case 128: return f.template operator()<TF, T, 128>();
+      default: return hipErrorInvalidValue;
+    }
+  };
+  if (fdt == Dt::BF16) return vdt == Dt::BF16 ? by_d(__bf16(), __bf16()) : by_d(__bf16(), float());
+  return vdt == Dt::BF16 ? by_d(float(), __bf16()) : by_d(float(), float());
+}
+
+struct StateLaunch {
+  const FeatArgs& a;
+  hipStream_t s;
+  template <typename TF, typename T, int DH>
+  hipError_t operator()() const { return state_launch<TF, T, DH>(a, s); }
+};
+struct ReadoutLaunch {
+  const FeatArgs& a;
+  hipStream_t s;
+  template <typename TF, typename T, int DH>
+  hipError_t operator()() const { return readout_launch<TF, T, DH>(a, s); }
+};
+
+}  // namespace
+
+// Value widths of whole fragments, and feature counts up to four 16-feature blocks a wave.
+bool feat_supported(int d, int D) { return (d == 32 || d == 64 || d == 128) && D >= 1 && D <= 256; }
+
+hipError_t launch_feat_state(Dt fdt, Dt vdt, int d, const FeatArgs& a, hipStream_t s) {
+  if (a.heads * a.pieces > 0x7fffffff) return hipErrorInvalidValue;
+  return by_type(fdt, vdt, d, StateLaunch{a, s});
+}
+
+hipError_t launch_feat_total(int d, const FeatArgs& a, hipStream_t s) {
+  if (a.pieces == 1) return hipSuccess;
+  const int64_t elems = (int64_t)a.D * (d + 1);
+  hipLaunchKernelGGL(feat_total_kernel, dim3((unsigned)((a.heads * elems + 255) / 256)), dim3(256), 0, s, a.state,
+                     a.heads, a.pieces, elems);
+  return hipGetLastError();
+}
+
+hipError_t launch_feat_readout(Dt fdt, Dt vdt, int d, const FeatArgs& a, hipStream_t s) {
+  return by_type(fdt, vdt, d, ReadoutLaunch{a, s});
+}
+
+hipError_t launch_feat_export(int d, const FeatArgs& a, float* S, float* z, int accumulate, hipStream_t s) {
+  const int64_t elems = (int64_t)a.D * (d + 1);
+  const dim3 grid((unsigned)std::min<int64_t>((a.heads * elems + 255) / 256, 65536));
+  hipLaunchKernelGGL(feat_export_kernel, grid, dim3(256), 0, s, a.state, a.pieces * elems, S, z, a.heads, a.D, d,
+                     accumulate);
+  return hipGetLastError();
+}
+
+}  // namespace luna

@@ -14,61 +14,11 @@
 #include "luna_device.hpp"
 #include "luna_grad.hpp"
 #include "luna_kernels.hpp"
+#include "luna_split.hpp"
 
 namespace luna {
 
 namespace {
-
-// fp32 values as three bf16 fragments whose sum is the value to 2^-24 (products with a
-// bf16 operand are then as exact as fp32 ones).
-struct Split3 {
-  Frag<__bf16> p[3];
-};
-__device__ __forceinline__ void split3(Split3& s, const float (&x)[8]) {
-  float r[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) r[e] = x[e];
-#pragma unroll
-  for (int k = 0; k < 3; ++k)
-#pragma unroll
-    for (int e = 0; e < 8; e += 2) {
-      s.p[k].set2(e, r[e], r[e + 1]);
-      if (k < 2) {
-        r[e] -= s.p[k].get(e);
-        r[e + 1] -= s.p[k].get(e + 1);
-      }
-    }
-}
-
-// c += a x with a in the call's type and x in fp32
-__device__ __forceinline__ void mma_ax(f32x4& c, const Frag<__bf16>& a, const Split3& x) {
-#pragma unroll
-  for (int k = 2; k >= 0; --k) mma(c, a, x.p[k]);
-}
-// c += x b
-__device__ __forceinline__ void mma_xb(f32x4& c, const Split3& x, const Frag<__bf16>& b) {
-#pragma unroll
-  for (int k = 2; k >= 0; --k) mma(c, x.p[k], b);
-}
-
-// an fp32 operand next to one of type T
-template <typename T>
-struct Wide;
-template <>
-struct Wide<__bf16> {
-  Split3 s;
-  __device__ __forceinline__ void set(const float (&x)[8]) { split3(s, x); }
-};
-template <>
-struct Wide<float> {
-  Frag<float> s;
-  __device__ __forceinline__ void set(const float (&x)[8]) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) s.v[e] = x[e];
-  }
-};
-__device__ __forceinline__ void mma_ax(f32x4& c, const Frag<float>& a, const Frag<float>& x) { mma(c, a, x); }
-__device__ __forceinline__ void mma_xb(f32x4& c, const Frag<float>& x, const Frag<float>& b) { mma(c, x, b); }
 
 __device__ __forceinline__ Frag<float> widen(const Frag<__bf16>& f) {
   Frag<float> w;
@@ -272,12 +222,15 @@ __global__ __launch_bounds__((map_threads<T, DH, L, PACK>())) void map_bwd_kerne
         }
       }
       if (half == 0 && mb + 1 < MB) continue;  // (uniform) the next block fills the other half
-      Wide<T> dw;
-      dw.set(du);
+      Frag<float> df;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) df.v[e] = du[e];
+      Operand<float, T> dw;
+      set_operand(dw, df);
 #pragma unroll
       for (int i = 0; i < NT; ++i)
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb) mma_ax(dx[i][cb], wt[PACK ? i : mb / 2][cb][lane], dw.s);
+        for (int cb = 0; cb < CB; ++cb) mma(dx[i][cb], wt[PACK ? i : mb / 2][cb][lane], dw);
     }
     if (!want_dx) continue;
     T* dX = reinterpret_cast<T*>(key ? a.dxk : a.dxq);
@@ -331,13 +284,13 @@ __global__ __launch_bounds__(256) void map_dw_kernel(MapBwd a) {
     const int rows = (int)min((int64_t)kDwRows, rr.rows - t0);
     const T* X = reinterpret_cast<const T*>(key ? a.xk : a.xq) + base * DH;
     const float* du = (key ? a.duk : a.duq) + base * M;
-    float v[2][8];
+    Frag<float> v[2];
 #pragma unroll
     for (int x = 0; x < 2; ++x)
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const int p = pb + 16 * x + r, k = 8 * g + e;
-        v[x][e] = p < M && k < rows ? du[(int64_t)k * M + p] : 0.0f;
+        v[x].v[e] = p < M && k < rows ? du[(int64_t)k * M + p] : 0.0f;
       }
     // the tile's x rows (zero past the last, so that padding rows add 0)
     constexpr int PER = kDwRows * DH / V / kWave;
@@ -353,12 +306,12 @@ __global__ __launch_bounds__(256) void map_dw_kernel(MapBwd a) {
       *reinterpret_cast<uint4*>(xs + k * LD + q * V) = xv[i];
     }
     __builtin_amdgcn_wave_barrier();
-    Wide<T> w[2];
+    Operand<float, T> w[2];
 #pragma unroll
     for (int x = 0; x < 2; ++x) {
-      w[x].set(v[x]);
+      set_operand(w[x], v[x]);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) db[x] += v[x][e];
+      for (int e = 0; e < 8; ++e) db[x] += v[x].v[e];
     }
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb) {
@@ -367,7 +320,7 @@ __global__ __launch_bounds__(256) void map_dw_kernel(MapBwd a) {
       load_tr4(xf, 4, xs, LD, 8 * g + 4, 16 * cb, lane);
 #pragma unroll
       for (int x = 0; x < 2; ++x)
-        if (pb + 16 * x < M) mma_xb(acc[x][cb], w[x].s, xf);  // (uniform)
+        if (pb + 16 * x < M) mma(acc[x][cb], w[x], xf);  // (uniform)
     }
     __builtin_amdgcn_wave_barrier();
   }

@@ -170,3 +170,20 @@ def test_features_of_the_base_map():
     f32 = torch.float32
     out = to_np(luna.attn_fwd_features(luna.featuremap(Qt, pt, f32), luna.featuremap(Kt, pt, f32), Vt))
     assert_close(out, to_np(luna.attn_fwd(Qt, Kt, Vt, pt)), "bf16", "features vs fused")
+
+
+@pytest.mark.parametrize("pdt,dt,d,D,n", [
+    ("bf16", "bf16", 32, 5, 31), ("bf16", "bf16", 64, 64, 512), ("bf16", "bf16", 64, 72, 513), ("bf16", "f32", 64, 128, 33),
+    ("bf16", "bf16", 128, 256, 1100), ("f32", "bf16", 32, 130, 97), ("f32", "f32", 128, 250, 600), ("f32", "f32", 64, 16, 1),
+    ("f32", "bf16", 128, 129, 257), ("bf16", "f32", 128, 200, 40)])
+def test_attn_features_noncausal_edges(pdt, dt, d, D, n):
+    """Non-causal attention from features of either type beside values of either type, at
+    the edges of the 32-token tiles, 512-token pieces and 16- and 64-feature blocks, with
+    feature rows that are not whole 16-byte pieces."""
+    say(f"features non-causal phi={pdt} {dt} d={d} D={D} n={n}")
+    rng = np.random.default_rng(1000 * D + n)
+    fq, fqr = _upload_rounded(np.abs(rng.standard_normal((2, 3, n, D))), pdt)
+    fk, fkr = _upload_rounded(np.abs(rng.standard_normal((2, 3, n, D))), pdt)
+    V, Vr = _upload_rounded(rng.standard_normal((2, 3, n, d)), dt)
+    out = to_np(luna.attn_fwd_features(fq, fk, V))
+    assert_close(out, VAR.attn_from_features(fqr, fkr, Vr), dt, "out")
