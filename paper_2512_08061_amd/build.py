@@ -22,7 +22,8 @@ LIB = os.path.join(PKG, "libluna.so")
 
 SOURCES = ["luna_prepare.hip", "luna_featuremap.hip", "luna_noncausal.hip", "luna_causal.hip", "luna_stream.hip",
            "luna_variants.hip", "luna_variants_bf16.hip", "luna_distill.hip",
-           "luna_backward.hip", "luna_map_backward.hip", "luna_features.hip", "luna_api.cpp"]
+           "luna_backward.hip", "luna_map_backward.hip", "luna_features.hip", "luna_chunk_query.hip", "luna_chunk_key.hip",
+           "luna_api.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 

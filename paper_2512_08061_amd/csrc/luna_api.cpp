@@ -12,6 +12,7 @@
 #include <mutex>
 #include <string>
 
+#include "luna_chunk.hpp"
 #include "luna_features.hpp"
 #include "luna_grad.hpp"
 #include "luna_kernels.hpp"
@@ -72,10 +73,10 @@ struct Layout {
   size_t tables = 0, partial = 0, frags = 0, total = 0;
   size_t phiq = 0, phik = 0;  // streaming step: features of the new queries and keys (fp32)
   size_t zcopy = 0;           // streaming step: z as it was before the call
-  // backward pass: [V | 1], [num | den] then [dnum | dden], per-chunk states and their
-  // gradients, intra-chunk P and R (causal), feature gradients, dV in fp32 (bf16
-  // calls), per-workgroup parameter partials, their fp64 sums and moment prefixes
-  size_t vx = 0, y = 0, sx = 0, dsx = 0, pm = 0, rm = 0, dphiq = 0, dphik = 0, dvtmp = 0;
+  // backward pass: per-piece states and their gradients, per query [1 / den, dden],
+  // feature gradients, per-workgroup parameter partials, their fp64 sums and moment
+  // prefixes; fp32 forward of given features by GEMMs: [V | 1], [num | den - eps], states, P
+  size_t sx = 0, dsx = 0, wq = 0, dphiq = 0, dphik = 0, vx = 0, y = 0, pm = 0;
   size_t duq = 0, duk = 0, dwp = 0;  // feature-map backward
   size_t bpart = 0, sum = 0, pre = 0;
   size_t dstats = 0;  // distillation: per query row the softmax max and sum and the kernel row sum
@@ -86,21 +87,28 @@ struct Layout {
   int pieces = 0, piece_chunks = 0;
   int staged = 0, sa = 0, sb = 0;  // staged causal scan: chunks of the first scanned part and of the state-only part
   int feat = 0;     // non-causal attention from given features in their own type
-  int generic = 0;  // forward in fp32 GEMMs and scans (shapes without a fused kernel)
+  int generic = 0;  // forward in fp32 (shapes without a fused kernel),
+  int chunked = 0;  // by the chunk kernels; else by GEMMs and scans
   int given = 0;    // causal: features mapped beforehand (bf16, in phiq / phik), then the scan kernel
 };
 
-// Buffers of the forward pass in fp32 GEMMs (the forward of shapes without a fused
-// kernel, and the recomputation that starts the backward pass): features of the keys
-// (and queries), [V | 1], [num | den - eps] and the per-chunk states, plus P for the
-// causal form.  Causal chunks are the 64-token chunks of the scan; the non-causal form
-// cuts its sums over tokens into 512-token pieces, for parallelism only.
+// Buffers of the forward pass in fp32 (the forward of shapes without a fused kernel, and
+// the start of the backward pass): features of the keys (and queries) and the statistics of
+// pieces of the tokens.  Causal pieces are a few tiles long (luna_chunk.hpp), the
+// non-causal form cuts its sums over tokens into 512-token pieces, for parallelism only.
+// Widths that only given features have take fp32 GEMMs over 64-token chunks: [V | 1],
+// [num | den - eps] and the per-chunk states, plus P for the causal form.
 // (features: the buffers for fp32 features, or none when the caller's are used)
 luna_status plan_f32_buffers(int64_t heads, int64_t n, int d, int D, bool causal, bool queries, bool features,
                              Layout* lay, size_t* off) {
   lay->chunk = causal ? 64 : 512;
-  const int64_t nch = (n + lay->chunk - 1) / lay->chunk;
+  int64_t nch = (n + lay->chunk - 1) / lay->chunk;
   if (nch > 65535) return fail(LUNA_ERR_UNSUPPORTED, causal ? "n must be <= 65535 * 64" : "n must be <= 65535 * 512");
+  lay->chunked = luna::chunk_supported(d, D);
+  if (lay->chunked && causal) {
+    lay->chunk = luna::kChunkPiece;
+    nch = (n + lay->chunk - 1) / lay->chunk;
+  }
   lay->nch = (int)nch;
   const size_t rows = (size_t)heads * (size_t)n, states = (size_t)heads * lay->nch;
   auto take = [&](size_t& at, size_t bytes) {
@@ -109,6 +117,10 @@ luna_status plan_f32_buffers(int64_t heads, int64_t n, int d, int D, bool causal
   };
   if (queries && features) take(lay->phiq, rows * D * 4);
   if (features) take(lay->phik, rows * D * 4);
+  if (lay->chunked) {
+    take(lay->sx, states * (size_t)luna::feat_elems(d, D) * 4);
+    return LUNA_OK;
+  }
   take(lay->vx, rows * (d + 1) * 4);
   if (queries) take(lay->y, rows * (d + 1) * 4);
   take(lay->sx, states * D * (d + 1) * 4);
@@ -306,11 +318,10 @@ luna_status plan(const Problem& pb, Layout* lay) {
       at = off;
       off = align256(off + bytes);
     };
-    take(lay->dsx, states * D * (d + 1) * 4);
-    if (causal) take(lay->rm, states * 64 * 64 * 4);
+    take(lay->dsx, states * (size_t)luna::feat_elems(d, D) * 4);
+    take(lay->wq, rows * 2 * 4);
     take(lay->dphiq, rows * D * 4);
     take(lay->dphik, rows * D * 4);
-    if (pb.dt == LUNA_BF16) take(lay->dvtmp, rows * d * 4);
     plan_phi_backward(pb, lay, &off);
   } else if (pb.op == kOpDistill || pb.op == kOpDistillGrads) {
     const int D = M * L;
@@ -426,7 +437,7 @@ luna_status enqueue_f32_attention(luna::Dt vdt, int64_t heads64, int64_t n, int 
   const int64_t sh = (int64_t)nch * st_el;  // head stride of the per-chunk states
   LUNA_TRY(gemm(phik, nD, (int64_t)C * D, 1, D, vx, nE, (int64_t)C * E, E, 1, sx, sh, st_el, E, 1, D, E, C, 0, 0, 1,
                 0, 0), "state GEMM");
-  LUNA_TRY(luna::launch_bwd_scan(sx, heads, nch, st_el, causal ? 0 : 2, s), "state scan");
+  LUNA_TRY(luna::launch_bwd_scan(sx, heads, nch, st_el, !causal, s), "state scan");
   if (!phiq) return LUNA_OK;
   LUNA_TRY(gemm(phiq, nD, (int64_t)C * D, D, 1, sx, sh, st_el, E, 1, y, nE, (int64_t)C * E, E, 1, C, E, D, 1, 0, 0,
                 0, 0), "readout GEMM");
@@ -472,46 +483,95 @@ luna_status enqueue_feat_attention(luna::Dt fdt, luna::Dt vdt, int64_t heads, in
   a.state = reinterpret_cast<float*>(w + lay.sx);
   a.heads = heads;
   a.n = n;
+  a.elems = luna::feat_elems(d, D);
   a.D = D;
   a.piece = lay.chunk;
   a.pieces = lay.nch;
   a.eps = eps;
   hipError_t e = luna::launch_feat_state(fdt, vdt, d, a, s);
   if (e != hipSuccess) return hip_fail(e, "state kernel launch");
-  if ((e = luna::launch_feat_total(d, a, s)) != hipSuccess) return hip_fail(e, "state sum launch");
+  if ((e = luna::launch_feat_total(a, s)) != hipSuccess) return hip_fail(e, "state sum launch");
   if (!phiq) return LUNA_OK;
   e = luna::launch_feat_readout(fdt, vdt, d, a, s);
   return e == hipSuccess ? LUNA_OK : hip_fail(e, "readout kernel launch");
 }
 
-// The forward pass in fp32: features of the keys (and queries) by the feature-map
-// kernel, then enqueue_f32_attention.  Q == nullptr: the state only.
-luna_status enqueue_f32_forward(const Problem& pb, uint8_t* w, const Layout& lay, const void* Q, const void* K,
-                                const void* V, bool causal, hipStream_t s) {
-  const luna::Dt dt = pb.dt == LUNA_BF16 ? luna::Dt::BF16 : luna::Dt::F32;
-  const int D = pb.p->M * pb.p->L, dd = (int)pb.d;
-  float* phiq = reinterpret_cast<float*>(w + lay.phiq);
-  float* phik = reinterpret_cast<float*>(w + lay.phik);
-  const luna_status st = enqueue_f32_features(pb, w, lay, Q, K, s);
-  if (st != LUNA_OK) return st;
-  return enqueue_f32_attention(dt, pb.B * pb.H, pb.n, dd, D, w, lay, Q ? phiq : nullptr, phik, V, causal, s);
+// Arguments of the chunk kernels: statistics at `state`, rows x with values u, columns y
+// with values v.
+luna::ChunkArgs chunk_args(int64_t heads, int64_t n, int d, int D, const Layout& lay, bool causal, const float* x,
+                           const void* u, const float* y, const void* v, const float* state, float eps) {
+  luna::ChunkArgs a{};
+  a.x = x;
+  a.u = u;
+  a.y = y;
+  a.v = v;
+  a.state = state;
+  a.heads = heads;
+  a.n = n;
+  a.elems = luna::feat_elems(d, D);
+  a.D = D;
+  a.piece = lay.chunk;
+  a.pieces = lay.nch;
+  a.causal = causal;
+  a.eps = eps;
+  return a;
 }
 
-// The generic forward: the fp32 forward, then out = num / den in the call's dtype.
+// Statistics of every piece (weighted by w when given) into `state`, then what the chunk
+// kernels start from: the exclusive prefix (suffix) over pieces, or the total.
+luna_status enqueue_chunk_state(luna::Dt vdt, int64_t heads, int64_t n, int d, int D, const Layout& lay, bool causal,
+                                bool suffix, const float* phi, const void* V, const float* wt, float* state,
+                                hipStream_t s) {
+  luna::FeatArgs a{};
+  a.phik = phi;
+  a.v = V;
+  a.w = wt;
+  a.state = state;
+  a.heads = heads;
+  a.n = n;
+  a.elems = luna::feat_elems(d, D);
+  a.D = D;
+  a.piece = lay.chunk;
+  a.pieces = lay.nch;
+  hipError_t e = luna::launch_feat_state(luna::Dt::F32, vdt, d, a, s);
+  if (e != hipSuccess) return hip_fail(e, "state kernel launch");
+  e = causal ? luna::launch_chunk_scan(state, heads, lay.nch, a.elems, suffix, s) : luna::launch_feat_total(a, s);
+  return e == hipSuccess ? LUNA_OK : hip_fail(e, "state scan launch");
+}
+
+// The causal forward from given fp32 features: out = num / den in the value type.
+luna_status enqueue_f32_causal(luna::Dt vdt, int64_t heads, int64_t n, int d, int D, uint8_t* w, const Layout& lay,
+                               const float* phiq, const float* phik, const void* V, float eps, void* out,
+                               hipStream_t s) {
+  hipError_t e;
+  if (!lay.chunked) {
+    const luna_status st = enqueue_f32_attention(vdt, heads, n, d, D, w, lay, phiq, phik, V, true, s);
+    if (st != LUNA_OK) return st;
+    e = luna::launch_fwd_out(vdt, reinterpret_cast<const float*>(w + lay.y), out, heads * n, d, eps, s);
+    return e == hipSuccess ? LUNA_OK : hip_fail(e, "output kernel launch");
+  }
+  float* state = reinterpret_cast<float*>(w + lay.sx);
+  const luna_status st = enqueue_chunk_state(vdt, heads, n, d, D, lay, true, false, phik, V, nullptr, state, s);
+  if (st != LUNA_OK) return st;
+  luna::ChunkArgs a = chunk_args(heads, n, d, D, lay, true, phiq, nullptr, phik, V, state, eps);
+  a.out = out;
+  e = luna::launch_chunk_query(vdt, d, a, s);
+  return e == hipSuccess ? LUNA_OK : hip_fail(e, "chunk kernel launch");
+}
+
+// The generic forward: the features in fp32, then attention from them.
 luna_status enqueue_generic_attn(const Problem& pb, uint8_t* w, const Layout& lay, const void* Q, const void* K,
                                  const void* V, float eps, void* out, bool causal, hipStream_t s) {
-  luna_status st;
-  if (!causal) {
-    if ((st = enqueue_f32_features(pb, w, lay, Q, K, s)) != LUNA_OK) return st;
-    luna::FeatArgs a{};
-    return enqueue_feat_attention(luna::Dt::F32, pb.dt == LUNA_BF16 ? luna::Dt::BF16 : luna::Dt::F32, pb.B * pb.H, pb.n,
-                                  (int)pb.d, pb.p->M * pb.p->L, w, lay, w + lay.phiq, w + lay.phik, V, eps, out, &a, s);
-  }
-  if ((st = enqueue_f32_forward(pb, w, lay, Q, K, V, causal, s)) != LUNA_OK) return st;
-  const hipError_t e = luna::launch_fwd_out(pb.dt == LUNA_BF16 ? luna::Dt::BF16 : luna::Dt::F32,
-                                            reinterpret_cast<const float*>(w + lay.y), out, pb.B * pb.H * pb.n,
-                                            (int)pb.d, eps, s);
-  return e == hipSuccess ? LUNA_OK : hip_fail(e, "output kernel launch");
+  const luna_status st = enqueue_f32_features(pb, w, lay, Q, K, s);
+  if (st != LUNA_OK) return st;
+  const luna::Dt dt = pb.dt == LUNA_BF16 ? luna::Dt::BF16 : luna::Dt::F32;
+  const int64_t heads = pb.B * pb.H;
+  const int D = pb.p->M * pb.p->L, d = (int)pb.d;
+  const float* phiq = reinterpret_cast<const float*>(w + lay.phiq);
+  const float* phik = reinterpret_cast<const float*>(w + lay.phik);
+  if (causal) return enqueue_f32_causal(dt, heads, pb.n, d, D, w, lay, phiq, phik, V, eps, out, s);
+  luna::FeatArgs a{};
+  return enqueue_feat_attention(luna::Dt::F32, dt, heads, pb.n, d, D, w, lay, phiq, phik, V, eps, out, &a, s);
 }
 
 // Scratch of luna_attn_fwd_causal_noalloc: one array per device, part of the code
@@ -606,7 +666,7 @@ luna_status plan_features(luna_dtype phi_dtype, luna_dtype dtype, int64_t B, int
     if (pieces > 65535) return fail(LUNA_ERR_UNSUPPORTED, "n must be <= 65535 * 512");
     lay->nch = (int)pieces;
     lay->sx = off;
-    off = align256(off + (size_t)heads * lay->nch * (size_t)D * (size_t)(d + 1) * 4);
+    off = align256(off + (size_t)heads * lay->nch * (size_t)luna::feat_elems(d, D) * 4);
   } else {
     lay->generic = 1;
     luna_status st = plan_f32_buffers(heads, n, (int)d, (int)D, causal != 0, true, phi_dtype == LUNA_BF16, lay, &off);
@@ -834,8 +894,8 @@ luna_status luna_attn_fwd_features(const void* phiQ, const void* phiK, luna_dtyp
     fq = q32;
     fk = k32;
   }
-  if ((st = enqueue_f32_attention(vdt, heads, n, (int)d, (int)D, w, lay, fq, fk, V, causal != 0, s)) != LUNA_OK)
-    return st;
+  if (causal) return enqueue_f32_causal(vdt, heads, n, (int)d, (int)D, w, lay, fq, fk, V, eps, out, s);
+  if ((st = enqueue_f32_attention(vdt, heads, n, (int)d, (int)D, w, lay, fq, fk, V, false, s)) != LUNA_OK) return st;
   e = luna::launch_fwd_out(vdt, reinterpret_cast<const float*>(w + lay.y), out, heads * n, (int)d, eps, s);
   return e == hipSuccess ? LUNA_OK : hip_fail(e, "output kernel launch");
 }
@@ -1152,55 +1212,29 @@ luna_status luna_attn_bwd(const void* Q, const void* K, const void* V, const voi
   uint8_t* w = static_cast<uint8_t*>(ws);
   if ((st = enqueue_prepare(pb, w, lay, s)) != LUNA_OK) return st;
   const luna::Dt dt = dtype == LUNA_BF16 ? luna::Dt::BF16 : luna::Dt::F32;
-  const int M = p->M, L = p->L, D = M * L, dd = (int)d, E = dd + 1;
-  const int heads = (int)(B * H), C = lay.chunk, nch = lay.nch;
-  const int64_t nD = n * D, nE = n * E, st_el = (int64_t)D * E, cc = (int64_t)C * C;
-  float* phiq = reinterpret_cast<float*>(w + lay.phiq);
-  float* phik = reinterpret_cast<float*>(w + lay.phik);
-  float* vx = reinterpret_cast<float*>(w + lay.vx);
-  float* y = reinterpret_cast<float*>(w + lay.y);
+  const int D = p->M * p->L, dd = (int)d;
+  const int64_t heads = B * H;
+  const float* phiq = reinterpret_cast<const float*>(w + lay.phiq);
+  const float* phik = reinterpret_cast<const float*>(w + lay.phik);
   float* sx = reinterpret_cast<float*>(w + lay.sx);
   float* dsx = reinterpret_cast<float*>(w + lay.dsx);
-  float* pm = reinterpret_cast<float*>(w + lay.pm);
-  float* rm = reinterpret_cast<float*>(w + lay.rm);
-  float* dphiq = reinterpret_cast<float*>(w + lay.dphiq);
-  float* dphik = reinterpret_cast<float*>(w + lay.dphik);
-  float* dvf = dt == luna::Dt::BF16 ? reinterpret_cast<float*>(w + lay.dvtmp) : static_cast<float*>(dV);
-  hipError_t e;
-#define LUNA_TRY(expr, what) \
-  if ((e = (expr)) != hipSuccess) return hip_fail(e, what)
-  // the forward pass in fp32: features, [V | 1], states, [num | den - eps] (and P)
-  if ((st = enqueue_f32_forward(pb, w, lay, Q, K, V, causal != 0, s)) != LUNA_OK) return st;
-  const ChunkGemm gemm{heads, nch, C, (int)n, s};
-  const int64_t sh = (int64_t)nch * st_el;  // head stride of the per-chunk states
-  LUNA_TRY(luna::launch_bwd_g(dt, y, dO, (int64_t)heads * n, dd, eps, s), "denominator kernel launch");
-  // dphi(Q_c) = G_c [S_c | z_c]^T (+ R_c phi(K_c), R_c = tril(G_c [V_c | 1]^T))
-  LUNA_TRY(gemm(y, nE, (int64_t)C * E, E, 1, sx, sh, st_el, 1, E, dphiq, nD, (int64_t)C * D, D, 1, C, D, E, 1, 0, 0,
-                0, 0), "dphi(Q) GEMM");
-  if (causal) {
-    LUNA_TRY(gemm(y, nE, (int64_t)C * E, E, 1, vx, nE, (int64_t)C * E, 1, E, rm, nch * cc, cc, C, 1, C, C, E, 1, 1, 0,
-                  1, 0), "R GEMM");
-    LUNA_TRY(gemm(rm, nch * cc, cc, C, 1, phik, nD, (int64_t)C * D, D, 1, dphiq, nD, (int64_t)C * D, D, 1, C, D, C, 1,
-                  0, 1, 0, 1), "dphi(Q) intra-chunk GEMM");
-  }
-  // per-chunk [dS | dz] = phi(Q_c)^T G_c, then exclusive suffix over chunks (causal)
-  LUNA_TRY(gemm(phiq, nD, (int64_t)C * D, 1, D, y, nE, (int64_t)C * E, E, 1, dsx, sh, st_el, E, 1, D, E, C, 0, 0, 1,
-                0, 0), "state-gradient GEMM");
-  LUNA_TRY(luna::launch_bwd_scan(dsx, heads, nch, st_el, causal ? 1 : 2, s), "state-gradient scan");
-  // dphi(K_c) = [V_c | 1] [dS_c | dz_c]^T (+ R_c^T phi(Q_c)); dV_c = phi(K_c) dS_c (+ P_c^T dnum_c)
-  LUNA_TRY(gemm(vx, nE, (int64_t)C * E, E, 1, dsx, sh, st_el, 1, E, dphik, nD, (int64_t)C * D, D, 1, C, D, E, 1, 0, 0,
-                0, 0), "dphi(K) GEMM");
-  LUNA_TRY(gemm(phik, nD, (int64_t)C * D, D, 1, dsx, sh, st_el, E, 1, dvf, n * dd, (int64_t)C * dd, dd, 1, C, dd, D, 1,
-                0, 0, 0, 0), "dV GEMM");
-  if (causal) {
-    LUNA_TRY(gemm(rm, nch * cc, cc, 1, C, phiq, nD, (int64_t)C * D, D, 1, dphik, nD, (int64_t)C * D, D, 1, C, D, C, 1,
-                  0, 1, 0, 1), "dphi(K) intra-chunk GEMM");
-    LUNA_TRY(gemm(pm, nch * cc, cc, 1, C, y, nE, (int64_t)C * E, E, 1, dvf, n * dd, (int64_t)C * dd, dd, 1, C, dd, C, 1,
-                  0, 1, 0, 1), "dV intra-chunk GEMM");
-  }
-  if (dt == luna::Dt::BF16) LUNA_TRY(luna::launch_bwd_convert(dt, dvf, dV, (int64_t)heads * n * dd, s), "dV convert");
+  float* wq = reinterpret_cast<float*>(w + lay.wq);
+  if ((st = enqueue_f32_features(pb, w, lay, Q, K, s)) != LUNA_OK) return st;
+  // [S | z]; 1 / den, dden and dphi(Q)
+  if ((st = enqueue_chunk_state(dt, heads, n, dd, D, lay, causal, false, phik, V, nullptr, sx, s)) != LUNA_OK) return st;
+  luna::ChunkArgs a = chunk_args(heads, n, dd, D, lay, causal, phiq, dO, phik, V, sx, eps);
+  a.w = wq;
+  a.dx = reinterpret_cast<float*>(w + lay.dphiq);
+  hipError_t e = luna::launch_chunk_query(dt, dd, a, s);
+  if (e != hipSuccess) return hip_fail(e, "query-gradient kernel launch");
+  // [dS | dz]; dphi(K) and dV
+  if ((st = enqueue_chunk_state(dt, heads, n, dd, D, lay, causal, true, phiq, dO, wq, dsx, s)) != LUNA_OK) return st;
+  a = chunk_args(heads, n, dd, D, lay, causal, phik, V, phiq, dO, dsx, eps);
+  a.w = wq;
+  a.out = dV;
+  a.dx = reinterpret_cast<float*>(w + lay.dphik);
+  if ((e = luna::launch_chunk_key(dt, dd, a, s)) != hipSuccess) return hip_fail(e, "key-gradient kernel launch");
   return enqueue_phi_backward(pb, w, lay, Q, K, dQ, dK, grads, s);
-#undef LUNA_TRY
 }
 
 size_t luna_distill_workspace_bytes(luna_dtype dtype, int64_t B, int64_t H, int64_t n, int64_t d,

@@ -22,17 +22,10 @@
 // state in place of the prefix and suffix states and no intra-chunk terms (its
 // chunks only split the sums over tokens among more workgroups).
 //
-// Kernels (all arithmetic in fp32):
-//   bwd_pack_kernel     V -> [V | 1] in fp32;
-//   bwd_gemm_kernel     batched C (+)= A B over (head, chunk) with strided operands, a
-//                       lower-triangular output mask and ragged last chunks;
-//   bwd_scan_kernel     exclusive prefix or suffix sums of the per-chunk states (or, for
-//                       the non-causal form, split into chunks only for parallelism,
-//                       their total);
-//   bwd_g_kernel        [num | den - eps] -> G = [dnum | dden];
-//   (luna_map_backward.hip: dphi -> du -> dx, [dW | db] per workgroup and the
-//                       (segment, channel) moments sum dy and sum dy u of the channel
-//                       outputs' gradients)
+// The attention part runs in luna_features.hip (states of pieces of the tokens) and
+// luna_chunk_kernel.hpp (scans, dphi and dV), the feature map's in luna_map_backward.hip
+// (dphi -> du -> dx, [dW | db] per workgroup and the (segment, channel) moments sum dy and
+// sum dy u of the channel outputs' gradients).  Here:
 //   bwd_dw_kernel       [dW | db] summed over workgroups (fp64);
 //   bwd_reduce_kernel   the partials summed over workgroups (fp64);
 //   bwd_prefix_kernel   exclusive prefix sums of the moments over segments, per channel;
@@ -42,10 +35,13 @@
 //                       dfc2_lk = a_k sum_on dy_l u + c_k sum_on dy_l,
 //                       dfc1_(l)k = f_lk sum_on dy_l u, dfc1_b likewise, dfc2_b_l = sum dy_l.
 //
-// The same pack, GEMM and scan kernels carry the forward pass of the shapes that have
-// no fused kernel (any d, L and M the feature-map kernel takes: one channel per
-// projection with M up to 256, fp32 at d = 128, ...), in fp32 throughout, with one more:
-//   fwd_out_kernel      [num | den - eps] -> out = num / den in the call's dtype;
+// Attention from given features whose widths the chunk kernels do not take (d other than 32,
+// 64 and 128, or more than 256 features) runs as fp32 GEMMs over 64-token chunks:
+//   bwd_pack_kernel     V -> [V | 1] in fp32;
+//   bwd_gemm_kernel     batched C (+)= A B over (head, chunk) with strided operands, a
+//                       lower-triangular output mask and ragged last chunks;
+//   bwd_scan_kernel     exclusive prefix sums of the per-chunk states, or their total;
+//   fwd_out_kernel      [num | den - eps] -> out = num / den in the value type.
 #include <algorithm>
 
 #include "luna_device.hpp"
@@ -68,13 +64,6 @@ __global__ __launch_bounds__(256) void bwd_pack_kernel(const T* __restrict__ V, 
     const int c = (int)(i - r * (d + 1));
     Vx[i] = c < d ? (float)V[r * d + c] : 1.0f;
   }
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void bwd_convert_kernel(const float* __restrict__ src, T* __restrict__ dst,
-                                                          int64_t n) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    dst[i] = (T)src[i];
 }
 
 // ---------------------------------------------------------------------------
@@ -183,44 +172,21 @@ __global__ __launch_bounds__(256) void bwd_gemm_kernel(BwdGemm g) {
 }
 
 // ---------------------------------------------------------------------------
-// exclusive prefix (forward) or suffix (backward) sums over chunks, in place
+// exclusive prefix sums over chunks in place, or (total) their total in every chunk
 // ---------------------------------------------------------------------------
-// mode 0: exclusive prefix, 1: exclusive suffix, 2: the total in every chunk
-__global__ __launch_bounds__(256) void bwd_scan_kernel(float* X, int heads, int chunks, int64_t elems, int mode) {
+__global__ __launch_bounds__(256) void bwd_scan_kernel(float* X, int heads, int chunks, int64_t elems, int total) {
   const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   const int h = blockIdx.y;
   if (e >= elems || h >= heads) return;
   float* base = X + (int64_t)h * chunks * elems + e;
   float run = 0.0f;
-  for (int i = 0; i < chunks; ++i) {
-    const int c = mode == 1 ? chunks - 1 - i : i;
+  for (int c = 0; c < chunks; ++c) {
     const float v = base[(int64_t)c * elems];
-    if (mode != 2) base[(int64_t)c * elems] = run;
+    if (!total) base[(int64_t)c * elems] = run;
     run += v;
   }
-  if (mode == 2)
+  if (total)
     for (int c = 0; c < chunks; ++c) base[(int64_t)c * elems] = run;
-}
-
-// ---------------------------------------------------------------------------
-// [num | den - eps] -> [dnum | dden], one wave per row
-// ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void bwd_g_kernel(float* __restrict__ Y, const T* __restrict__ dO, int64_t rows,
-                                                    int d, float eps) {
-  const int lane = threadIdx.x % kWave;
-  const int64_t r = blockIdx.x * (int64_t)(blockDim.x / kWave) + threadIdx.x / kWave;
-  if (r >= rows) return;
-  float* y = Y + r * (d + 1);
-  const T* go = dO + r * d;
-  const float den = y[d] + eps;
-  float dot = 0.0f;
-  for (int c = lane; c < d; c += kWave) dot = fmaf((float)go[c], y[c], dot);
-#pragma unroll
-  for (int o = kWave / 2; o > 0; o >>= 1) dot += __shfl_xor(dot, o, kWave);
-  const float inv = 1.0f / den;
-  for (int c = lane; c < d; c += kWave) y[c] = (float)go[c] * inv;
-  if (lane == 0) y[d] = -dot * inv * inv;
 }
 
 // ---------------------------------------------------------------------------
@@ -440,13 +406,6 @@ hipError_t launch_bwd_pack(Dt dt, const void* V, float* Vx, int64_t rows, int d,
   return hipGetLastError();
 }
 
-hipError_t launch_bwd_convert(Dt dt, const float* src, void* dst, int64_t n, hipStream_t s) {
-  const dim3 grid((unsigned)std::min<int64_t>((n + 255) / 256, 65536)), block(256);
-  if (dt == Dt::BF16) hipLaunchKernelGGL(bwd_convert_kernel<__bf16>, grid, block, 0, s, src, (__bf16*)dst, n);
-  else hipLaunchKernelGGL(bwd_convert_kernel<float>, grid, block, 0, s, src, (float*)dst, n);
-  return hipGetLastError();
-}
-
 hipError_t launch_bwd_gemm(const BwdGemm& g, hipStream_t s) {
   // at most 65535 (head, chunk) batches per launch: whole heads per slice
   const int per = std::max(1, 65535 / std::max(1, g.chunks));
@@ -465,23 +424,16 @@ hipError_t launch_bwd_gemm(const BwdGemm& g, hipStream_t s) {
   return hipSuccess;
 }
 
-hipError_t launch_bwd_scan(float* X, int heads, int chunks, int64_t elems, int mode, hipStream_t s) {
+hipError_t launch_bwd_scan(float* X, int heads, int chunks, int64_t elems, bool total, hipStream_t s) {
   for (int h0 = 0; h0 < heads; h0 += 65535) {  // at most 65535 heads per launch
     const int hn = std::min(65535, heads - h0);
     const dim3 grid((unsigned)((elems + 255) / 256), (unsigned)hn);
     hipLaunchKernelGGL(bwd_scan_kernel, grid, dim3(256), 0, s, X + (int64_t)h0 * chunks * elems, hn, chunks, elems,
-                       mode);
+                       total);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
-}
-
-hipError_t launch_bwd_g(Dt dt, float* Y, const void* dO, int64_t rows, int d, float eps, hipStream_t s) {
-  const dim3 grid((unsigned)((rows + 3) / 4)), block(256);
-  if (dt == Dt::BF16) hipLaunchKernelGGL(bwd_g_kernel<__bf16>, grid, block, 0, s, Y, (const __bf16*)dO, rows, d, eps);
-  else hipLaunchKernelGGL(bwd_g_kernel<float>, grid, block, 0, s, Y, (const float*)dO, rows, d, eps);
-  return hipGetLastError();
 }
 
 bool bwd_supported(int d, int L, int M) {

@@ -39,7 +39,7 @@ __device__ __forceinline__ uint4 piece16(const T* base, int k, int q, int rows, 
 // ---------------------------------------------------------------------------
 constexpr int kFsTok = 32;
 
-template <typename TF, typename T, int DH, int FBW>
+template <typename TF, typename T, int DH, int FBW, bool WGT>
 __global__ __launch_bounds__(256) void feat_state_kernel(FeatArgs a) {
   constexpr int CB = DH / 16, VF = Vec16<TF>::N, VT = Vec16<T>::N;
   constexpr int DPM = 64 * FBW;                                  // features at most
@@ -47,6 +47,7 @@ __global__ __launch_bounds__(256) void feat_state_kernel(FeatArgs a) {
   constexpr int NP = kFsTok * DPM / VF / 256, NV = (kFsTok * DH / VT + 255) / 256;
   __shared__ __attribute__((aligned(16))) TF ps[kFsTok * LDP];
   __shared__ __attribute__((aligned(16))) T vs[kFsTok * LDV];
+  __shared__ float2 ws[WGT ? kFsTok : 1];
   const int64_t head = blockIdx.x / a.pieces;
   const int piece = (int)(blockIdx.x - head * a.pieces);
   const int64_t first = (int64_t)piece * a.piece;
@@ -98,6 +99,9 @@ __global__ __launch_bounds__(256) void feat_state_kernel(FeatArgs a) {
       const int c = tid + 256 * i;
       if (c < kFsTok * DH / VT) *reinterpret_cast<uint4*>(vs + c / (DH / VT) * LDV + c % (DH / VT) * VT) = vr[i];
     }
+    if (WGT && tid < kFsTok)
+      ws[tid] = t0 + tid < rows ? reinterpret_cast<const float2*>(a.w)[head * a.n + first + t0 + tid]
+                                : make_float2(0.0f, 0.0f);
     __syncthreads();
     if (t0 + kFsTok < rows) load(t0 + kFsTok);
     Operand<TF, T> af[FBW];
@@ -108,7 +112,15 @@ __global__ __launch_bounds__(256) void feat_state_kernel(FeatArgs a) {
       load_tr4(x, 0, ps, LDP, 8 * g, 16 * fb, lane);
       load_tr4(x, 4, ps, LDP, 8 * g + 4, 16 * fb, lane);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) z[f] += x.get(e);
+      for (int e = 0; e < 8; ++e) {
+        if constexpr (WGT) {
+          const float2 w = ws[8 * g + e];
+          z[f] = fmaf(x.v[e], w.y, z[f]);
+          x.v[e] *= w.x;
+        } else {
+          z[f] += x.get(e);
+        }
+      }
       set_operand(af[f], x);
     }
 #pragma unroll
@@ -123,7 +135,7 @@ __global__ __launch_bounds__(256) void feat_state_kernel(FeatArgs a) {
         if (f == 0 || 16 * (wave + 4 * f) < D) mma(acc[f][cb], af[f], bf);  // (uniform)
     }
   }
-  float* S = a.state + blockIdx.x * (int64_t)D * (DH + 1);
+  float* S = a.state + blockIdx.x * a.elems;
 #pragma unroll
   for (int f = 0; f < FBW; ++f) {
     z[f] += __shfl_xor(z[f], 16, kWave);
@@ -185,7 +197,7 @@ __global__ __launch_bounds__(kFrThreads) void feat_readout_kernel(FeatArgs a) {
   const int D = a.D, tid = threadIdx.x, lane = tid % kWave, wave = wave_id();
   const int g = lane / 16, r = lane % 16;
   const int kbs = (D + 31) / 32;
-  const float* S = a.state + head * a.pieces * (int64_t)D * (DH + 1);
+  const float* S = a.state + head * a.pieces * a.elems;
   for (int i = tid; i < kbs * (CBW + 1) * kWave; i += kFrThreads) {
     const int ln = i % kWave, blk = i / kWave % (CBW + 1), kb = i / (kWave * (CBW + 1));
     const int k0 = 32 * kb + 8 * (ln / 16), c = c0 + 16 * blk + ln % 16;
@@ -264,13 +276,19 @@ __global__ __launch_bounds__(256) void feat_export_kernel(const float* __restric
   }
 }
 
+template <typename TF, typename T, int DH, bool WGT>
+hipError_t state_launch_w(const FeatArgs& a, hipStream_t s) {
+  const dim3 grid((unsigned)(a.heads * a.pieces)), block(256);
+  if (a.D <= 64) hipLaunchKernelGGL((feat_state_kernel<TF, T, DH, 1, WGT>), grid, block, 0, s, a);
+  else if (a.D <= 128) hipLaunchKernelGGL((feat_state_kernel<TF, T, DH, 2, WGT>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((feat_state_kernel<TF, T, DH, 4, WGT>), grid, block, 0, s, a);
+  return hipGetLastError();
+}
 template <typename TF, typename T, int DH>
 hipError_t state_launch(const FeatArgs& a, hipStream_t s) {
-  const dim3 grid((unsigned)(a.heads * a.pieces)), block(256);
-  if (a.D <= 64) hipLaunchKernelGGL((feat_state_kernel<TF, T, DH, 1>), grid, block, 0, s, a);
-  else if (a.D <= 128) hipLaunchKernelGGL((feat_state_kernel<TF, T, DH, 2>), grid, block, 0, s, a);
-  else hipLaunchKernelGGL((feat_state_kernel<TF, T, DH, 4>), grid, block, 0, s, a);
-  return hipGetLastError();
+  if (a.w == nullptr) return state_launch_w<TF, T, DH, false>(a, s);
+  if constexpr (sizeof(TF) == 4) return state_launch_w<TF, T, DH, true>(a, s);
+  return hipErrorInvalidValue;  // (weights go with fp32 features)
 }
 
 template <auto Kernel>
@@ -336,27 +354,47 @@ struct ReadoutLaunch {
 // Value widths of whole fragments, and feature counts up to four 16-feature blocks a wave.
 bool feat_supported(int d, int D) { return (d == 32 || d == 64 || d == 128) && D >= 1 && D <= 256; }
 
-hipError_t launch_feat_state(Dt fdt, Dt vdt, int d, const FeatArgs& a, hipStream_t s) {
-  if (a.heads * a.pieces > 0x7fffffff) return hipErrorInvalidValue;
-  return by_type(fdt, vdt, d, StateLaunch{a, s});
+// the arguments of heads h0 .. h0 + hn - 1
+static FeatArgs feat_heads(const FeatArgs& a, Dt fdt, Dt vdt, int d, int64_t h0, int64_t hn) {
+  const int64_t rows = h0 * a.n, fs = fdt == Dt::BF16 ? 2 : 4, vs = vdt == Dt::BF16 ? 2 : 4;
+  FeatArgs q = a;
+  q.phiq = advance(a.phiq, rows * a.D * fs);
+  q.phik = advance(a.phik, rows * a.D * fs);
+  q.v = advance(a.v, rows * d * vs);
+  q.out = advance(a.out, rows * d * vs);
+  q.state = a.state + h0 * a.pieces * a.elems;
+  if (a.w) q.w = a.w + rows * 2;
+  q.heads = hn;
+  return q;
 }
 
-hipError_t launch_feat_total(int d, const FeatArgs& a, hipStream_t s) {
+hipError_t launch_feat_state(Dt fdt, Dt vdt, int d, const FeatArgs& a, hipStream_t s) {
+  return by_heads(a.heads, (int64_t)a.pieces * 256, [&](int64_t h0, int64_t hn) {
+    const FeatArgs q = feat_heads(a, fdt, vdt, d, h0, hn);
+    return by_type(fdt, vdt, d, StateLaunch{q, s});
+  });
+}
+
+hipError_t launch_feat_total(const FeatArgs& a, hipStream_t s) {
   if (a.pieces == 1) return hipSuccess;
-  const int64_t elems = (int64_t)a.D * (d + 1);
-  hipLaunchKernelGGL(feat_total_kernel, dim3((unsigned)((a.heads * elems + 255) / 256)), dim3(256), 0, s, a.state,
-                     a.heads, a.pieces, elems);
-  return hipGetLastError();
+  return by_heads(a.heads, a.elems + 256, [&](int64_t h0, int64_t hn) {
+    hipLaunchKernelGGL(feat_total_kernel, dim3((unsigned)((hn * a.elems + 255) / 256)), dim3(256), 0, s,
+                       a.state + h0 * a.pieces * a.elems, hn, a.pieces, a.elems);
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_feat_readout(Dt fdt, Dt vdt, int d, const FeatArgs& a, hipStream_t s) {
-  return by_type(fdt, vdt, d, ReadoutLaunch{a, s});
+  return by_heads(a.heads, (a.n + 255) / 256 * kFrThreads, [&](int64_t h0, int64_t hn) {
+    const FeatArgs q = feat_heads(a, fdt, vdt, d, h0, hn);
+    return by_type(fdt, vdt, d, ReadoutLaunch{q, s});
+  });
 }
 
 hipError_t launch_feat_export(int d, const FeatArgs& a, float* S, float* z, int accumulate, hipStream_t s) {
   const int64_t elems = (int64_t)a.D * (d + 1);
   const dim3 grid((unsigned)std::min<int64_t>((a.heads * elems + 255) / 256, 65536));
-  hipLaunchKernelGGL(feat_export_kernel, grid, dim3(256), 0, s, a.state, a.pieces * elems, S, z, a.heads, a.D, d,
+  hipLaunchKernelGGL(feat_export_kernel, grid, dim3(256), 0, s, a.state, a.pieces * a.elems, S, z, a.heads, a.D, d,
                      accumulate);
   return hipGetLastError();
 }

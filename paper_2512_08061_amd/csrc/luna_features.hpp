@@ -6,24 +6,27 @@
 
 namespace luna {
 
-// Statistics of a piece of a head's tokens: S [D][d], then z [D], fp32.
+// Statistics of a piece of a head's tokens: S [D][d], then z [D], fp32, `elems` floats apart.
 struct FeatArgs {
   const void* phiq;   // [heads][n][D], feature type
   const void* phik;
   const void* v;      // [heads][n][d], value type
   void* out;          // [heads][n][d], value type
   float* state;       // [heads][pieces] statistics
-  int64_t heads, n;
+  const float* w;     // [heads][n][2] or null: S = (w0 phi(K))^T V, z = phi(K)^T w1
+  int64_t heads, n, elems;
   int D, piece, pieces;  // tokens per piece (a multiple of 32) and pieces per head
   int tokens;            // readout: tokens per workgroup (set by the launcher)
   float eps;
 };
 
 bool feat_supported(int d, int D);
+// floats from one piece's statistics to the next's: whole 16-byte rows of S
+constexpr int64_t feat_elems(int64_t d, int64_t D) { return (D * (d + 1) + 3) / 4 * 4; }
 // per piece: S = phi(K)^T V, z = phi(K)^T 1
 hipError_t launch_feat_state(Dt fdt, Dt vdt, int d, const FeatArgs& a, hipStream_t s);
 // the pieces of every head summed into its first (in order)
-hipError_t launch_feat_total(int d, const FeatArgs& a, hipStream_t s);
+hipError_t launch_feat_total(const FeatArgs& a, hipStream_t s);
 // out = phi(Q) S / (phi(Q) z + eps) with each head's first piece as its statistics
 hipError_t launch_feat_readout(Dt fdt, Dt vdt, int d, const FeatArgs& a, hipStream_t s);
 // each head's first piece into (or added to) S [heads][D][d] and z [heads][D]

@@ -65,10 +65,8 @@ int map_dw_groups(int64_t rows_per_set, int sets);
 hipError_t launch_map_bwd(Dt dt, int d, int L, const MapBwd& a, int sets, hipStream_t s);
 int bwd_nseg_cap(int L);
 hipError_t launch_bwd_pack(Dt dt, const void* V, float* Vx, int64_t rows, int d, hipStream_t s);
-hipError_t launch_bwd_convert(Dt dt, const float* src, void* dst, int64_t n, hipStream_t s);
 hipError_t launch_bwd_gemm(const BwdGemm& g, hipStream_t s);
-hipError_t launch_bwd_scan(float* X, int heads, int chunks, int64_t elems, int mode, hipStream_t s);
-hipError_t launch_bwd_g(Dt dt, float* Y, const void* dO, int64_t rows, int d, float eps, hipStream_t s);
+hipError_t launch_bwd_scan(float* X, int heads, int chunks, int64_t elems, bool total, hipStream_t s);
 hipError_t launch_bwd_dw(const float* partial, float* dW, float* db, int groups, int M, int d, int sets,
                          hipStream_t s);
 hipError_t launch_bwd_reduce(const float* partial, double* sum, int groups, int part_floats, int used, int sets,
@@ -76,7 +74,6 @@ hipError_t launch_bwd_reduce(const float* partial, double* sum, int groups, int 
 hipError_t launch_bwd_prefix(const double* sum, double* pre, const uint8_t* tables, int M, int d, int L,
                              int part_floats, int nseg_cap, int sets, hipStream_t s);
 hipError_t launch_bwd_mlp(const BwdMlp& a, int sets, hipStream_t s);
-// forward pass of the shapes without a fused kernel (fp32 GEMMs and scans as above)
 hipError_t launch_fwd_out(Dt dt, const float* Y, void* out, int64_t rows, int d, float eps, hipStream_t s);
 
 }  // namespace luna

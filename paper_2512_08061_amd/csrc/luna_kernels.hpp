@@ -246,6 +246,20 @@ struct DistillArgs {
 bool distill_supported(Dt dt, int d, int D);
 hipError_t launch_distill(Dt dt, int d, int D, const DistillArgs& a, bool grads, hipStream_t s);
 
+// Head ranges [h0, h0 + hn) of launches that would otherwise pass the 2^32 threads that one
+// may have: f(h0, hn) for each.
+template <typename F>
+hipError_t by_heads(int64_t heads, int64_t threads_per_head, F f) {
+  const int64_t most = ((int64_t)1 << 31) / threads_per_head, per = most > 1 ? most : 1;
+  for (int64_t h0 = 0; h0 < heads; h0 += per) {
+    const hipError_t e = f(h0, heads - h0 < per ? heads - h0 : per);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+inline const void* advance(const void* p, int64_t bytes) { return p ? static_cast<const char*>(p) + bytes : nullptr; }
+inline void* advance(void* p, int64_t bytes) { return p ? static_cast<char*>(p) + bytes : nullptr; }
+
 // Launchers; each returns hipSuccess or the launch error.  `ok` reports whether
 // a kernel exists for the (dtype, d, L, M) combination.
 hipError_t launch_prepare(const PrepareArgs& a, hipStream_t s);

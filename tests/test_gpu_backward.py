@@ -115,6 +115,17 @@ def test_attn_bwd_map_tiles(dtype, d, M, L, hidden, n):
     _check(w, seed=43 + n, causal=False)
 
 
+@pytest.mark.parametrize("dtype,d,M,L,hidden,n", [
+    ("f32", 32, 5, 2, 64, 64), ("bf16", 64, 7, 8, 64, 65), ("bf16", 128, 20, 4, 64, 128), ("f32", 64, 33, 1, 64, 193),
+    ("bf16", 32, 16, 16, 16, 129), ("f32", 128, 8, 16, 16, 257), ("f32", 128, 3, 1, 8, 127)])
+def test_attn_bwd_causal_tiles(dtype, d, M, L, hidden, n):
+    """Sequences off and at the 64-token tiles and the pieces of two, feature counts off the
+    8-, 32- and 64-feature steps."""
+    w = small_workload(dtype, B=2, H=2, n=n, d=d, M=M, L=L, hidden=hidden, causal=True)
+    say(f"backward causal tiles {w.name}")
+    _check(w, seed=47 + n, causal=True)
+
+
 def test_attn_bwd_rejects_bad_arguments():
     import torch
     w = small_workload("f32", B=1, H=1, n=8, d=64, M=16, L=8)
