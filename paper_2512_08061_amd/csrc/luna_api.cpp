@@ -82,7 +82,9 @@ struct Layout {
   size_t dstats = 0;  // distillation: per query row the softmax max and sum and the kernel row sum
   int chunk = 0, nch = 1, groups = 0, dw_groups = 0, part_floats = 0;
   int splits = 1, tokens_per_split = 0, tile_tokens = 256, tiles = 1, fused = 0;
-  int parts = 1, split = 0;  // causal: workgroups per head, first token of part 1
+  int parts = 1, split = 0;  // causal: workgroups per head, first token of part 1 (of the last of equal parts)
+  int part_chunks = 0;       // chunks of equal parts
+  size_t state_floats = 0;   // floats per state piece
   size_t state = 0;          // causal with 2 parts: state pieces of the first `split` tokens
   int pieces = 0, piece_chunks = 0;
   int staged = 0, sa = 0, sb = 0;  // staged causal scan: chunks of the first scanned part and of the state-only part
@@ -131,13 +133,30 @@ luna_status plan_f32_forward(const Problem& pb, bool causal, bool queries, Layou
   return plan_f32_buffers(pb.B * pb.H, pb.n, (int)pb.d, pb.p->M * pb.p->L, causal, queries, true, lay, off);
 }
 
-// The causal kernel's split.  Too few heads to fill the device: with 97 to 128 heads
-// the staged form below (two scan launches); otherwise cut every head in two at a
+// The causal kernel's split.  Too few heads to fill the device: up to 85 heads in three or
+// more equal parts, with 97 to 128 heads the staged form below (two scan launches); otherwise
+// cut every head in two at a
 // chunk boundary x near n/2, where a state launch first sums the state of [0, x) in
 // pieces (one workgroup per head and piece, enough pieces to fill the device) and part
 // 1 of the scan launch starts from the sum of the pieces.
 void plan_causal_parts(int64_t heads, int64_t n, size_t state_floats, Layout* lay, size_t* off, bool staged_ok) {
   const int64_t nch = (n + 63) / 64;
+  lay->state_floats = state_floats;
+  if (heads <= 85 && nch >= 3) {
+    // Equal parts: a state launch over all but the last, their running sums, one scan
+    // launch.  One scanned part in place of a two-part cut's n / 2 tokens: 16 heads of 1999
+    // tokens, d = 128, 32 projections: 48 us instead of 215.
+    int64_t parts = 256 / heads;
+    if (parts > nch) parts = nch;
+    const int64_t pc = (nch + parts - 1) / parts;
+    lay->part_chunks = lay->piece_chunks = (int)pc;
+    lay->parts = (int)((nch + pc - 1) / pc);
+    lay->pieces = lay->parts - 1;
+    lay->split = (int)(64 * pc * lay->pieces);
+    lay->state = *off;
+    *off = align256(*off + (size_t)heads * lay->pieces * state_floats * sizeof(float));
+    return;
+  }
   if (staged_ok && heads > 96 && heads <= 128 && nch >= 5) {
     // Two workgroups per head fill the device, so both launches are scan launches
     // (staged): the first scans chunks [0, A) of every head and, beside it, sums the
@@ -676,6 +695,29 @@ luna_status plan_features(luna_dtype phi_dtype, luna_dtype dtype, int64_t B, int
   return LUNA_OK;
 }
 
+// The causal kernel over its parts: with more than one, the state launch first (and the
+// running sums of equal parts' states).  `launch` launches the kernel with `a`.
+template <typename Launch>
+luna_status enqueue_causal_parts(const Layout& lay, uint8_t* w, luna::CausalArgs& a, Launch launch, hipStream_t s) {
+  hipError_t e;
+  if (lay.parts > 1) {
+    float* st = reinterpret_cast<float*>(w + lay.state);
+    a.pieces = lay.pieces;
+    a.piece_chunks = lay.piece_chunks;
+    a.part_chunks = lay.part_chunks;
+    a.state_out = st;
+    if ((e = launch()) != hipSuccess) return hip_fail(e, "causal attention state launch");
+    if (lay.part_chunks) {
+      e = luna::launch_causal_prefix(st, a.heads, lay.pieces, lay.state_floats, s);
+      if (e != hipSuccess) return hip_fail(e, "causal state sum launch");
+    }
+    a.state_out = nullptr;
+    a.state_in = st;
+  }
+  e = launch();
+  return e == hipSuccess ? LUNA_OK : hip_fail(e, "causal attention kernel launch");
+}
+
 // Through the feature map, from dphi(Q) and dphi(K) in the workspace (fp32, [head][n][D]):
 // dx into dQ, dK (when given), [dW | db] and the channel-MLP gradients into grads (when
 // given).  Used by the backward pass and by the distillation loss.
@@ -866,17 +908,7 @@ luna_status luna_attn_fwd_features(const void* phiQ, const void* phiK, luna_dtyp
     a.eps = eps;
     a.phiq = phiQ;
     a.phik = phiK;
-    if (lay.parts == 2) {
-      float* stp = reinterpret_cast<float*>(w + lay.state);
-      a.pieces = lay.pieces;
-      a.piece_chunks = lay.piece_chunks;
-      a.state_out = stp;
-      if ((e = luna::launch_causal_given((int)d, (int)D, a, s)) != hipSuccess) return hip_fail(e, "state launch");
-      a.state_out = nullptr;
-      a.state_in = stp;
-    }
-    e = luna::launch_causal_given((int)d, (int)D, a, s);
-    return e == hipSuccess ? LUNA_OK : hip_fail(e, "causal attention kernel launch");
+    return enqueue_causal_parts(lay, w, a, [&]() { return luna::launch_causal_given((int)d, (int)D, a, s); }, s);
   }
   const int64_t heads = B * H;
   if (lay.feat) {
@@ -1037,18 +1069,7 @@ luna_status luna_attn_fwd_causal(const void* Q, const void* K, const void* V, lu
     e = launch();
     return e == hipSuccess ? LUNA_OK : hip_fail(e, "causal attention second scan launch");
   }
-  if (lay.parts == 2) {
-    float* st = reinterpret_cast<float*>(w + lay.state);
-    a.pieces = lay.pieces;
-    a.piece_chunks = lay.piece_chunks;
-    a.state_out = st;
-    hipError_t e = launch();
-    if (e != hipSuccess) return hip_fail(e, "causal attention state launch");
-    a.state_out = nullptr;
-    a.state_in = st;
-  }
-  hipError_t e = launch();
-  return e == hipSuccess ? LUNA_OK : hip_fail(e, "causal attention kernel launch");
+  return enqueue_causal_parts(lay, w, a, launch, s);
 }
 
 luna_status luna_attn_fwd_causal_noalloc(const void* Q, const void* K, const void* V, luna_dtype dtype,

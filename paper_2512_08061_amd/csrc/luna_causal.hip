@@ -16,6 +16,10 @@
 //    of [A, A + B), both writing their final states; the second scans [A, A + B) and
 //    [A + B, nch) from those states (A = nch / 5, B = 2 nch / 5: a state-only chunk
 //    costs about half a scanned one, so both launches are balanced);
+//  - up to 85 heads: every head in three or more equal parts, as many as fill the device.
+//    The state launch (a separate instantiation, ST) sums the state of every part but the
+//    last, causal_prefix_kernel their running sums, and the scan launch starts each part
+//    from the state before it;
 //  - otherwise each head is cut at a chunk boundary x near n/2: the state launch (a
 //    separate instantiation, ST) sums the state of [0, x) in pieces, one workgroup per
 //    (head, piece), and writes them in fp32; the scan launch then runs part 0 over
@@ -256,6 +260,10 @@ __global__ __launch_bounds__(512, 1) void causal_kernel(CausalArgs a) {
     c_begin = part == 0 ? a.pc_begin[0] : a.pc_begin[1];
     c_end = part == 0 ? a.pc_end[0] : a.pc_end[1];
     t_end = min(n, 64 * c_end);
+  } else if (a.part_chunks > 0) {
+    c_first = c_begin = part * a.part_chunks;
+    c_end = min((n + 63) / 64, c_begin + a.part_chunks);
+    t_end = min(n, 64 * c_end);
   } else {
     const int t_begin = part == 0 ? 0 : a.split;
     t_end = part == a.parts - 1 ? n : a.split;
@@ -265,9 +273,11 @@ __global__ __launch_bounds__(512, 1) void causal_kernel(CausalArgs a) {
   }
   // part 1 of the scan launch starts from the state of the first c_first chunks: the
   // sum of the pieces, in piece order (a staged part from the sum of its first npc)
-  const int npc = a.staged ? (part == 0 ? a.pseed[0] : a.pseed[1]) : a.pieces;
+  // (with equal parts the one running sum before it)
+  const int npc = a.staged ? (part == 0 ? a.pseed[0] : a.pseed[1]) : a.part_chunks > 0 ? 1 : a.pieces;
   const bool seeded = !state_run && (a.staged ? npc > 0 : c_first > 0);
-  const float* seed = seeded ? a.state_in + (size_t)head * a.pieces * C::STATE : nullptr;
+  const int first_piece = a.part_chunks > 0 ? part - 1 : 0;
+  const float* seed = seeded ? a.state_in + (size_t)(head * a.pieces + first_piece) * C::STATE : nullptr;
 
   // Q, K, V rows of chunk cc and the output rows of chunk cc as range-checked
   // buffers: rows at or past n (t_end for the output) read as 0 and are not written.
@@ -1020,6 +1030,35 @@ __global__ __launch_bounds__(512, 1) void causal_kernel(CausalArgs a) {
   }
 }
 
+// Running sums of every head's pieces, in place and in piece order: a thread takes four
+// elements through the pieces, eight loads in flight.
+__global__ __launch_bounds__(256) void causal_prefix_kernel(f32x4* state, int64_t heads, int pieces, int64_t quads) {
+  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (i >= heads * quads) return;
+  const int64_t h = i / quads;
+  f32x4* p = state + h * pieces * quads + (i - h * quads);
+  f32x4 run = zero4();
+  for (int c = 0; c < pieces; c += 8) {
+    f32x4 v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = p[(int64_t)min(c + k, pieces - 1) * quads];
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      if (c + k < pieces) {
+        run += v[k];
+        p[(int64_t)(c + k) * quads] = run;
+      }
+  }
+}
+
+hipError_t launch_causal_prefix(float* state, int heads, int pieces, size_t floats, hipStream_t s) {
+  if (pieces < 2) return hipSuccess;
+  const int64_t quads = (int64_t)floats / 4;
+  hipLaunchKernelGGL(causal_prefix_kernel, dim3((unsigned)((heads * quads + 255) / 256)), dim3(256), 0, s,
+                     reinterpret_cast<f32x4*>(state), (int64_t)heads, pieces, quads);
+  return hipGetLastError();
+}
+
 // State export: the state launch's pieces summed in piece order and written as
 // S [M*L][d], z [M*L] (fp32, feature i*L + l, the coefficient rows' power-of-two scale
 // removed), or added to them.  A piece holds the matrix waves' S tiles, lane-major
@@ -1058,7 +1097,14 @@ __global__ __launch_bounds__(256) void causal_state_export_kernel(CausalArgs a) 
     proj_chan(f, p, l);
     if (p >= M) continue;
     float v = 0.0f;
-    for (int q = 0; q < a.pieces; ++q) v += pc[(size_t)q * C::STATE + i];
+    for (int q = 0; q < a.pieces; q += 8) {  // eight loads in flight: one at a time took 41 us for 16 pieces
+      float x[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) x[k] = pc[(size_t)min(q + k, a.pieces - 1) * C::STATE + i];
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        if (q + k < a.pieces) v += x[k];
+    }
     v *= unscale;
     const int fp = p * L + l;
     float* dst = col >= 0 ? &S[(size_t)fp * DH + col] : &z[fp];
@@ -1069,7 +1115,9 @@ __global__ __launch_bounds__(256) void causal_state_export_kernel(CausalArgs a) 
 template <typename T, int DH, int L, int MB>
 static hipError_t cs_run(const CausalArgs& a, hipStream_t s) {
   if (a.export_S != nullptr) {  // pieces already written by a state launch
-    hipLaunchKernelGGL((causal_state_export_kernel<T, DH, L, MB>), dim3(a.heads, 16), dim3(256), 0, s, a);
+    using C = CsCfg<T, DH, L, MB>;
+    hipLaunchKernelGGL((causal_state_export_kernel<T, DH, L, MB>), dim3(a.heads, (C::SF + C::FP + 255) / 256),
+                       dim3(256), 0, s, a);
     return hipGetLastError();
   }
   const int per_head = a.state_out != nullptr ? a.pieces : a.parts;

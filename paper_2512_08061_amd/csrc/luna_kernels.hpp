@@ -147,7 +147,8 @@ struct CausalArgs {
   void* out;
   PhiArgs phi;
   int n, H, heads;
-  int parts;     // workgroups per head (1 or 2)
+  int parts;     // workgroups per head
+  int part_chunks;  // > 0: equal parts of that many chunks, part p > 0 starting from piece p - 1
   int split;     // with 2 parts: first token of part 1 (a multiple of 64)
   float eps;
   // State of the first `split` tokens of every head, built beforehand in `pieces`
@@ -284,6 +285,8 @@ bool causal_supported(Dt dt, int d, int L, int M);
 // floats of one state piece (S slices of the matrix waves, then z) for a combination
 size_t causal_state_floats(Dt dt, int d, int L, int M);
 hipError_t launch_causal(Dt dt, int d, int L, int M, const CausalArgs& a, hipStream_t s);
+// running sums of every head's state pieces (of `floats` floats), in place
+hipError_t launch_causal_prefix(float* state, int heads, int pieces, size_t floats, hipStream_t s);
 // The causal kernel with the features given in bf16 (D of them per token), for the
 // feature maps whose projections and tables the fused kernel cannot hold.
 bool causal_given_supported(Dt dt, int d, int D);

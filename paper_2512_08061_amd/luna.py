@@ -452,6 +452,10 @@ def attn_state(K, V, p: PhiParams, S=None, z=None, accumulate: bool = False):
     [B, H, M*L] (fp32), written into S, z (allocated when None) or added to them."""
     lib = load_library()
     B, H, n, d = _qkv_shape(K, V)
+    if S is None and z is None and not accumulate:  # (every element is written)
+        torch = _torch()
+        S = torch.empty((B, H, p.M * p.L, d), dtype=torch.float32, device=K.device)
+        z = torch.empty((B, H, p.M * p.L), dtype=torch.float32, device=K.device)
     S, z = _state_tensors(B, H, p.M * p.L, d, K.device, S, z)
     pc = p.c()
     dt = _dt(K)

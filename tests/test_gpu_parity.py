@@ -344,6 +344,24 @@ def test_attn_causal_staged(dtype, d, M, B, H, n):
     assert_close_rows(pick(out), ref, dtype, "out")
 
 
+@pytest.mark.parametrize("dtype,d,M,L,B,H,n", [
+    ("bf16", 128, 32, 8, 1, 1, 129), ("bf16", 128, 32, 8, 1, 85, 193), ("bf16", 64, 16, 8, 5, 17, 641),
+    ("f32", 64, 16, 8, 2, 30, 321), ("bf16", 32, 8, 8, 1, 7, 1999), ("bf16", 128, 256, 1, 1, 43, 449),
+    ("bf16", 64, 16, 8, 1, 86, 200)])
+def test_attn_causal_equal_parts(dtype, d, M, L, B, H, n):
+    """Up to 85 heads: equal parts from the running sums of the states before them, with one
+    to several chunks a part, ragged last parts and chunks, and the first head count past it."""
+    w = small_workload(dtype, B=B, H=H, n=n, d=d, M=M, L=L, causal=True)
+    say(f"causal equal parts {dtype} d={d} M={M} L={L} B={B} H={H} n={n}")
+    Q, K, V, p = inputs(w, seed=71)
+    (Qt, Kt, Vt), pt = upload(w, [Q, K, V], p)
+    out = to_np(luna.attn_fwd_causal(Qt, Kt, Vt, pt, chunk=64, eps=w.eps))
+    bs, hs = sorted({0, B - 1}), sorted({0, H // 2, H - 1})
+    pick = lambda X: X[bs][:, hs]  # noqa: E731
+    ref = oracle.attn_causal(pick(Q), pick(K), pick(V), p, eps=w.eps)
+    assert_close_rows(pick(out), ref, dtype, "out")
+
+
 def test_attn_causal_workload_full_size():
     w = wl.WORKLOADS["long_causal"]
     say("causal full size long_causal")
