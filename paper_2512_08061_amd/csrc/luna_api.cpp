@@ -94,10 +94,19 @@ struct Layout {
   int given = 0;    // causal: features mapped beforehand (bf16, in phiq / phik), then the scan kernel
 };
 
+// Tokens per piece of the statistics of a whole sequence: 512, or the fewer (64 at least) that
+// put a piece on every compute unit.  A piece is a serial chain of 32-token steps, 16 of them
+// 40 us at d = 128 and 256 features.
+int state_piece(int64_t heads, int64_t n) {
+  int piece = 512;
+  while (piece > 64 && heads * ((n + piece - 1) / piece) < 256) piece /= 2;
+  return piece;
+}
+
 // Buffers of the forward pass in fp32 (the forward of shapes without a fused kernel, and
 // the start of the backward pass): features of the keys (and queries) and the statistics of
 // pieces of the tokens.  Causal pieces are a few tiles long (luna_chunk.hpp), the
-// non-causal form cuts its sums over tokens into 512-token pieces, for parallelism only.
+// non-causal form cuts its sums over tokens into pieces for parallelism only.
 // Widths that only given features have take fp32 GEMMs over 64-token chunks: [V | 1],
 // [num | den - eps] and the per-chunk states, plus P for the causal form.
 // (features: the buffers for fp32 features, or none when the caller's are used)
@@ -107,8 +116,8 @@ luna_status plan_f32_buffers(int64_t heads, int64_t n, int d, int D, bool causal
   int64_t nch = (n + lay->chunk - 1) / lay->chunk;
   if (nch > 65535) return fail(LUNA_ERR_UNSUPPORTED, causal ? "n must be <= 65535 * 64" : "n must be <= 65535 * 512");
   lay->chunked = luna::chunk_supported(d, D);
-  if (lay->chunked && causal) {
-    lay->chunk = luna::kChunkPiece;
+  if (lay->chunked) {
+    lay->chunk = causal ? luna::kChunkPiece : state_piece(heads, n);
     nch = (n + lay->chunk - 1) / lay->chunk;
   }
   lay->nch = (int)nch;
@@ -195,10 +204,13 @@ void plan_causal_parts(int64_t heads, int64_t n, size_t state_floats, Layout* la
 }
 
 // Token ranges of the non-causal state pass: enough state workgroups to fill the
-// device, at least 256 tokens each, a multiple of 128 tokens per range.
+// device, at least 256 tokens each, a multiple of 128 tokens per range.  Where that leaves
+// at most a quarter of the compute units at work, 128 tokens: a workgroup's time is then its
+// own serial chain.
 void plan_splits(const Problem& pb, int64_t heads, Layout* lay) {
   const int64_t want = (512 + heads - 1) / heads;
-  const int64_t maxs = (pb.n + 255) / 256;
+  const int64_t least = heads * ((pb.n + 255) / 256) <= 64 ? 128 : 256;
+  const int64_t maxs = (pb.n + least - 1) / least;
   int64_t splits = want < maxs ? want : maxs;
   if (splits < 1) splits = 1;
   int64_t tps = (pb.n + splits - 1) / splits;
@@ -261,8 +273,10 @@ luna_status plan(const Problem& pb, Layout* lay) {
       return LUNA_OK;
     }
     plan_splits(pb, heads, lay);
-    lay->tile_tokens = 256;
-    lay->tiles = (int)((pb.n + 255) / 256);
+    // 256 tokens a readout workgroup, or 64 (one block of 16 per wave) while one round of
+    // workgroups then still does (1 head of 256 fp32 tokens, d = 32: 7 us instead of 14)
+    lay->tile_tokens = heads * ((pb.n + 63) / 64) <= 256 ? 64 : 256;
+    lay->tiles = (int)((pb.n + lay->tile_tokens - 1) / lay->tile_tokens);
     lay->partial = off;
     off = align256(off + (size_t)heads * lay->splits * np.DP * (d + 1) * sizeof(float));
     lay->frags = off;
@@ -678,11 +692,11 @@ luna_status plan_features(luna_dtype phi_dtype, luna_dtype dtype, int64_t B, int
     lay->given = 1;
     plan_causal_parts(heads, n, luna::causal_given_state_floats((int)d, (int)D), lay, &off, false);
   } else if (!causal && luna::feat_supported((int)d, (int)D)) {
-    // the features in their own type: statistics of 512-token pieces only
+    // the features in their own type: statistics of pieces only
     lay->feat = 1;
-    lay->chunk = 512;
+    if ((n + 511) / 512 > 65535) return fail(LUNA_ERR_UNSUPPORTED, "n must be <= 65535 * 512");
+    lay->chunk = state_piece(heads, n);
     const int64_t pieces = (n + lay->chunk - 1) / lay->chunk;
-    if (pieces > 65535) return fail(LUNA_ERR_UNSUPPORTED, "n must be <= 65535 * 512");
     lay->nch = (int)pieces;
     lay->sx = off;
     off = align256(off + (size_t)heads * lay->nch * (size_t)luna::feat_elems(d, D) * 4);

@@ -1097,14 +1097,15 @@ __global__ __launch_bounds__(256) void causal_state_export_kernel(CausalArgs a) 
     proj_chan(f, p, l);
     if (p >= M) continue;
     float v = 0.0f;
-    for (int q = 0; q < a.pieces; q += 8) {  // eight loads in flight: one at a time took 41 us for 16 pieces
+    int q = 0;
+    for (; q + 8 <= a.pieces; q += 8) {  // eight loads in flight: one at a time took 41 us for 16 pieces
       float x[8];
 #pragma unroll
-      for (int k = 0; k < 8; ++k) x[k] = pc[(size_t)min(q + k, a.pieces - 1) * C::STATE + i];
+      for (int k = 0; k < 8; ++k) x[k] = pc[(size_t)(q + k) * C::STATE + i];
 #pragma unroll
-      for (int k = 0; k < 8; ++k)
-        if (q + k < a.pieces) v += x[k];
+      for (int k = 0; k < 8; ++k) v += x[k];
     }
+    for (; q < a.pieces; ++q) v += pc[(size_t)q * C::STATE + i];
     v *= unscale;
     const int fp = p * L + l;
     float* dst = col >= 0 ? &S[(size_t)fp * DH + col] : &z[fp];

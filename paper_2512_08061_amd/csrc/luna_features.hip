@@ -21,13 +21,16 @@ namespace luna {
 
 namespace {
 
-// Rows k < rows of a [.][cols] array, columns cols .. cols_pad (16-byte pieces; cols a
-// multiple of the piece) read as 0.
-template <typename T>
-__device__ __forceinline__ uint4 piece16(const T* base, int k, int q, int rows, int cols) {
-  constexpr int V = Vec16<T>::N;
-  return k < rows && q * V < cols ? *reinterpret_cast<const uint4*>(base + (int64_t)k * cols + q * V)
-                                  : make_uint4(0, 0, 0, 0);
+// Features, values and statistics are read through range-checked buffers that end with their
+// last row, so that rows past it read as 0: a test per load puts a branch around each.
+using Buf = __amdgpu_buffer_rsrc_t;
+__device__ __forceinline__ Buf buffer(const void* p, int bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, __builtin_amdgcn_readfirstlane(bytes),
+                                           kBufferFlags);
+}
+constexpr int kPastEnd = 0x7ffffff0;  // an offset no buffer reaches
+__device__ __forceinline__ uint4 piece16(Buf b, int off) {
+  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(b, off, 0, 0));
 }
 
 // ---------------------------------------------------------------------------
@@ -66,18 +69,16 @@ __global__ __launch_bounds__(256) void feat_state_kernel(FeatArgs a) {
     for (int cb = 0; cb < CB; ++cb) acc[f][cb] = zero4();
   }
   uint4 pr[NP], vr[NV];
+  const Buf bphi = buffer(phi, rows * D * (int)sizeof(TF)), bv = buffer(V, rows * DH * (int)sizeof(T));
   auto load = [&](int t0) {
     if (vec)
 #pragma unroll
       for (int i = 0; i < NP; ++i) {
-        const int c = tid + 256 * i;
-        pr[i] = piece16(phi + (int64_t)t0 * D, c / (DPM / VF), c % (DPM / VF), rows - t0, D);
+        const int c = tid + 256 * i, q = c % (DPM / VF) * VF;
+        pr[i] = piece16(bphi, q < D ? ((t0 + c / (DPM / VF)) * D + q) * (int)sizeof(TF) : kPastEnd);
       }
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      const int c = tid + 256 * i;
-      vr[i] = piece16(V + (int64_t)t0 * DH, c / (DH / VT), c % (DH / VT), min(rows - t0, kFsTok), DH);
-    }
+    for (int i = 0; i < NV; ++i) vr[i] = piece16(bv, t0 * DH * (int)sizeof(T) + (tid + 256 * i) * 16);
   };
   load(0);
   for (int t0 = 0; t0 < rows; t0 += kFsTok) {
@@ -167,6 +168,14 @@ __global__ __launch_bounds__(256) void feat_total_kernel(float* state, int64_t h
 #pragma unroll
     for (int k = 0; k < 8; ++k) s += v[k];
   }
+  if (c + 4 <= pieces) {
+    float v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = p[(c + k) * elems];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) s += v[k];
+    c += 4;
+  }
   for (; c < pieces; ++c) s += p[c * elems];
   *p = s;
 }
@@ -197,38 +206,43 @@ __global__ __launch_bounds__(kFrThreads) void feat_readout_kernel(FeatArgs a) {
   const int D = a.D, tid = threadIdx.x, lane = tid % kWave, wave = wave_id();
   const int g = lane / 16, r = lane % 16;
   const int kbs = (D + 31) / 32;
-  const float* S = a.state + head * a.pieces * a.elems;
-  for (int i = tid; i < kbs * (CBW + 1) * kWave; i += kFrThreads) {
-    const int ln = i % kWave, blk = i / kWave % (CBW + 1), kb = i / (kWave * (CBW + 1));
+  const Buf bS = buffer(a.state + head * a.pieces * a.elems, D * (DH + 1) * 4);
+  // (every load of a thread's fragments before the first is split: in turn, the five rounds
+  // of 256 features took 20 us of a short call)
+  constexpr int NI = (KB * (CBW + 1) * kWave + kFrThreads - 1) / kFrThreads;
+  Frag<float> fr[NI];
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const int at = tid + kFrThreads * i, ln = at % kWave, blk = at / kWave % (CBW + 1), kb = at / (kWave * (CBW + 1));
     const int k0 = 32 * kb + 8 * (ln / 16), c = c0 + 16 * blk + ln % 16;
-    Frag<float> f;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const int k = k0 + e;
-      f.v[e] = k < D ? (blk < CBW ? S[k * DH + c] : S[D * DH + k]) : 0.0f;
+      const int k = k0 + e, el = blk < CBW ? k * DH + c : D * DH + k;
+      fr[i].v[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(bS, k < D ? 4 * el : kPastEnd, 0, 0));
     }
-    set_operand(frags[i], f);
   }
+#pragma unroll
+  for (int i = 0; i < NI; ++i)
+    if (tid + kFrThreads * i < kbs * (CBW + 1) * kWave) set_operand(frags[tid + kFrThreads * i], fr[i]);
   __syncthreads();
-  const TF* phi = reinterpret_cast<const TF*>(a.phiq) + head * a.n * D;
+  const TF* phi = reinterpret_cast<const TF*>(a.phiq) + (head * a.n + first) * D;
   T* out = reinterpret_cast<T*>(a.out) + head * a.n * DH;
   const bool vec = D % Vec16<TF>::N == 0 && D % 8 == 0;  // (uniform)
   for (int64_t t0 = first + wave * 16 * NTL; t0 < last; t0 += (kFrThreads / kWave) * 16 * NTL) {
     Frag<TF> q[NTL][KB];
 #pragma unroll
     for (int i = 0; i < NTL; ++i) {
-      const int64_t t = t0 + 16 * i + r;
-      const TF* row = phi + t * D;
+      const int t = (int)(t0 - first) + 16 * i + r;
 #pragma unroll
       for (int kb = 0; kb < KB; ++kb) {
         const int k0 = 32 * kb + 8 * g;
         q[i][kb].zero();
         if (vec) {
-          if (t < last && k0 < D) load8(q[i][kb], row + k0);
-        } else if (t < last) {
+          if (first + t < last && k0 < D) load8(q[i][kb], phi + t * D + k0);
+        } else if (first + t < last) {
 #pragma unroll
-          for (int e = 0; e < 8; ++e)
-            if (k0 + e < D) q[i][kb].v[e] = row[k0 + e];
+            for (int e = 0; e < 8; ++e)
+              if (k0 + e < D) q[i][kb].v[e] = phi[t * D + k0 + e];
         }
       }
     }
@@ -306,10 +320,11 @@ template <typename TF, typename T, int DH>
 hipError_t readout_launch(const FeatArgs& args, hipStream_t s) {
   constexpr int CB = DH / 16, CBW = CB < 4 ? CB : 4;
   FeatArgs a = args;
-  // 256 tokens per pass of a workgroup's waves; more passes, up to four, as long as about
-  // two workgroups per CU remain (the fragments are set up once per workgroup)
-  const int64_t passes = a.heads * a.n / (512 * 256);
-  a.tokens = 256 * (int)std::max<int64_t>(1, std::min<int64_t>(4, passes));
+  // one pass of a workgroup's waves over its tokens; more passes, up to 1024 tokens, as long as
+  // about two workgroups per CU remain (the fragments are set up once per workgroup)
+  constexpr int kPass = kFrThreads / kWave * 16 * readout_tiles<TF>();
+  const int64_t passes = a.heads * a.n / (512 * kPass);
+  a.tokens = kPass * (int)std::max<int64_t>(1, std::min<int64_t>(1024 / kPass, passes));
   const int64_t blocks = a.heads * ((a.n + a.tokens - 1) / a.tokens);
   if (blocks > 0x7fffffff) return hipErrorInvalidValue;
   const dim3 grid((unsigned)blocks, (unsigned)(CB / CBW));
@@ -385,7 +400,7 @@ hipError_t launch_feat_total(const FeatArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_feat_readout(Dt fdt, Dt vdt, int d, const FeatArgs& a, hipStream_t s) {
-  return by_heads(a.heads, (a.n + 255) / 256 * kFrThreads, [&](int64_t h0, int64_t hn) {
+  return by_heads(a.heads, (a.n + 127) / 128 * kFrThreads * 2, [&](int64_t h0, int64_t hn) {
     const FeatArgs q = feat_heads(a, fdt, vdt, d, h0, hn);
     return by_type(fdt, vdt, d, ReadoutLaunch{q, s});
   });

@@ -230,6 +230,21 @@ __global__ __launch_bounds__(256, 1) void nc_state_kernel(NoncausalArgs a) {
   for (int i = threadIdx.x; i < C::DP * (DH + 1); i += blockDim.x) part[i] = src[i];
 }
 
+// The sum of `splits` partials `stride` floats apart, in order, eight loads in flight.
+__device__ __forceinline__ float sum_splits(const float* p, int splits, int stride) {
+  float v = 0.0f;
+  int s = 0;
+  for (; s + 8 <= splits; s += 8) {
+    float x[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) x[k] = p[(size_t)(s + k) * stride];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v += x[k];
+  }
+  for (; s < splits; ++s) v += p[(size_t)s * stride];
+  return v;
+}
+
 // ---------------------------------------------------------------------------
 // reduce pass: partials -> readout fragments
 // ---------------------------------------------------------------------------
@@ -256,7 +271,7 @@ __global__ __launch_bounds__(256) void nc_reduce_kernel(NoncausalArgs a) {
       const int mb = mbj / 4, j = mbj % 4;
       const int row = (mb * L + l) * 16 + 4 * g + j;
       const int src = row * (DH + 1) + (cb < C::CB ? 16 * cb + r : DH);
-      for (int sp = 0; sp < a.splits; ++sp) v += part[(size_t)sp * C::DP * (DH + 1) + src];
+      v = sum_splits(part + src, a.splits, C::DP * (DH + 1));
     }
     fr[idx] = (T)v;
   }
@@ -284,9 +299,7 @@ __global__ __launch_bounds__(256) void nc_state_export_kernel(NoncausalArgs a) {
     // partial row (mb, l, i16) holds projection 16 mb + i16, channel l
     const int mb = row / (16 * L), l = (row / 16) % L, p = 16 * mb + row % 16;
     if (p >= M) continue;
-    float v = 0.0f;
-    for (int sp = 0; sp < a.splits; ++sp) v += part[(size_t)sp * C::DP * (DH + 1) + i];
-    v *= unscale;
+    const float v = unscale * sum_splits(part + i, a.splits, C::DP * (DH + 1));
     const int f = p * L + l;
     float* dst = col < DH ? &S[(size_t)f * DH + col] : &z[f];
     *dst = a.accumulate ? *dst + v : v;

@@ -37,8 +37,8 @@
 // channel scales, and variant_finish_kernel applies them, the bank sum and 1/sqrt(M).
 //
 // The one-feature kinds take two 16-projection blocks at a time so that a lane holds
-// 8 consecutive projections (a 16-byte run of bf16 features), and read the next item's
-// rows while mapping the current one.
+// 8 consecutive projections (a 16-byte run of bf16 features), and read the next rows
+// while mapping the current ones; rows of up to 256 bytes have a kernel of their own.
 #pragma once
 
 #include <math.h>
@@ -132,17 +132,14 @@ __device__ __forceinline__ void store_run(void* out, bool obf, const float (&f)[
 // The one-feature kinds stream rows through: registers are capped so that eight waves
 // per SIMD are resident (four for rows of 128 elements, which carry twice the bytes);
 // the channel MLPs are bound by their arithmetic.
-template <typename Tin, int DH, int KIND, int ACT, int LC, bool STAGED>
-__global__ __launch_bounds__(256, KIND == kVarMlp ? 1 : (DH <= 64 ? (STAGED ? 6 : 8) : 4)) void variant_map_kernel(VariantArgs a) {
+template <typename Tin, int DH, int KIND, int ACT, int LC>
+__global__ __launch_bounds__(256, KIND == kVarMlp ? 1 : (DH <= 64 ? 8 : 4)) void variant_map_kernel(VariantArgs a) {
   constexpr int KS = DH / 32;
   constexpr bool MLP = KIND == kVarMlp;
   // a lane's run of features: 8 projections' (sin/cos: two each) for the one-feature
   // kinds, four projections' for the channel MLPs (with a bank; per channel otherwise)
   constexpr int RUN = MLP ? 4 : (KIND == kVarSinCos ? 16 : 8);
   __shared__ float s_bias[256];  // b of the parameter set, zero past M
-  // one-feature kinds: each wave's 16 output rows (at most 256 bytes each), written back
-  // as contiguous 1 KB stores
-  __shared__ uint4 s_rows[STAGED ? 4 * 16 * 16 : 1];
   __shared__ float s_env[MLP ? LC * DH : 4];
   __shared__ double s_sum[4][LC];  // channel RMS: per-wave sums of y^2
 
@@ -165,8 +162,6 @@ __global__ __launch_bounds__(256, KIND == kVarMlp ? 1 : (DH <= 64 ? (STAGED ? 6 
                    (reinterpret_cast<uintptr_t>(a.out) & 15) == 0;
   const float inv_sqrt_m = 1.0f / sqrtf((float)M);
   const float half_inv_sqrt_d = 0.5f / sqrtf((float)DH);
-  const int row_chunks = D * esz / 16;  // 16-byte pieces of an output row
-  constexpr bool staged = STAGED;  // (the host checks: one-feature kind, rows of whole 16-byte pieces, <= 256 bytes)
   const int64_t n = a.rows_per_head;
   const int tiles_per_head = (int)((n + 63) / 64);
   const int64_t items = a.heads * tiles_per_head;
@@ -289,44 +284,7 @@ __global__ __launch_bounds__(256, KIND == kVarMlp ? 1 : (DH <= 64 ? (STAGED ? 6 
               f[e] = hw_exp(u - sq * half_inv_sqrt_d) * inv_sqrt_m;
             }
           }
-        if constexpr (staged) {  // the run's whole 16-byte pieces into the wave's row tile
-          uint4* dst = s_rows + (wave * 16 + r) * 16 + base * lout * esz / 16;
-          const int nfeat = nv * lout;
-          if (obf) {
-#pragma unroll
-            for (int k = 0; k < RUN / 8; ++k) {
-              if (8 * k < nfeat) {
-                bf16x8 v;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) v[e] = (__bf16)f[8 * k + e];
-                dst[k] = __builtin_bit_cast(uint4, v);
-              }
-            }
-          } else {
-#pragma unroll
-            for (int k = 0; k < RUN / 4; ++k)
-              if (4 * k < nfeat)
-                dst[k] = make_uint4(__float_as_uint(f[4 * k]), __float_as_uint(f[4 * k + 1]),
-                                    __float_as_uint(f[4 * k + 2]), __float_as_uint(f[4 * k + 3]));
-          }
-        } else {
-          store_run<RUN>(out_row + (int64_t)base * lout * esz, obf, f, nv * lout, vec && nv == 8);
-        }
-      }
-      if constexpr (staged) {  // the wave's 16 rows back, consecutive lanes on consecutive pieces
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        const int64_t t0 = (int64_t)tile * 64 + wave * 16;
-        char* rows = reinterpret_cast<char*>(a.out) + (head * n + t0) * (int64_t)D * esz;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int c = lane + kWave * q;
-          if (c < 16 * row_chunks) {
-            const int row = c / row_chunks, col = c - row * row_chunks;
-            if (t0 + row < n)
-              *reinterpret_cast<uint4*>(rows + (int64_t)row * D * esz + 16 * col) = s_rows[(wave * 16 + row) * 16 + col];
-          }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        store_run<RUN>(out_row + (int64_t)base * lout * esz, obf, f, nv * lout, vec && nv == 8);
       }
     } else {
       for (int mb = 0; mb < MB; ++mb) {
@@ -476,14 +434,150 @@ __global__ __launch_bounds__(256, KIND == kVarMlp ? 1 : (DH <= 64 ? (STAGED ? 6 
   }
 }
 
-// As many workgroups as the device holds at once (registers and LDS permitting), at
-// most kVariantMaxGrid; more items loop.  The occupancy query runs once per kernel.
-template <typename Tin, int DH, int KIND, int ACT, int LC, bool STAGED = false>
-hipError_t variant_launch(const VariantArgs& a, int64_t items, int* grid, hipStream_t s) {
+// The one-feature kinds with rows of whole 16-byte pieces, at most 256 bytes (so at most four
+// 32-projection blocks): a wave keeps the W fragments of one block in registers and maps every
+// row tile of an item through it (with one or two blocks the waves share the row tiles), and
+// the item's 64 rows leave through LDS in consecutive pieces.  Reading W again for every 16
+// rows, |x|^2 by lanes and a division per piece stored made a 128-feature Performer map of
+// 64 heads of 4096 rows, d = 64, take 44 us, 37 now.
+template <typename Tin, int DH, int KIND>
+__global__ __launch_bounds__(256) void variant_rows_kernel(VariantArgs a) {
+  constexpr int KS = DH / 32, LOUT = KIND == kVarSinCos ? 2 : 1, RUN = 8 * LOUT;
+  __shared__ uint4 s_rows[2][64 * 16];
+  const int tid = threadIdx.x, wave = wave_id(), lane = tid % kWave;
+  const int g = lane / 16, r = lane % 16;
+  const int M = a.M;
+  const bool obf = a.out_bf16 != 0;
+  const int row_bytes = M * LOUT * (obf ? 2 : 4), chunks = row_bytes / 16;
+  const int blocks = M <= 32 ? 1 : M <= 64 ? 2 : 4;  // waves across the projections
+  const int q = wave % blocks, step = 4 / blocks;    // this wave's block; row tiles wave / blocks, + step, ...
+  const int base = 32 * q + 8 * g;                   // this lane's projections base .. base + 7
+  const int nfeat = max(0, min(8, M - base)) * LOUT;
+  // pieces of a row are swizzled by the row where their count is a power of two (all sixteen
+  // rows that a store takes would start on one bank)
+  const bool pow2 = (chunks & (chunks - 1)) == 0;
+  const int swz = pow2 ? chunks - 1 : 0, shift = pow2 ? __builtin_ctz(chunks) : 31;
+  const float inv_sqrt_m = 1.0f / sqrtf((float)M);
+  const float log2_scale = -0.5f * log2f((float)M), half_inv_sqrt_d = 0.5f / sqrtf((float)DH) * kLog2e;
+  const int64_t n = a.rows_per_head, tiles = (n + 63) / 64, items = a.heads * tiles;
+  auto locate = [&](int64_t item, int64_t* head, int64_t* t0) {
+    *head = items <= 0xffffffffll ? (int64_t)((unsigned)item / (unsigned)tiles) : item / tiles;
+    *t0 = (item - *head * tiles) * 64;
+  };
+  auto load = [&](Frag<Tin> (&x)[KS], int64_t item, int tile) {
+    int64_t head, t0;
+    locate(item, &head, &t0);
+    const auto rs = rows_rsrc(reinterpret_cast<const Tin*>(a.X) + (head * n + t0) * DH, 0, 64,
+                              (int)min((int64_t)64, n - t0), DH, sizeof(Tin));
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+      buf_load8(x[ks], rs, ((16 * tile + r) * DH + 32 * ks + 8 * g) * (int)sizeof(Tin));
+  };
+  // W rows permuted so that lane group g holds 8 consecutive projections of its row: A-operand
+  // row 4 g' + j of sub-block bl is projection 32 q + 8 g' + 4 bl + j, which the output puts
+  // in acc[bl][j] of lane group g'
+  Frag<Tin> wf[2][KS];
+  f32x4 bias[2];
+  int loaded = -1, buf = 0;
+  const int first = wave / blocks;
+  Frag<Tin> xn[KS];
+  load(xn, blockIdx.x, first);
+  for (int64_t item = blockIdx.x; item < items; item += gridDim.x, buf ^= 1) {
+    int64_t head, t0;
+    locate(item, &head, &t0);
+    const int hset = a.per_head ? (int)(head % a.H) : 0;
+    if (hset != loaded) {  // (uniform)
+      const Tin* W = reinterpret_cast<const Tin*>(a.W) + (size_t)hset * M * DH;
+#pragma unroll
+      for (int bl = 0; bl < 2; ++bl) {
+        const int prow = 32 * q + 8 * (r / 4) + 4 * bl + r % 4;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+          if (prow < M) load8(wf[bl][ks], W + (size_t)prow * DH + 32 * ks + 8 * g);
+          else wf[bl][ks].zero();
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int p = base + 4 * bl + j;
+          bias[bl][j] = p < M ? a.b[(size_t)hset * M + p] : 0.0f;
+        }
+      }
+      loaded = hset;
+    }
+    for (int tile = first; tile < 4; tile += step) {
+      Frag<Tin> x[KS];
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) x[ks] = xn[ks];
+      if (tile + step < 4) load(xn, item, tile + step);
+      else if (item + gridDim.x < items) load(xn, item + gridDim.x, first);
+      float k = 0.0f;
+      if constexpr (KIND == kVarPerformer) {  // |x|^2: the diagonal of x x^T
+        f32x4 xx = zero4();
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) mma(xx, x[ks], x[ks]);
+        const float lo = r % 2 ? xx[1] : xx[0], hi = r % 2 ? xx[3] : xx[2];
+        const float sq = __shfl(r % 4 < 2 ? lo : hi, 16 * (r / 4) + r, kWave);
+        k = fmaf(-sq, half_inv_sqrt_d, log2_scale);
+      }
+      float f[RUN];
+#pragma unroll
+      for (int bl = 0; bl < 2; ++bl) {
+        f32x4 u = bias[bl];
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) mma(u, wf[bl][ks], x[ks]);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int e = 4 * bl + j;
+          if constexpr (KIND == kVarCos) {
+            f[e] = 1.41421356237309505f * inv_sqrt_m * __builtin_amdgcn_cosf(to_turns(u[j]));
+          } else if constexpr (KIND == kVarSinCos) {
+            const float tu = to_turns(u[j]);
+            f[2 * e] = __builtin_amdgcn_sinf(tu) * inv_sqrt_m;
+            f[2 * e + 1] = __builtin_amdgcn_cosf(tu) * inv_sqrt_m;
+          } else {
+            f[e] = __builtin_amdgcn_exp2f(fmaf(u[j], kLog2e, k));
+          }
+        }
+      }
+      const int row = 16 * tile + r;
+      uint4* dst = s_rows[buf] + row * chunks;
+      const int piece = base * LOUT * (obf ? 2 : 4) / 16;
+      if (obf) {
+#pragma unroll
+        for (int c = 0; c < RUN / 8; ++c)
+          if (8 * c < nfeat) {
+            bf16x8 v;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = (__bf16)f[8 * c + e];
+            dst[(piece + c) ^ (row & swz)] = __builtin_bit_cast(uint4, v);
+          }
+      } else {
+#pragma unroll
+        for (int c = 0; c < RUN / 4; ++c)
+          if (4 * c < nfeat)
+            dst[(piece + c) ^ (row & swz)] = make_uint4(__float_as_uint(f[4 * c]), __float_as_uint(f[4 * c + 1]),
+                                                        __float_as_uint(f[4 * c + 2]), __float_as_uint(f[4 * c + 3]));
+      }
+    }
+    __syncthreads();  // the item's rows are whole; the other buffer's have left
+    const int pieces = (int)min((int64_t)64, n - t0) * chunks;
+    uint4* out = reinterpret_cast<uint4*>(reinterpret_cast<char*>(a.out) + (head * n + t0) * row_bytes);
+#pragma unroll
+    for (int c0 = 0; c0 < 64 * 16; c0 += 256) {
+      const int c = c0 + tid;
+      if (c < pieces) out[c] = s_rows[buf][c ^ ((c >> shift) & swz)];
+    }
+  }
+}
+
+// As many workgroups of the kernel as the device holds at once (registers and LDS
+// permitting), at most kVariantMaxGrid; more items loop.  The occupancy query runs once per
+// kernel.
+template <auto Kernel>
+hipError_t variant_launch_k(const VariantArgs& a, int64_t items, int* grid, hipStream_t s) {
   static const int resident = []() {
     int per_cu = 0, dev = 0, cus = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, variant_map_kernel<Tin, DH, KIND, ACT, LC, STAGED>, 256, 0) !=
-            hipSuccess ||
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, Kernel, 256, 0) != hipSuccess ||
         per_cu < 1)
       per_cu = 1;
     if (hipGetDevice(&dev) != hipSuccess) dev = 0;
@@ -492,26 +586,37 @@ hipError_t variant_launch(const VariantArgs& a, int64_t items, int* grid, hipStr
   }();
   const int g = (int)std::min<int64_t>(items, resident);
   *grid = g;
-  hipLaunchKernelGGL((variant_map_kernel<Tin, DH, KIND, ACT, LC, STAGED>), dim3(g), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(Kernel, dim3(g), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+template <typename Tin, int DH, int KIND, int ACT, int LC>
+hipError_t variant_launch(const VariantArgs& a, int64_t items, int* grid, hipStream_t s) {
+  return variant_launch_k<variant_map_kernel<Tin, DH, KIND, ACT, LC>>(a, items, grid, s);
+}
+
+template <typename Tin, int DH, int KIND>
+hipError_t variant_launch_rows(const VariantArgs& a, int64_t items, int* grid, hipStream_t s) {
+  *grid = (int)std::min<int64_t>(items, 1 << 14);
+  hipLaunchKernelGGL((variant_rows_kernel<Tin, DH, KIND>), dim3(*grid), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
 template <typename Tin, int DH>
 hipError_t variant_dispatch_kind(const VariantArgs& a, int64_t items, int* grid, hipStream_t s) {
   // one-feature kinds whose output rows are whole 16-byte pieces, at most 256 bytes, at
-  // an aligned address: rows staged in LDS and written back contiguously
+  // an aligned address: their own kernel
   const int row_bytes = a.M * (a.kind == kVarSinCos ? 2 : 1) * (a.out_bf16 ? 2 : 4);
-  const bool stage = row_bytes % 16 == 0 && row_bytes <= 256 && (reinterpret_cast<uintptr_t>(a.out) & 15) == 0;
+  const bool rows = row_bytes % 16 == 0 && row_bytes <= 256 && (reinterpret_cast<uintptr_t>(a.out) & 15) == 0;
   switch (a.kind) {
     case kVarCos:
-      return stage ? variant_launch<Tin, DH, kVarCos, 0, 1, true>(a, items, grid, s)
-                   : variant_launch<Tin, DH, kVarCos, 0, 1>(a, items, grid, s);
+      return rows ? variant_launch_rows<Tin, DH, kVarCos>(a, items, grid, s)
+                  : variant_launch<Tin, DH, kVarCos, 0, 1>(a, items, grid, s);
     case kVarSinCos:
-      return stage ? variant_launch<Tin, DH, kVarSinCos, 0, 1, true>(a, items, grid, s)
-                   : variant_launch<Tin, DH, kVarSinCos, 0, 1>(a, items, grid, s);
+      return rows ? variant_launch_rows<Tin, DH, kVarSinCos>(a, items, grid, s)
+                  : variant_launch<Tin, DH, kVarSinCos, 0, 1>(a, items, grid, s);
     case kVarPerformer:
-      return stage ? variant_launch<Tin, DH, kVarPerformer, 0, 1, true>(a, items, grid, s)
-                   : variant_launch<Tin, DH, kVarPerformer, 0, 1>(a, items, grid, s);
+      return rows ? variant_launch_rows<Tin, DH, kVarPerformer>(a, items, grid, s)
+                  : variant_launch<Tin, DH, kVarPerformer, 0, 1>(a, items, grid, s);
     case kVarMlp: break;
     default: return hipErrorInvalidValue;
   }

@@ -362,6 +362,22 @@ def test_attn_causal_equal_parts(dtype, d, M, L, B, H, n):
     assert_close_rows(pick(out), ref, dtype, "out")
 
 
+@pytest.mark.parametrize("dtype,d,M,L,B,H,n", [
+    ("f32", 32, 8, 8, 1, 1, 256), ("bf16", 64, 16, 8, 1, 4, 64), ("bf16", 64, 16, 8, 1, 64, 257), ("f32", 64, 16, 4, 1, 3, 129),
+    ("bf16", 128, 32, 8, 2, 32, 255), ("bf16", 128, 32, 8, 1, 33, 512), ("bf16", 32, 8, 8, 1, 1, 4500)])
+def test_attn_noncausal_few_heads(dtype, d, M, L, B, H, n):
+    """Few workgroups of state and readout: token ranges of 128 and 256 tokens, readout tiles
+    of 64 and 256, on either side of both limits, and more ranges than one batch of loads."""
+    w = small_workload(dtype, B=B, H=H, n=n, d=d, M=M, L=L)
+    say(f"non-causal few heads {dtype} d={d} M={M} L={L} B={B} H={H} n={n}")
+    Q, K, V, p = inputs(w, seed=81)
+    (Qt, Kt, Vt), pt = upload(w, [Q, K, V], p)
+    out = to_np(luna.attn_fwd(Qt, Kt, Vt, pt, eps=w.eps))
+    hs = sorted({0, H // 2, H - 1})
+    pick = lambda X: X[:, hs]  # noqa: E731
+    assert_close_rows(pick(out), oracle.attn_noncausal(pick(Q), pick(K), pick(V), p, eps=w.eps), dtype, "out")
+
+
 def test_attn_causal_workload_full_size():
     w = wl.WORKLOADS["long_causal"]
     say("causal full size long_causal")

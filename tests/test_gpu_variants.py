@@ -187,3 +187,19 @@ def test_attn_features_noncausal_edges(pdt, dt, d, D, n):
     V, Vr = _upload_rounded(rng.standard_normal((2, 3, n, d)), dt)
     out = to_np(luna.attn_fwd_features(fq, fk, V))
     assert_close(out, VAR.attn_from_features(fqr, fkr, Vr), dt, "out")
+
+
+@pytest.mark.parametrize("kind,dtype,d,M,n", [
+    ("performer", "bf16", 64, 128, 200), ("performer", "f32", 128, 64, 63), ("rff_cos", "bf16", 32, 8, 65),
+    ("rff_cos", "f32", 64, 36, 64), ("rff_cos", "bf16", 128, 72, 1), ("rff_sincos", "bf16", 64, 12, 129),
+    ("rff_sincos", "f32", 32, 32, 130), ("rff_sincos", "bf16", 128, 64, 77), ("performer", "bf16", 64, 96, 128)])
+def test_featuremap_variant_rows(kind, dtype, d, M, n):
+    """One-feature kinds with rows of whole 16-byte pieces up to 256 bytes: one, two and four
+    projection blocks across the waves, piece counts that are and are not powers of two,
+    feature counts off the 8- and 32-projection steps, rows off the 64-row items."""
+    say(f"variant rows {kind} {dtype} d={d} M={M} n={n}")
+    rng = np.random.default_rng(zlib.crc32(f"rows/{kind}/{d}/{M}/{n}".encode()))
+    p = _variant_params(rng, kind, M, d)
+    X = rng.standard_normal((2, 3, n, d))
+    got, ref = _run_variant(p, X, dtype)
+    assert_close(got, ref, dtype, "phi")
