@@ -367,7 +367,7 @@ size_t luna_attn_features_workspace_bytes(luna_dtype phi_dtype, luna_dtype dtype
  * (causal = 1) over the prefix s <= t, evaluated as the chunked scan with chunk 64.
  * Features may be signed: the denominator is then the caller's concern.  Non-causal calls
  * with d in {32, 64, 128} and D <= 256 read the features in their own type (sums in fp32);
- * the others run on the fp32 GEMM path (bf16 features widened to fp32), or, for causal bf16
+ * the others run on the fp32 path (bf16 features widened to fp32), or, for causal bf16
  * calls with (d, D) = (128, 256) or (64, 128), on the causal scan kernel.
  * 1 <= d <= 256, 1 <= D <= 512.
  */

@@ -129,7 +129,15 @@ luna_status plan_f32_buffers(int64_t heads, int64_t n, int d, int D, bool causal
   if (queries && features) take(lay->phiq, rows * D * 4);
   if (features) take(lay->phik, rows * D * 4);
   if (lay->chunked) {
+    // The size asked for stays that of the GEMM form below (larger but for short sequences of
+    // many features), which callers' workspaces may have been sized by.
+    const size_t gemm_states = (size_t)heads * (size_t)((n + (causal ? 63 : 511)) / (causal ? 64 : 512));
+    size_t asked = align256(*off + rows * (d + 1) * 4);
+    if (queries) asked = align256(asked + rows * (d + 1) * 4);
+    asked = align256(asked + gemm_states * D * (d + 1) * 4);
+    if (causal && queries) asked = align256(asked + gemm_states * 64 * 64 * 4);
     take(lay->sx, states * (size_t)luna::feat_elems(d, D) * 4);
+    if (*off < asked) *off = asked;
     return LUNA_OK;
   }
   take(lay->vx, rows * (d + 1) * 4);
@@ -675,7 +683,8 @@ size_t variant_ws_bytes(const luna_phi_variant* v, int64_t rows) {
 }
 
 // Buffers of luna_attn_fwd_features: the causal scan kernel on the bf16 features when
-// it is built for (d, D), else the fp32 GEMM path (fp32 copies of bf16 features).
+// it is built for (d, D), non-causal the kernels on features in their own type, else the
+// fp32 path (fp32 copies of bf16 features).
 luna_status plan_features(luna_dtype phi_dtype, luna_dtype dtype, int64_t B, int64_t H, int64_t n, int64_t d,
                           int64_t D, int32_t causal, int32_t chunk, Layout* lay) {
   if ((phi_dtype != LUNA_F32 && phi_dtype != LUNA_BF16) || (dtype != LUNA_F32 && dtype != LUNA_BF16))

@@ -113,17 +113,36 @@ __global__ __launch_bounds__((map_threads<T, DH, L, PACK>())) void map_bwd_kerne
   const float floor = tab.floor;
   const float rsm = 1.0f / sqrtf((float)M);
   const RowRuns rr = row_runs(a.n, a.heads, a.H, a.per_head, set);
+  const auto bw = rows_rsrc(W, 0, M, M, DH, sizeof(T));  // (projections past M read as 0)
   const int64_t tps = (rr.rows + TR - 1) / TR, per_side = rr.segs * tps;
   const bool vec = (M * L) % 4 == 0;  // rows of dphi (and, with M % 4, of du) start 16-byte aligned
   const bool vecu = M % 4 == 0;
-  for (int64_t t = (int64_t)blockIdx.x * nwaves + wave; t < 2 * per_side; t += (int64_t)gridDim.x * nwaves) {
+  // The rows of step t (B operands; past a run's last they read as 0).  With 8 waves, too few
+  // to cover their latency, they are asked for a step ahead (92 us instead of 98 for 2 x 65,536
+  // rows of 128 elements and 32 projections); 16 waves have no registers for it.
+  constexpr bool AHEAD = map_threads<T, DH, L, PACK>() == 512;
+  auto load_rows = [&](Frag<T> (&xf)[NT][KS], int64_t t) {
     const bool key = t >= per_side;
     const int64_t ts = key ? t - per_side : t;
-    const int64_t seg = ts / tps, t0 = (ts - seg * tps) * TR;
+    const int64_t seg = rr.segs == 1 ? 0 : ts / tps, t0 = (ts - seg * tps) * TR;
+    const auto rs = rows_rsrc(reinterpret_cast<const T*>(key ? a.xk : a.xq) + (rr.first + seg * rr.seg_stride + t0) * DH,
+                              0, TR, (int)min((int64_t)TR, rr.rows - t0), DH, sizeof(T));
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+        buf_load8(xf[i][ks], rs, ((16 * i + r) * DH + 32 * ks + 8 * g) * (int)sizeof(T));
+  };
+  const int64_t first = (int64_t)blockIdx.x * nwaves + wave, stride = (int64_t)gridDim.x * nwaves;
+  Frag<T> xn[NT][KS];
+  if (AHEAD && first < 2 * per_side) load_rows(xn, first);
+  for (int64_t t = first; t < 2 * per_side; t += stride) {
+    const bool key = t >= per_side;
+    const int64_t ts = key ? t - per_side : t;
+    const int64_t seg = rr.segs == 1 ? 0 : ts / tps, t0 = (ts - seg * tps) * TR;
     const int64_t base = rr.first + seg * rr.seg_stride;
-    const T* X = reinterpret_cast<const T*>(key ? a.xk : a.xq);
     const float* dphi = key ? a.dphik : a.dphiq;
-    // this lane's row of each tile (B operand), and the row whose projections it holds
+    // this lane's row of each tile, and the row whose projections it holds
     int64_t xrow[NT];
     bool xok[NT];
     Frag<T> xf[NT][KS];
@@ -133,11 +152,11 @@ __global__ __launch_bounds__((map_threads<T, DH, L, PACK>())) void map_bwd_kerne
       xok[i] = tr < rr.rows;
       xrow[i] = base + (xok[i] ? tr : t0);
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        if (xok[i]) load8(xf[i][ks], X + xrow[i] * DH + 32 * ks + 8 * g);
-        else xf[i][ks].zero();
-      }
+      for (int ks = 0; ks < KS; ++ks)
+        if constexpr (AHEAD) xf[i][ks] = xn[i][ks];
     }
+    if constexpr (!AHEAD) load_rows(xf, t);
+    else if (t + stride < 2 * per_side) load_rows(xn, t + stride);
     const int mine = PACK ? g / 2 : 0;  // the tile whose projections this lane holds
     const int64_t row = mine ? xrow[NT - 1] : xrow[0];
     const bool ok = mine ? xok[NT - 1] : xok[0];
@@ -169,8 +188,7 @@ __global__ __launch_bounds__((map_threads<T, DH, L, PACK>())) void map_bwd_kerne
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
           Frag<T> wf;
-          if (prow >= 0 && prow < M) load8(wf, W + (size_t)prow * DH + 32 * ks + 8 * g);
-          else wf.zero();
+          buf_load8(wf, bw, prow >= 0 ? (prow * DH + 32 * ks + 8 * g) * (int)sizeof(T) : 0x7ffffff0);
           mma(acc, widen(wf), widen(xf[i][ks]));
         }
       }

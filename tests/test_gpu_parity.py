@@ -308,10 +308,10 @@ def test_attn_causal_small(dtype, d, M, L, n):
 @pytest.mark.parametrize("M,L", [(32, 8), (256, 1)])
 @pytest.mark.parametrize("B,H,n", [(1, 3, 1000), (4, 25, 650), (8, 20, 300)])
 def test_attn_causal_state_pieces(B, H, n, M, L):
-    """With fewer than 256 heads each head is cut at x (n/2 rounded down to whole
+    """With 86 to 255 heads each head is cut at x (n/2 rounded down to whole
     chunks) and the state of [0, x) is summed in pieces, one workgroup per head and
-    piece: seven one-chunk pieces (3 heads), two pieces (160 heads); 100 heads take the
-    staged form (two scan launches) instead.
+    piece: two pieces (160 heads); 100 heads take the staged form (two scan launches)
+    and 3 heads equal parts of one chunk instead.
     Checked against the oracle on sampled heads (the parameters are shared).  M = 256,
     L = 1: the features are mapped beforehand and the kernel reads them."""
     w = small_workload("bf16", B=B, H=H, n=n, d=128, M=M, L=L, causal=True)
