@@ -222,7 +222,9 @@ struct Pack4<float> {
 
 // ST: the state launch (state-only chunks, S and z dumped); otherwise a scan launch.
 // PF: the features are given (a.phiq, a.phik); L = 1 and MB = FP / 16.
-template <typename T, int DH, int L, int MB, bool ST, bool PF>
+// EQ: a scan launch over equal parts (its own instantiation: the part arithmetic in the others
+// cost the staged launches 0.5%).
+template <typename T, int DH, int L, int MB, bool ST, bool PF, bool EQ = false>
 __global__ __launch_bounds__(512, 1) void causal_kernel(CausalArgs a) {
   using C = CsCfg<T, DH, L, MB, PF>;
   constexpr int KS = C::KS, FP = C::FP, NF = C::NF, RB = C::RB, VE = C::VE, NMW = C::NMW, NMS = C::NMS;
@@ -255,12 +257,12 @@ __global__ __launch_bounds__(512, 1) void causal_kernel(CausalArgs a) {
     c_end = min(a.split / 64, c_first + a.piece_chunks);
     c_begin = c_end;
     t_end = 0;
-  } else if (a.staged) {
+  } else if (!EQ && a.staged) {
     c_first = part == 0 ? a.pc_first[0] : a.pc_first[1];
     c_begin = part == 0 ? a.pc_begin[0] : a.pc_begin[1];
     c_end = part == 0 ? a.pc_end[0] : a.pc_end[1];
     t_end = min(n, 64 * c_end);
-  } else if (a.part_chunks > 0) {
+  } else if (EQ) {
     c_first = c_begin = part * a.part_chunks;
     c_end = min((n + 63) / 64, c_begin + a.part_chunks);
     t_end = min(n, 64 * c_end);
@@ -274,10 +276,11 @@ __global__ __launch_bounds__(512, 1) void causal_kernel(CausalArgs a) {
   // part 1 of the scan launch starts from the state of the first c_first chunks: the
   // sum of the pieces, in piece order (a staged part from the sum of its first npc)
   // (with equal parts the one running sum before it)
-  const int npc = a.staged ? (part == 0 ? a.pseed[0] : a.pseed[1]) : a.part_chunks > 0 ? 1 : a.pieces;
-  const bool seeded = !state_run && (a.staged ? npc > 0 : c_first > 0);
-  const int first_piece = a.part_chunks > 0 ? part - 1 : 0;
-  const float* seed = seeded ? a.state_in + (size_t)(head * a.pieces + first_piece) * C::STATE : nullptr;
+  const int npc = EQ ? 1 : a.staged ? (part == 0 ? a.pseed[0] : a.pseed[1]) : a.pieces;
+  const bool seeded = !state_run && (!EQ && a.staged ? npc > 0 : c_first > 0);
+  const float* seed = seeded ? a.state_in + (size_t)head * a.pieces * C::STATE : nullptr;
+  if constexpr (EQ)
+    if (seeded) seed += (size_t)(part - 1) * C::STATE;
 
   // Q, K, V rows of chunk cc and the output rows of chunk cc as range-checked
   // buffers: rows at or past n (t_end for the output) read as 0 and are not written.
@@ -1124,6 +1127,8 @@ static hipError_t cs_run(const CausalArgs& a, hipStream_t s) {
   const int per_head = a.state_out != nullptr ? a.pieces : a.parts;
   if (a.state_out != nullptr)
     hipLaunchKernelGGL((causal_kernel<T, DH, L, MB, true, false>), dim3(a.heads * per_head), dim3(512), 0, s, a);
+  else if (a.part_chunks > 0)
+    hipLaunchKernelGGL((causal_kernel<T, DH, L, MB, false, false, true>), dim3(a.heads * per_head), dim3(512), 0, s, a);
   else
     hipLaunchKernelGGL((causal_kernel<T, DH, L, MB, false, false>), dim3(a.heads * per_head), dim3(512), 0, s, a);
   return hipGetLastError();
@@ -1136,6 +1141,9 @@ static hipError_t cs_run_given(const CausalArgs& a, hipStream_t s) {
   if (a.state_out != nullptr)
     hipLaunchKernelGGL((causal_kernel<__bf16, DH, 1, FP / 16, true, true>), dim3(a.heads * per_head), dim3(512), 0,
                        s, a);
+  else if (a.part_chunks > 0)
+    hipLaunchKernelGGL((causal_kernel<__bf16, DH, 1, FP / 16, false, true, true>), dim3(a.heads * per_head),
+                       dim3(512), 0, s, a);
   else
     hipLaunchKernelGGL((causal_kernel<__bf16, DH, 1, FP / 16, false, true>), dim3(a.heads * per_head), dim3(512), 0,
                        s, a);
