@@ -28,6 +28,23 @@ __device__ __forceinline__ Frag<float> widen(const Frag<__bf16>& f) {
 }
 __device__ __forceinline__ Frag<float> widen(const Frag<float>& f) { return f; }
 
+// an operand, or zeros in the lanes where `keep` is false
+__device__ __forceinline__ Frag<float> only(Frag<float> f, bool keep) {
+#pragma unroll
+  for (int e = 0; e < 8; ++e) f.v[e] = keep ? f.v[e] : 0.0f;
+  return f;
+}
+__device__ __forceinline__ Split3 only(Split3 s, bool keep) {
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    i32x4 w = __builtin_bit_cast(i32x4, s.p[k].v);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) w[i] = keep ? w[i] : 0;
+    s.p[k].v = __builtin_bit_cast(bf16x8, w);
+  }
+  return s;
+}
+
 // Rows: a parameter set's rows of one side are `segs` runs of `rows` rows, `seg_stride`
 // rows apart, the first at row `first` (one run of all heads' rows when the set is
 // shared; one run per batch entry otherwise).
@@ -62,9 +79,9 @@ constexpr int map_threads() {
 // LDS as fragments of that order.
 //
 // PACK (M <= 8): half the lanes would hold padding projections.  Two tiles of 16 rows
-// share the block instead: the first multiplies W in block rows 0-7, the second W in
-// rows 8-15, so lanes g < 2 hold the first tile's and g >= 2 the second's projections,
-// and dx takes W^T fragments that are zero for the other tile's slots.
+// share the block instead: W fills block rows 0-7 and 8-15, lanes g < 2 keep the first
+// tile's projections and g >= 2 the second's, and dx takes du and W^T fragments that are
+// zero for the other tile's slots (both: a row that is not finite stays alone).
 //
 // The moments are LDS atomics in fp64: an fp32 LDS atomic takes 195 cycles per wave
 // instruction here (a probe with one workgroup of 8 waves per CU; 3 cycles a lane whatever
@@ -181,17 +198,18 @@ __global__ __launch_bounds__((map_threads<T, DH, L, PACK>())) void map_bwd_kerne
           for (int l = 0; l < L; ++l)
             gv[j][l] = ok && p0 + j < M ? dphi[row * D + (int64_t)(p0 + j) * L + l] : 0.0f;
       }
-      f32x4 acc = zero4();
+      f32x4 us[NT];
 #pragma unroll
-      for (int i = 0; i < NT; ++i) {
-        const int prow = PACK ? r - 8 * i : 16 * mb + r;  // W row this lane feeds to the A operand
+      for (int i = 0; i < NT; ++i) us[i] = zero4();
+      const int prow = PACK ? r % 8 : 16 * mb + r;  // W row this lane feeds to the A operand
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          Frag<T> wf;
-          buf_load8(wf, bw, prow >= 0 ? (prow * DH + 32 * ks + 8 * g) * (int)sizeof(T) : 0x7ffffff0);
-          mma(acc, widen(wf), widen(xf[i][ks]));
-        }
+      for (int ks = 0; ks < KS; ++ks) {
+        Frag<T> wf;
+        buf_load8(wf, bw, (prow * DH + 32 * ks + 8 * g) * (int)sizeof(T));
+#pragma unroll
+        for (int i = 0; i < NT; ++i) mma(us[i], widen(wf), widen(xf[i][ks]));
       }
+      const f32x4 acc = mine ? us[NT - 1] : us[0];
       float u[4];
       int sg[4];
 #pragma unroll
@@ -246,9 +264,12 @@ __global__ __launch_bounds__((map_threads<T, DH, L, PACK>())) void map_bwd_kerne
       Operand<float, T> dw;
       set_operand(dw, df);
 #pragma unroll
-      for (int i = 0; i < NT; ++i)
+      for (int i = 0; i < NT; ++i) {
+        // (the other tile's slots as 0: W^T's own zeros would turn its infinities into NaN here)
+        const Operand<float, T> di = PACK ? only(dw, mine == i) : dw;
 #pragma unroll
-        for (int cb = 0; cb < CB; ++cb) mma(dx[i][cb], wt[PACK ? i : mb / 2][cb][lane], dw);
+        for (int cb = 0; cb < CB; ++cb) mma(dx[i][cb], wt[PACK ? i : mb / 2][cb][lane], di);
+      }
     }
     if (!want_dx) continue;
     T* dX = reinterpret_cast<T*>(key ? a.dxk : a.dxq);

@@ -135,3 +135,25 @@ def test_attn_bwd_rejects_bad_arguments():
         luna.attn_bwd(Qt, Kt, Vt, Qt[..., :32].contiguous(), pt)
     with pytest.raises(luna.LunaError):
         luna.attn_bwd(Qt, Kt, Vt, Qt.to(torch.bfloat16), pt)
+
+
+@pytest.mark.parametrize("bad", ["dO", "Q"])
+@pytest.mark.parametrize("dtype,M", [("f32", 8), ("bf16", 8), ("bf16", 5), ("bf16", 16)])
+def test_attn_bwd_rows_stay_apart(dtype, M, bad):
+    """A NaN in one query row (its own or its gradient's) leaves dQ of every other row as it
+    is without: with at most 8 projections the feature-map gradients take two row tiles, 16
+    rows apart, in one matrix block, whose zero entries must not meet the other tile's rows."""
+    import torch
+    w = small_workload(dtype, B=1, H=2, n=75, d=64, M=M, L=8)
+    say(f"backward rows stay apart {w.name} bad={bad}")
+    Q, K, V, p = inputs(w, seed=51)
+    dO = np.random.default_rng(52).standard_normal(Q.shape).astype(np.float32)
+    (Qt, Kt, Vt, dOt), pt = upload(w, [Q, K, V, dO], p)
+    clean = luna.attn_bwd(Qt, Kt, Vt, dOt, pt, eps=w.eps)[0]
+    rows = [5, 40, 74]
+    t = dOt if bad == "dO" else Qt
+    t[:, :, rows, 7] = float("nan")
+    got = luna.attn_bwd(Qt, Kt, Vt, dOt, pt, eps=w.eps)[0]
+    others = [r for r in range(w.n) if r not in rows]
+    assert torch.isfinite(clean.float()).all()
+    assert torch.equal(got[:, :, others], clean[:, :, others])
