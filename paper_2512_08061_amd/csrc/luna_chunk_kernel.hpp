@@ -85,18 +85,10 @@ __device__ __forceinline__ void col8(Frag<__bf16>& f, Buf b, int at, int stride)
 __device__ __forceinline__ void mma_value(f32x4&, f32x4& lo, const Frag<float>& a, const Frag<float>& b) {
   mma(lo, a, b);
 }
-template <typename A, typename B>
-__device__ __forceinline__ void mma_parts(f32x4& c, f32x4& lo, const A& a2, const A& a1, const A& a0, const B& b2,
-                                          const B& b1, const B& b0) {
-  mma(lo, a2, b2);
-  mma(lo, a1, b1);
-  mma(c, a0, b0);
-}
-__device__ __forceinline__ void mma_value(f32x4& c, f32x4& lo, const Frag<__bf16>& a, const Split3& b) {
-  mma_parts(c, lo, a, a, a, b.p[2], b.p[1], b.p[0]);
-}
 __device__ __forceinline__ void mma_value(f32x4& c, f32x4& lo, const Split3& a, const Frag<__bf16>& b) {
-  mma_parts(c, lo, a.p[2], a.p[1], a.p[0], b, b, b);
+  mma(lo, a.p[2], b);
+  mma(lo, a.p[1], b);
+  mma(c, a.p[0], b);
 }
 
 // P in LDS as the other operand of a value: split in bf16 planes, or fp32
@@ -115,11 +107,6 @@ __device__ __forceinline__ void put_p(const f32x4& p, __bf16* dst, int plane) {
   }
 }
 __device__ __forceinline__ void put_p(const f32x4& p, float* dst, int) { *reinterpret_cast<f32x4*>(dst) = p; }
-__device__ __forceinline__ void get_p(Split3& s, const __bf16* src, int plane) {
-#pragma unroll
-  for (int k = 0; k < 3; ++k) s.p[k].v = *reinterpret_cast<const bf16x8*>(src + k * plane);
-}
-__device__ __forceinline__ void get_p(Frag<float>& f, const float* src, int) { load8(f, src); }
 
 // KB: 32-feature steps held (D <= 32 KB)
 template <typename T, int DH, int KB>
@@ -315,14 +302,41 @@ __global__ __launch_bounds__(kCkThreads, KB <= 4 ? 4 : 2) void chunk_kernel(Chun
       put_p(p[b], ps + (16 * (sr + b) + r) * LDP + 16 * sc + 4 * g, PP);
     }
     __syncthreads();
+    auto p_of = [&](int ks, int b, int k) {
+      Frag<T> p;
+      load8(p, ps + k * PP + (16 * (rb1 + b) + r) * LDP + 32 * ks + 8 * g);
+      return p;
+    };
+    bool rest = true;  // (the parts gather as in mma_value)
+    if constexpr (sizeof(T) == 2)
+      if (__any(not_finite(va[0]) || not_finite(va[1]))) {  // (uniform) the first parts, then the others by 1
+        rest = false;
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks)
+        for (int ks = 0; ks < 2; ++ks) {
 #pragma unroll
-      for (int b = 0; b < R1; ++b) {
-        SOp pb;
-        get_p(pb, ps + (16 * (rb1 + b) + r) * LDP + 32 * ks + 8 * g, PP);
-        mma_value(num[b], lo1[b], va[ks], pb);
+          for (int b = 0; b < R1; ++b) mma(num[b], va[ks], p_of(ks, b, 0));
+          to_ones(va[ks]);
+#pragma unroll
+          for (int b = 0; b < R1; ++b) {
+            mma(lo1[b], va[ks], p_of(ks, b, 2));
+            mma(lo1[b], va[ks], p_of(ks, b, 1));
+          }
+        }
       }
+    if (rest) {
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int b = 0; b < R1; ++b) {
+          if constexpr (sizeof(T) == 2) {
+            mma(lo1[b], va[ks], p_of(ks, b, 2));
+            mma(lo1[b], va[ks], p_of(ks, b, 1));
+            mma(num[b], va[ks], p_of(ks, b, 0));
+          } else {
+            mma(lo1[b], va[ks], p_of(ks, b, 0));
+          }
+        }
+    }
   }
 #pragma unroll
   for (int b = 0; b < R1; ++b) num[b] += lo1[b];

@@ -122,7 +122,8 @@ __global__ __launch_bounds__(256) void feat_state_kernel(FeatArgs a) {
           z[f] += x.get(e);
         }
       }
-      set_operand(af[f], x);
+      if constexpr (sizeof(TF) > sizeof(T)) split3<false>(af[f], x.v);  // (checked below)
+      else set_operand(af[f], x);
     }
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb) {
@@ -137,18 +138,59 @@ __global__ __launch_bounds__(256) void feat_state_kernel(FeatArgs a) {
     }
   }
   float* S = a.state + blockIdx.x * a.elems;
+  auto store = [&](const f32x4& c, int f, int cb) {
+    const int f0 = 16 * (wave + 4 * f) + 4 * g;
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (f0 + j < D) S[(f0 + j) * DH + 16 * cb + r] = c[j];
+  };
+  bool nan = false;
 #pragma unroll
   for (int f = 0; f < FBW; ++f) {
     z[f] += __shfl_xor(z[f], 16, kWave);
     z[f] += __shfl_xor(z[f], 32, kWave);
     const int f0 = 16 * (wave + 4 * f);
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (f0 + 4 * g + j < D) S[(f0 + 4 * g + j) * DH + 16 * cb + r] = acc[f][cb][j];
+    for (int cb = 0; cb < CB; ++cb) {
+      const f32x4 c = acc[f][cb];
+      store(c, f, cb);
+      nan = nan || __builtin_isunordered(c[0], c[1]) || __builtin_isunordered(c[2], c[3]);
+    }
     if (g == 0 && f0 + r < D) S[D * DH + f0 + r] = z[f];
   }
+  // fp32 features beside bf16 values: an infinite value, or a feature above the largest bf16
+  // one, has met parts of either sign, and such sums end as NaN.  They are formed again as fp32
+  // products, each wave's from memory.
+  if constexpr (sizeof(TF) > sizeof(T))
+    if (__any(nan)) {  // (uniform)
+#pragma unroll 1
+      for (int cb = 0; cb < CB; ++cb) {
+        f32x4 c[FBW];
+#pragma unroll
+        for (int f = 0; f < FBW; ++f) c[f] = zero4();
+        for (int t0 = 0; t0 < rows; t0 += kFsTok) {
+          Frag<float> x[FBW];
+          Frag<T> y;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const int t = t0 + 8 * g + e;
+            const float w = WGT && t < rows ? reinterpret_cast<const float2*>(a.w)[head * a.n + first + t].x : 1.0f;
+#pragma unroll
+            for (int f = 0; f < FBW; ++f) {
+              const int k = 16 * (wave + 4 * f) + r;
+              x[f].v[e] = w * __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                                  bphi, k < D ? (t * D + k) * (int)sizeof(TF) : kPastEnd, 0, 0));
+            }
+            y.v[e] = __builtin_bit_cast(
+                T, __builtin_amdgcn_raw_buffer_load_b16(bv, (t * DH + 16 * cb + r) * (int)sizeof(T), 0, 0));
+          }
+#pragma unroll
+          for (int f = 0; f < FBW; ++f) mma(c[f], x[f], widen(y));
+        }
+#pragma unroll
+        for (int f = 0; f < FBW; ++f) store(c[f], f, cb);
+      }
+    }
 }
 
 // ---------------------------------------------------------------------------

@@ -20,14 +20,6 @@ namespace luna {
 
 namespace {
 
-__device__ __forceinline__ Frag<float> widen(const Frag<__bf16>& f) {
-  Frag<float> w;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) w.v[e] = f.get(e);
-  return w;
-}
-__device__ __forceinline__ Frag<float> widen(const Frag<float>& f) { return f; }
-
 // an operand, or zeros in the lanes where `keep` is false
 __device__ __forceinline__ Frag<float> only(Frag<float> f, bool keep) {
 #pragma unroll

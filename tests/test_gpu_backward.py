@@ -157,3 +157,37 @@ def test_attn_bwd_rows_stay_apart(dtype, M, bad):
     others = [r for r in range(w.n) if r not in rows]
     assert torch.isfinite(clean.float()).all()
     assert torch.equal(got[:, :, others], clean[:, :, others])
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d,M,L", [(64, 16, 8), (128, 32, 8), (32, 16, 2)])
+def test_attn_bwd_infinite_gradient(d, M, L, causal):
+    """A bf16 infinity in dO meets fp32 features as in fp32 products: its column of dV is
+    infinite (not NaN) for every key that the row sees, and nothing else of dV and of the other
+    rows' dQ changes."""
+    import torch
+    n, t, c = 200, 70, 3
+    w = small_workload("bf16", B=1, H=2, n=n, d=d, M=M, L=L, causal=causal)
+    say(f"backward infinite gradient {w.name} causal={causal}")
+    Q, K, V, p = inputs(w, seed=53)
+    p = dict(p, fc2_b=p["fc2_b"] + 1.0)  # (positive kernels)
+    dO = np.random.default_rng(54).standard_normal(Q.shape).astype(np.float32)
+    (Qt, Kt, Vt, dOt), pt = upload(w, [Q, K, V, dO], p)
+    dOt[:, :, t, c] = 0.0
+    cQ, _, cV, _ = luna.attn_bwd(Qt, Kt, Vt, dOt, pt, causal=causal, eps=w.eps)
+    dOt[0, :, t, c] = torch.tensor([float("inf"), -float("inf")])
+    gQ, _, gV, _ = luna.attn_bwd(Qt, Kt, Vt, dOt, pt, causal=causal, eps=w.eps)
+    phiQ, phiK = oracle.featuremap(Q, p), oracle.featuremap(K, p)
+    kern = (phiK @ phiQ[0, :, t, :, None])[0, ..., 0]  # [H][n]
+    last = t + 1 if causal else n
+    assert (kern[:, :last] > 1e-3).all()
+    got = to_np(gV)[0]
+    assert (got[0, :last, c] == np.inf).all() and (got[1, :last, c] == -np.inf).all()
+    if causal:  # (in the row's own 64-token tile the masked keys meet it as 0 times infinity)
+        assert np.isfinite(got[:, 128:, c]).all()
+    cols = [i for i in range(d) if i != c]
+    # (summed in another order they may round to the neighbouring bf16 value)
+    a, b = gV[..., cols].float(), cV[..., cols].float()
+    assert ((a - b).abs() <= 2.0 ** -7 * b.abs() + 1e-5 * b.abs().max()).all()
+    rows = [r for r in range(n) if r != t]
+    assert torch.equal(gQ[:, :, rows], cQ[:, :, rows])

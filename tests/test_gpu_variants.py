@@ -203,3 +203,80 @@ def test_featuremap_variant_rows(kind, dtype, d, M, n):
     X = rng.standard_normal((2, 3, n, d))
     got, ref = _run_variant(p, X, dtype)
     assert_close(got, ref, dtype, "phi")
+
+
+def _positive_features(rng, shape):
+    return np.exp(rng.standard_normal(shape) * 0.5) / math.sqrt(shape[-1])
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("d,D,n", [(32, 48, 200), (64, 128, 700), (128, 256, 200)])
+def test_attn_features_infinite_values(d, D, n, causal):
+    """A bf16 infinity in V beside fp32 features: its column is infinite (not NaN) for every
+    row that sees it, the other columns are as without it."""
+    say(f"features beside infinite values d={d} D={D} n={n} causal={causal}")
+    rng = np.random.default_rng(45 + D)
+    fq, rq = _upload_rounded(_positive_features(rng, (1, 2, n, D)), "f32")
+    fk, rk = _upload_rounded(_positive_features(rng, (1, 2, n, D)), "f32")
+    V, rv = _upload_rounded(rng.standard_normal((1, 2, n, d)), "bf16")
+    t, c = 70, 3
+    for h, x in enumerate((math.inf, -math.inf)):
+        V[0, h, t, c] = x
+        rv[0, h, t, c] = 0.0
+    got = to_np(luna.attn_fwd_features(fq, fk, V, causal=causal))
+    ref = VAR.attn_from_features(rq, rk, rv, causal=causal)
+    first = t if causal else 0
+    assert (got[0, 0, first:, c] == math.inf).all() and (got[0, 1, first:, c] == -math.inf).all()
+    cols = [i for i in range(d) if i != c]
+    assert_close_rows(got[..., cols], ref[..., cols], "bf16", "other columns")
+    if causal:  # (rows before t in its own 64-token tile meet it as 0 times infinity)
+        assert_close_rows(got[:, :, :64], ref[:, :, :64], "bf16", "rows before its tile")
+
+
+@pytest.mark.parametrize("d,M", [(128, 256), (128, 200), (64, 100)])
+def test_attn_state_infinite_value(d, M):
+    """The same in the state of shapes whose features are held in fp32."""
+    from gpu_util import inputs, small_workload, upload
+    import torch
+    n, t, c = 600, 70, 3
+    w = small_workload("bf16", B=1, H=2, n=n, d=d, M=M, L=1)
+    say(f"state beside an infinite value {w.name}")
+    _, K, V, p = inputs(w, seed=46)
+    p = dict(p, fc2_b=np.abs(p["fc2_b"]) + 1.0)
+    (Kt, Vt), pt = upload(w, [K, V], p)
+    Vt[:, :, t, c] = 0.0
+    S0, z0 = luna.attn_state(Kt, Vt, pt)
+    Vt[0, :, t, c] = torch.tensor([math.inf, -math.inf])
+    S, z = luna.attn_state(Kt, Vt, pt)
+    phi = luna.featuremap(Kt, pt, torch.float32)[0, :, t]  # [H][M]
+    assert (phi > 0).float().mean() > 0.5
+    for h, x in enumerate((math.inf, -math.inf)):
+        assert (S[0, h, phi[h] > 0, c] == x).all()
+    cols = [i for i in range(d) if i != c]
+    # (the columns beside it may be summed in another order: twice n roundings of the terms)
+    phi_all = luna.featuremap(Kt, pt, torch.float32)
+    Vt[:, :, t, c] = 0.0
+    terms = torch.matmul(phi_all.transpose(-1, -2).contiguous(), Vt.float().abs())
+    assert ((S - S0)[..., cols].abs() <= 2 * n * 2.0 ** -24 * terms[..., cols]).all()
+    assert torch.equal(z, z0)
+
+
+@pytest.mark.parametrize("pdt,dt,D,n,causal", [("bf16", "f32", 64, 40, False), ("f32", "bf16", 1, 1, True),
+                                               ("bf16", "f32", 48, 1, False)])
+def test_attn_features_largest_values(pdt, dt, D, n, causal):
+    """fp32 operands above the largest bf16 value: sums that fp32 holds stay finite."""
+    import torch
+    say(f"largest fp32 values phi={pdt} {dt} D={D} n={n} causal={causal}")
+    big = 3.4e38
+    V = torch.full((1, 1, n, 32), 0.5, dtype=torch_dtype(dt), device="cuda")
+    if dt == "f32":  # (statistics of up to 3.4e38 from features of 1, read out by features of 2^-8)
+        fq = torch.full((1, 1, n, D), 2.0 ** -8, dtype=torch_dtype(pdt), device="cuda")
+        fk = torch.ones((1, 1, n, D), dtype=torch_dtype(pdt), device="cuda")
+        V[0, 0, 0, ::2], V[0, 0, 0, 1::2] = big, -big
+        ref = V.double().sum(2, keepdim=True) / n
+    else:  # one token whose kernel value is 3.4e38
+        fq = torch.full((1, 1, n, D), 1.8e19, dtype=torch.float32, device="cuda")
+        fk = torch.full((1, 1, n, D), 1.8888e19, dtype=torch.float32, device="cuda")
+        ref = V.double()
+    got = luna.attn_fwd_features(fq, fk, V, causal=causal, eps=0.0)
+    assert_close(to_np(got), ref.expand(got.shape).cpu().numpy(), dt, "out")
