@@ -22,6 +22,9 @@
  *    call, keeps no pointer after it returns and, apart from the static scratch of
  *    luna_attn_fwd_causal_noalloc, has no global mutable state, so calls on
  *    different streams may run concurrently if their workspaces differ.
+ *    Outputs must not overlap inputs or each other, except that `out` may be V's own
+ *    buffer and, in the backward pass, dQ, dK and dV may be those of Q, K and V (or dV
+ *    that of dO).
  *  - `stream` is a hipStream_t (NULL = the null stream).  Work is enqueued on it
  *    asynchronously; LUNA_OK means "enqueued", not "finished".
  *  - All arguments are validated on the host before anything is launched.  A

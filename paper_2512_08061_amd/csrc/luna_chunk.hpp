@@ -22,6 +22,7 @@ struct ChunkArgs {
   float* dx;           // row feature gradients [heads][n][D]
   int64_t heads, n, elems;
   int D, piece, pieces, causal;  // tokens per piece (a multiple of the tile), pieces per head
+  int first, step;               // tiles first, first + step, ... of every head (set by the launcher)
   float eps;
 };
 

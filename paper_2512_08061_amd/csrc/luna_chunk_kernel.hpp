@@ -150,8 +150,9 @@ __global__ __launch_bounds__(kCkThreads, KB <= 4 ? 4 : 2) void chunk_kernel(Chun
   const unsigned per = gridDim.x / 8, extra = gridDim.x % 8, die = blockIdx.x % 8;
   const unsigned id = die * per + min(die, extra) + blockIdx.x / 8;
   const int tiles = (int)((a.n + kChunkTile - 1) / kChunkTile);
-  const int64_t head = id / (unsigned)tiles;
-  const int tile = (int)(id - (unsigned)head * (unsigned)tiles);
+  const unsigned launched = (unsigned)((tiles - a.first + a.step - 1) / a.step);  // of every head
+  const int64_t head = id / launched;
+  const int tile = a.first + a.step * (int)(id - (unsigned)head * launched);
   const int64_t t0 = (int64_t)tile * kChunkTile;
   const int rows = (int)min((int64_t)kChunkTile, a.n - t0);
   const int D = a.D, kbs = (D + 31) / 32, tpp = a.piece / kChunkTile;
@@ -357,12 +358,14 @@ __global__ __launch_bounds__(kCkThreads, KB <= 4 ? 4 : 2) void chunk_kernel(Chun
   }
 
   if (PASS == kPassKey) {
+    if (!a.dx) __syncthreads();  // (dV in the place of dO: every wave has its columns)
     T* out = reinterpret_cast<T*>(a.out) + (head * a.n + t0) * DH;
 #pragma unroll
     for (int b = 0; b < R1; ++b) {
       const int t = 16 * (rb1 + b) + r;
-      if (t < rows) store4(out + (int64_t)t * DH + 16 * cb + 4 * g, num[b][0], num[b][1], num[b][2], num[b][3]);
+      if (a.out && t < rows) store4(out + (int64_t)t * DH + 16 * cb + 4 * g, num[b][0], num[b][1], num[b][2], num[b][3]);
     }
+    if (!a.dx) return;
   } else {
     if (grads)
 #pragma unroll
@@ -526,7 +529,8 @@ hipError_t chunk_launch(const ChunkArgs& a, hipStream_t s) {
                                                     hipFuncAttributeMaxDynamicSharedMemorySize,
                                                     (int)C::lds(true, true));
   if (set != hipSuccess) return set;
-  const int64_t blocks = a.heads * ((a.n + kChunkTile - 1) / kChunkTile);
+  const int64_t tiles = (a.n + kChunkTile - 1) / kChunkTile;
+  const int64_t blocks = a.heads * ((tiles - a.first + a.step - 1) / a.step);
   hipLaunchKernelGGL((chunk_kernel<T, DH, KB, PASS>), dim3((unsigned)blocks), dim3(kCkThreads),
                      C::lds(a.causal, PASS == kPassKey || a.u != nullptr), s, a);
   return hipGetLastError();
@@ -559,7 +563,29 @@ hipError_t chunk_launch_p(Dt dt, int d, const ChunkArgs& a, hipStream_t s) {
     if (a.w) q.w = a.w + rows * 2;
     if (a.dx) q.dx = a.dx + rows * a.D;
     q.heads = hn;
-    return dt == Dt::BF16 ? chunk_launch_t<__bf16, PASS>(d, q, s) : chunk_launch_t<float, PASS>(d, q, s);
+    // An output in the place of the columns (out = V, dV = dO): a tile meets the columns of its
+    // piece's tiles up to its own (query pass) or from its own on (key pass), so the tiles of a
+    // piece go one after the other, those that the others do not meet first.  dphi(K), for which
+    // the key pass reads the columns again, is formed before.
+    auto launch = [&]() {
+      return dt == Dt::BF16 ? chunk_launch_t<__bf16, PASS>(d, q, s) : chunk_launch_t<float, PASS>(d, q, s);
+    };
+    q.first = 0;
+    q.step = 1;
+    if (!a.causal || a.out == nullptr || (a.out != a.v && a.out != (const void*)a.y)) return launch();
+    hipError_t e = hipSuccess;
+    if (PASS == kPassKey) {
+      q.out = nullptr;
+      if ((e = launch()) != hipSuccess) return e;
+      q.out = advance(a.out, values);
+      q.dx = nullptr;
+    }
+    q.step = a.piece / kChunkTile;
+    for (int i = 0; i < q.step && e == hipSuccess; ++i) {
+      q.first = PASS == kPassQuery ? q.step - 1 - i : i;
+      if (q.first < tiles) e = launch();
+    }
+    return e;
   });
 }
 

@@ -399,19 +399,29 @@ hipError_t map_launch_L(const MapBwd& a, int sets, hipStream_t s) {
 
 template <typename T, int DH>
 hipError_t map_launch_d(int L, const MapBwd& a, int sets, hipStream_t s) {
-  hipError_t e = hipErrorInvalidValue;
-  switch (L) {
-    case 1: e = map_launch_L<T, DH, 1>(a, sets, s); break;
-    case 2: e = map_launch_L<T, DH, 2>(a, sets, s); break;
-    case 4: e = map_launch_L<T, DH, 4>(a, sets, s); break;
-    case 8: e = map_launch_L<T, DH, 8>(a, sets, s); break;
-    case 16: e = map_launch_L<T, DH, 16>(a, sets, s); break;
-    default: return e;
-  }
+  auto launch = [&](const MapBwd& q) {
+    switch (L) {
+      case 1: return map_launch_L<T, DH, 1>(q, sets, s);
+      case 2: return map_launch_L<T, DH, 2>(q, sets, s);
+      case 4: return map_launch_L<T, DH, 4>(q, sets, s);
+      case 8: return map_launch_L<T, DH, 8>(q, sets, s);
+      case 16: return map_launch_L<T, DH, 16>(q, sets, s);
+      default: return hipErrorInvalidValue;
+    }
+  };
+  // dx in the place of x: after map_dw_kernel, which reads x too
+  const bool late = a.duq && a.dxq && (a.dxq == a.xq || a.dxk == a.xk);
+  MapBwd q = a;
+  if (late) q.dxq = q.dxk = nullptr;
+  hipError_t e = launch(q);
   if (e != hipSuccess || a.duq == nullptr) return e;
   const dim3 grid((unsigned)a.dw_groups, (unsigned)((a.M + kDwProj - 1) / kDwProj), (unsigned)sets);
   hipLaunchKernelGGL((map_dw_kernel<T, DH>), grid, dim3(256), 0, s, a);
-  return hipGetLastError();
+  e = hipGetLastError();
+  if (e != hipSuccess || !late) return e;
+  q = a;
+  q.duq = q.duk = nullptr;
+  return launch(q);
 }
 
 template <typename T>

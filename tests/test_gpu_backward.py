@@ -191,3 +191,36 @@ def test_attn_bwd_infinite_gradient(d, M, L, causal):
     assert ((a - b).abs() <= 2.0 ** -7 * b.abs() + 1e-5 * b.abs().max()).all()
     rows = [r for r in range(n) if r != t]
     assert torch.equal(gQ[:, :, rows], cQ[:, :, rows])
+
+
+@pytest.mark.parametrize("place", ["inputs", "dV in dO"])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("dtype,d,M,L", [("bf16", 64, 8, 8), ("f32", 128, 32, 8)])
+def test_attn_bwd_in_place(dtype, d, M, L, causal, place):
+    """dQ, dK, dV in the buffers of Q, K, V (dV also in that of dO): the gradients of a call
+    with buffers of their own."""
+    import ctypes
+    import torch
+    w = small_workload(dtype, B=2, H=16, n=421, d=d, M=M, L=L, causal=causal)
+    say(f"backward in place {w.name} causal={causal} {place}")
+    Q, K, V, p = inputs(w, seed=57)
+    dO = np.random.default_rng(58).standard_normal(Q.shape).astype(np.float32)
+    (Qt, Kt, Vt, dOt), pt = upload(w, [Q, K, V, dO], p)
+    dQ, dK, dV, g = luna.attn_bwd(Qt, Kt, Vt, dOt, pt, causal=causal, eps=w.eps)
+    lib = luna.load_library()
+    dt, pc = luna._dt(Qt), pt.c()
+    nb = lib.luna_workspace_bytes(luna.OP_ATTN_CAUSAL_BWD if causal else luna.OP_ATTN_BWD, dt, w.B, w.H, w.n, d,
+                                  ctypes.byref(pc), 64)
+    ws = torch.empty(nb, dtype=torch.uint8, device="cuda")
+    h = {k: torch.empty_like(v) for k, v in g.items()}
+    gc = luna.PhiGradsC(*(h[k].data_ptr() for k in NAMES))
+    outs = (Qt, Kt, Vt) if place == "inputs" else (torch.empty_like(Qt), torch.empty_like(Kt), dOt)
+    st = lib.luna_attn_bwd(Qt.data_ptr(), Kt.data_ptr(), Vt.data_ptr(), dOt.data_ptr(), dt, w.B, w.H, w.n, d,
+                           ctypes.byref(pc), int(causal), w.eps, *(t.data_ptr() for t in outs), ctypes.byref(gc),
+                           ws.data_ptr(), nb, torch.cuda.current_stream().cuda_stream)
+    assert st == luna.LUNA_OK
+    torch.cuda.synchronize()
+    for got, ref in zip(outs, (dQ, dK, dV)):
+        assert torch.equal(got, ref)
+    for k in NAMES:  # (the channel moments are summed by atomics: fp64, then rounded to fp32 per workgroup)
+        assert (h[k] - g[k]).abs().max() <= 1e-6 * g[k].abs().max(), k

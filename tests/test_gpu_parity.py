@@ -567,3 +567,20 @@ def test_deterministic(causal):
     b = f(Qt, Kt, Vt, pt).clone()
     import torch
     assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("dtype,d,M,L,B,H,n,causal", [
+    ("f32", 128, 32, 8, 2, 16, 421, True), ("bf16", 64, 128, 1, 1, 40, 300, True), ("bf16", 128, 100, 1, 1, 3, 421, True),
+    ("bf16", 128, 32, 8, 1, 16, 421, True), ("bf16", 128, 32, 8, 1, 100, 421, True), ("bf16", 64, 16, 8, 1, 90, 421, True),
+    ("f32", 128, 32, 8, 1, 4, 421, False), ("bf16", 64, 16, 8, 1, 4, 421, False), ("bf16", 64, 16, 8, 16, 16, 421, False)])
+def test_attn_out_in_v(dtype, d, M, L, B, H, n, causal):
+    """The output in V's buffer: what a buffer of its own receives, on every path."""
+    import torch
+    w = small_workload(dtype, B=B, H=H, n=n, d=d, M=M, L=L, causal=causal)
+    say(f"out in V {w.name} B={B} H={H} causal={causal}")
+    Q, K, V, p = inputs(w, seed=91)
+    (Qt, Kt, Vt), pt = upload(w, [Q, K, V], p)
+    f = luna.attn_fwd_causal if causal else luna.attn_fwd
+    ref = f(Qt, Kt, Vt, pt, eps=w.eps)
+    f(Qt, Kt, Vt, pt, eps=w.eps, out=Vt)
+    assert torch.equal(Vt, ref)
