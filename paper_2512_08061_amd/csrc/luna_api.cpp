@@ -129,15 +129,7 @@ luna_status plan_f32_buffers(int64_t heads, int64_t n, int d, int D, bool causal
   if (queries && features) take(lay->phiq, rows * D * 4);
   if (features) take(lay->phik, rows * D * 4);
   if (lay->chunked) {
-    // The size asked for stays that of the GEMM form below (larger but for short sequences of
-    // many features), which callers' workspaces may have been sized by.
-    const size_t gemm_states = (size_t)heads * (size_t)((n + (causal ? 63 : 511)) / (causal ? 64 : 512));
-    size_t asked = align256(*off + rows * (d + 1) * 4);
-    if (queries) asked = align256(asked + rows * (d + 1) * 4);
-    asked = align256(asked + gemm_states * D * (d + 1) * 4);
-    if (causal && queries) asked = align256(asked + gemm_states * 64 * 64 * 4);
     take(lay->sx, states * (size_t)luna::feat_elems(d, D) * 4);
-    if (*off < asked) *off = asked;
     return LUNA_OK;
   }
   take(lay->vx, rows * (d + 1) * 4);

@@ -141,16 +141,15 @@ def test_workspace_sizes(lib):
 
 
 def test_generic_path_planning(lib):
-    """Shapes without a fused kernel take the fp32 GEMM path: its workspace holds the
-    features, [V | 1], [num | den - eps] and the per-chunk states (and P, causal), and
-    its chunk count is capped; M above 256 is invalid."""
+    """Shapes without a fused kernel run in fp32: their workspace holds the features of the
+    queries and keys and the statistics of pieces of 128 tokens (causal) or 512 tokens, and
+    the piece count is capped; M above 256 is invalid."""
     d, n, B, H = 128, 16384, 8, 16
     rows = B * H * n
     p200 = _params(M=200, L=1)
-    for op, chunk_bytes in [(luna.OP_ATTN_CAUSAL, 200 * 129 * 4 + 64 * 64 * 4), (luna.OP_ATTN, 200 * 129 * 4)]:
-        chunk = 64 if op == luna.OP_ATTN_CAUSAL else 512
+    for op, piece in [(luna.OP_ATTN_CAUSAL, 128), (luna.OP_ATTN, 512)]:
         nb = lib.luna_workspace_bytes(op, luna.LUNA_BF16, B, H, n, d, ctypes.byref(p200), 64)
-        floor = rows * (2 * 200 + 2 * 129) * 4 + B * H * (n // chunk) * chunk_bytes
+        floor = rows * 2 * 200 * 4 + B * H * (n // piece) * 200 * 129 * 4
         assert floor <= nb <= floor + (1 << 20), (op, nb, floor)
     # one channel per projection with 256 features at d = 128, causal: the features of
     # Q and K in bf16, then the scan kernel (its state pieces are a few MB)
@@ -234,18 +233,19 @@ def test_variant_features_and_rejects(lib):
 
 def test_attn_features_planning(lib):
     """Attention from given features: the causal scan kernel for bf16 features with
-    (d, D) = (128, 256) (state pieces only), otherwise the fp32 GEMM path (fp32 copies
-    of bf16 features, per-chunk states); argument checks on the host."""
+    (d, D) = (128, 256) (state pieces only), otherwise fp32 (copies of bf16 features, states
+    of 128-token pieces); argument checks on the host."""
     B, H, n = 8, 16, 16384
     wsb = lambda pdt, dt, d, D, causal, chunk=64: lib.luna_attn_features_workspace_bytes(  # noqa: E731
         pdt, dt, B, H, n, d, D, causal, chunk)
     given = wsb(luna.LUNA_BF16, luna.LUNA_BF16, 128, 256, 1)
     assert 0 < given < 64 << 20
     rows = B * H * n
-    gemm32 = wsb(luna.LUNA_F32, luna.LUNA_BF16, 128, 256, 1)
-    assert rows * 2 * 129 * 4 <= gemm32 < rows * 2 * 129 * 4 + B * H * 256 * (256 * 129 * 4 + 64 * 64 * 4) + (1 << 20)
-    gemm16 = wsb(luna.LUNA_BF16, luna.LUNA_F32, 128, 256, 1)
-    assert gemm16 >= gemm32 + rows * 256 * 8 - (1 << 20)  # plus the fp32 copies
+    states = B * H * (n // 128) * 256 * 129 * 4
+    fp32 = wsb(luna.LUNA_F32, luna.LUNA_BF16, 128, 256, 1)
+    assert states <= fp32 < states + (1 << 20)
+    widened = wsb(luna.LUNA_BF16, luna.LUNA_F32, 128, 256, 1)
+    assert 0 <= widened - fp32 - rows * 256 * 8 < 1 << 20  # plus the fp32 copies
     assert wsb(luna.LUNA_BF16, luna.LUNA_BF16, 128, 256, 1, chunk=32) == 0
     assert wsb(luna.LUNA_BF16, luna.LUNA_BF16, 128, 600, 0) == 0
     assert wsb(luna.LUNA_BF16, luna.LUNA_BF16, 300, 64, 0) == 0
