@@ -71,7 +71,7 @@ typedef enum luna_status {
   LUNA_OK = 0,
   LUNA_ERR_INVALID_ARG = 1, /* null pointer, non-positive size, inconsistent parameters */
   LUNA_ERR_UNSUPPORTED = 2, /* valid problem that the built kernels do not cover */
-  LUNA_ERR_WORKSPACE = 3,   /* ws_bytes smaller than luna_workspace_bytes() */
+  LUNA_ERR_WORKSPACE = 3,   /* ws_bytes smaller than the call can do with */
   LUNA_ERR_HIP = 4          /* a HIP runtime call or kernel launch failed */
 } luna_status;
 
@@ -123,8 +123,11 @@ typedef struct luna_phi_params {
 } luna_phi_params;
 
 /*
- * Bytes of device workspace an operation needs (0 if the arguments are invalid or
- * unsupported).  op is LUNA_OP_*; dtype is the call's dtype (for LUNA_OP_FEATUREMAP
+ * Bytes of device workspace an operation runs fastest with (0 if the arguments are
+ * invalid or unsupported); it does not grow steadily with n, so ask for every shape.  A
+ * call with less that still holds its statistics in as few pieces as it can do with runs
+ * too, slower and to the rounding of fp32 sums with the same results; one with less than
+ * that returns LUNA_ERR_WORKSPACE.  op is LUNA_OP_*; dtype is the call's dtype (for LUNA_OP_FEATUREMAP
  * the input dtype); chunk is used by LUNA_OP_ATTN_CAUSAL only.  The workspace must
  * be 256-byte aligned.  The workspace holds
  * the exact piecewise-linear tables of the channel MLPs, built on the device at the
@@ -169,12 +172,12 @@ luna_status luna_attn_fwd_causal(const void* Q, const void* K, const void* V, lu
  * luna_attn_fwd_causal without a workspace argument, for callers that cannot
  * allocate device memory: code under HIP graph capture, tight serving loops and
  * harnesses that forbid allocation.  It computes exactly what luna_attn_fwd_causal
- * computes (the same kernels) and allocates nothing: its workspace is a static
+ * computes with a workspace of the same size and allocates nothing: its workspace is a static
  * array of luna_noalloc_scratch_bytes() bytes (64 MiB) in the library's code object,
  * one per device, held from the library's load until the process ends, on the
  * calling thread's current device (which must be the stream's device).  Problems
- * whose workspace (luna_workspace_bytes with LUNA_OP_ATTN_CAUSAL) exceeds it return
- * LUNA_ERR_WORKSPACE before anything is enqueued.  Every call on a device shares that
+ * that need more than it holds, in as few pieces as luna_attn_fwd_causal can do with,
+ * return LUNA_ERR_WORKSPACE before anything is enqueued.  Every call on a device shares that
  * device's array and needs nothing from an earlier call (every buffer in it is
  * written before it is read), but two calls whose kernels overlap in time on one
  * device -- on different streams, or from different threads -- race on it; order

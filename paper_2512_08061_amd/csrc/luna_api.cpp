@@ -7,6 +7,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <mutex>
@@ -88,6 +89,7 @@ struct Layout {
   size_t state = 0;          // causal with 2 parts: state pieces of the first `split` tokens
   int pieces = 0, piece_chunks = 0;
   int staged = 0, sa = 0, sb = 0;  // staged causal scan: chunks of the first scanned part and of the state-only part
+  bool few = false;  // the plan of a small workspace: statistics in as few pieces as it can
   int feat = 0;     // non-causal attention from given features in their own type
   int generic = 0;  // forward in fp32 (shapes without a fused kernel),
   int chunked = 0;  // by the chunk kernels; else by GEMMs and scans
@@ -97,9 +99,9 @@ struct Layout {
 // Tokens per piece of the statistics of a whole sequence: 512, or the fewer (64 at least) that
 // put a piece on every compute unit.  A piece is a serial chain of 32-token steps, 16 of them
 // 40 us at d = 128 and 256 features.
-int state_piece(int64_t heads, int64_t n) {
+int state_piece(int64_t heads, int64_t n, bool few) {
   int piece = 512;
-  while (piece > 64 && heads * ((n + piece - 1) / piece) < 256) piece /= 2;
+  while (!few && piece > 64 && heads * ((n + piece - 1) / piece) < 256) piece /= 2;
   return piece;
 }
 
@@ -117,7 +119,7 @@ luna_status plan_f32_buffers(int64_t heads, int64_t n, int d, int D, bool causal
   if (nch > 65535) return fail(LUNA_ERR_UNSUPPORTED, causal ? "n must be <= 65535 * 64" : "n must be <= 65535 * 512");
   lay->chunked = luna::chunk_supported(d, D);
   if (lay->chunked) {
-    lay->chunk = causal ? luna::kChunkPiece : state_piece(heads, n);
+    lay->chunk = causal ? luna::kChunkPiece : state_piece(heads, n, lay->few);
     nch = (n + lay->chunk - 1) / lay->chunk;
   }
   lay->nch = (int)nch;
@@ -142,22 +144,31 @@ luna_status plan_f32_forward(const Problem& pb, bool causal, bool queries, Layou
   return plan_f32_buffers(pb.B * pb.H, pb.n, (int)pb.d, pb.p->M * pb.p->L, causal, queries, true, lay, off);
 }
 
-// The causal kernel's split.  Too few heads to fill the device: up to 85 heads in three or
-// more equal parts, with 97 to 128 heads the staged form below (two scan launches); otherwise
-// cut every head in two at a
-// chunk boundary x near n/2, where a state launch first sums the state of [0, x) in
-// pieces (one workgroup per head and piece, enough pieces to fill the device) and part
-// 1 of the scan launch starts from the sum of the pieces.
+// The causal kernel's split.  Too few heads to fill the device: up to 85 heads in equal parts,
+// with 97 to 128 heads the staged form below (two scan launches); otherwise cut every head in
+// two at a chunk boundary x near n/2, where a state launch first sums the state of [0, x) in
+// pieces (one workgroup per head and piece, enough pieces to fill the device) and part 1 of
+// the scan launch starts from the sum of the pieces.
 void plan_causal_parts(int64_t heads, int64_t n, size_t state_floats, Layout* lay, size_t* off, bool staged_ok) {
   const int64_t nch = (n + 63) / 64;
   lay->state_floats = state_floats;
+  // the cut in two: chunks before it, chunks of a piece, pieces
+  const int64_t cx = heads < 256 && n >= 256 ? n / 64 / 2 : 0;
+  int64_t pc = 0, pieces = 0;
+  if (cx > 0) {
+    pieces = std::min((256 + heads - 1) / heads, cx);
+    pc = (cx + pieces - 1) / pieces;
+    pieces = (cx + pc - 1) / pc;  // every piece non-empty
+  }
   if (heads <= 85 && nch >= 3) {
     // Equal parts: a state launch over all but the last, their running sums, one scan
     // launch.  One scanned part in place of a two-part cut's n / 2 tokens: 16 heads of 1999
     // tokens, d = 128, 32 projections: 48 us instead of 215.
-    int64_t parts = 256 / heads;
-    if (parts > nch) parts = nch;
-    const int64_t pc = (nch + parts - 1) / parts;
+    // With a small workspace no more states than the cut in two would hold.
+    int64_t parts = std::min(256 / heads, nch);
+    if (lay->few) parts = std::min(parts, pieces + 1);
+    if (parts == 1) return;
+    pc = (nch + parts - 1) / parts;
     lay->part_chunks = lay->piece_chunks = (int)pc;
     lay->parts = (int)((nch + pc - 1) / pc);
     lay->pieces = lay->parts - 1;
@@ -187,19 +198,13 @@ void plan_causal_parts(int64_t heads, int64_t n, size_t state_floats, Layout* la
     *off = align256(*off + (size_t)heads * 2 * state_floats * sizeof(float));
     return;
   }
-  if (heads < 256 && n >= 256) {
-    const int64_t cx = n / 64 / 2;  // chunks before the split
-    if (cx >= 1) {
-      lay->parts = 2;
-      lay->split = (int)(cx * 64);
-      int64_t pieces = (256 + heads - 1) / heads;
-      if (pieces > cx) pieces = cx;
-      const int64_t pc = (cx + pieces - 1) / pieces;
-      lay->piece_chunks = (int)pc;
-      lay->pieces = (int)((cx + pc - 1) / pc);  // every piece non-empty
-      lay->state = *off;
-      *off = align256(*off + (size_t)heads * lay->pieces * state_floats * sizeof(float));
-    }
+  if (cx > 0) {
+    lay->parts = 2;
+    lay->split = (int)(cx * 64);
+    lay->piece_chunks = (int)pc;
+    lay->pieces = (int)pieces;
+    lay->state = *off;
+    *off = align256(*off + (size_t)heads * lay->pieces * state_floats * sizeof(float));
   }
 }
 
@@ -209,7 +214,7 @@ void plan_causal_parts(int64_t heads, int64_t n, size_t state_floats, Layout* la
 // own serial chain.
 void plan_splits(const Problem& pb, int64_t heads, Layout* lay) {
   const int64_t want = (512 + heads - 1) / heads;
-  const int64_t least = heads * ((pb.n + 255) / 256) <= 64 ? 128 : 256;
+  const int64_t least = !lay->few && heads * ((pb.n + 255) / 256) <= 64 ? 128 : 256;
   const int64_t maxs = (pb.n + least - 1) / least;
   int64_t splits = want < maxs ? want : maxs;
   if (splits < 1) splits = 1;
@@ -245,7 +250,18 @@ void plan_phi_backward(const Problem& pb, Layout* lay, size_t* off) {
   take(lay->pre, (size_t)P * L * (luna::bwd_nseg_cap(L) + 1) * 2 * 8);
 }
 
-luna_status plan(const Problem& pb, Layout* lay) {
+// The plan that `f` makes: with a workspace of `room` bytes that does not hold it, the one with
+// as few pieces as the call can do with (the same sums over tokens in fewer parts, slower).
+template <typename F>
+luna_status plan_within(size_t room, Layout* lay, F f) {
+  const luna_status st = f(lay);
+  if (st != LUNA_OK || lay->total <= room) return st;
+  *lay = Layout();
+  lay->few = true;
+  return f(lay);
+}
+
+luna_status plan_pieces(const Problem& pb, Layout* lay) {
   luna_status st = check_common(pb);
   if (st != LUNA_OK) return st;
   const luna::Dt dt = pb.dt == LUNA_BF16 ? luna::Dt::BF16 : luna::Dt::F32;
@@ -381,6 +397,10 @@ luna_status plan(const Problem& pb, Layout* lay) {
   }
   lay->total = off;
   return LUNA_OK;
+}
+
+luna_status plan(const Problem& pb, Layout* lay, size_t room = SIZE_MAX) {
+  return plan_within(room, lay, [&](Layout* l) { return plan_pieces(pb, l); });
 }
 
 luna_status check_ws(const Layout& lay, void* ws, size_t ws_bytes) {
@@ -677,8 +697,8 @@ size_t variant_ws_bytes(const luna_phi_variant* v, int64_t rows) {
 // Buffers of luna_attn_fwd_features: the causal scan kernel on the bf16 features when
 // it is built for (d, D), non-causal the kernels on features in their own type, else the
 // fp32 path (fp32 copies of bf16 features).
-luna_status plan_features(luna_dtype phi_dtype, luna_dtype dtype, int64_t B, int64_t H, int64_t n, int64_t d,
-                          int64_t D, int32_t causal, int32_t chunk, Layout* lay) {
+luna_status plan_features_pieces(luna_dtype phi_dtype, luna_dtype dtype, int64_t B, int64_t H, int64_t n, int64_t d,
+                                 int64_t D, int32_t causal, int32_t chunk, Layout* lay) {
   if ((phi_dtype != LUNA_F32 && phi_dtype != LUNA_BF16) || (dtype != LUNA_F32 && dtype != LUNA_BF16))
     return fail(LUNA_ERR_INVALID_ARG, "dtypes must be LUNA_F32 or LUNA_BF16");
   if (B < 1 || H < 1 || n < 1) return fail(LUNA_ERR_INVALID_ARG, "B, H and n must be >= 1");
@@ -696,7 +716,7 @@ luna_status plan_features(luna_dtype phi_dtype, luna_dtype dtype, int64_t B, int
     // the features in their own type: statistics of pieces only
     lay->feat = 1;
     if ((n + 511) / 512 > 65535) return fail(LUNA_ERR_UNSUPPORTED, "n must be <= 65535 * 512");
-    lay->chunk = state_piece(heads, n);
+    lay->chunk = state_piece(heads, n, lay->few);
     const int64_t pieces = (n + lay->chunk - 1) / lay->chunk;
     lay->nch = (int)pieces;
     lay->sx = off;
@@ -708,6 +728,13 @@ luna_status plan_features(luna_dtype phi_dtype, luna_dtype dtype, int64_t B, int
   }
   lay->total = off;
   return LUNA_OK;
+}
+
+luna_status plan_features(luna_dtype phi_dtype, luna_dtype dtype, int64_t B, int64_t H, int64_t n, int64_t d,
+                          int64_t D, int32_t causal, int32_t chunk, Layout* lay, size_t room = SIZE_MAX) {
+  return plan_within(room, lay, [&](Layout* l) {
+    return plan_features_pieces(phi_dtype, dtype, B, H, n, d, D, causal, chunk, l);
+  });
 }
 
 // The causal kernel over its parts: with more than one, the state launch first (and the
@@ -899,7 +926,7 @@ luna_status luna_attn_fwd_features(const void* phiQ, const void* phiK, luna_dtyp
                                    void* stream) {
   g_last_error.clear();
   Layout lay;
-  luna_status st = plan_features(phi_dtype, dtype, B, H, n, d, D, causal, chunk, &lay);
+  luna_status st = plan_features(phi_dtype, dtype, B, H, n, d, D, causal, chunk, &lay, ws_bytes);
   if (st != LUNA_OK) return st;
   if (!phiQ || !phiK || !V || !out) return fail(LUNA_ERR_INVALID_ARG, "phiQ, phiK, V or out is NULL");
   if (!finite_nonneg(eps)) return fail(LUNA_ERR_INVALID_ARG, "eps must be finite and >= 0");
@@ -961,7 +988,7 @@ luna_status luna_featuremap(const void* X, luna_dtype x_dtype, int64_t B, int64_
   g_last_error.clear();
   Problem pb{LUNA_OP_FEATUREMAP, x_dtype, B, H, n, d, p, 0};
   Layout lay;
-  luna_status st = plan(pb, &lay);
+  luna_status st = plan(pb, &lay, ws_bytes);
   if (st != LUNA_OK) return st;
   if (out_dtype != LUNA_F32 && out_dtype != LUNA_BF16) return fail(LUNA_ERR_INVALID_ARG, "out_dtype must be LUNA_F32 or LUNA_BF16");
   if (!X || !phi_out) return fail(LUNA_ERR_INVALID_ARG, "X or phi_out is NULL");
@@ -987,7 +1014,7 @@ luna_status luna_attn_fwd(const void* Q, const void* K, const void* V, luna_dtyp
   g_last_error.clear();
   Problem pb{LUNA_OP_ATTN, dtype, B, H, n, d, p, 0};
   Layout lay;
-  luna_status st = plan(pb, &lay);
+  luna_status st = plan(pb, &lay, ws_bytes);
   if (st != LUNA_OK) return st;
   if (!Q || !K || !V || !out) return fail(LUNA_ERR_INVALID_ARG, "Q, K, V or out is NULL");
   if (!finite_nonneg(eps)) return fail(LUNA_ERR_INVALID_ARG, "eps must be finite and >= 0");
@@ -1023,7 +1050,7 @@ luna_status luna_attn_fwd_causal(const void* Q, const void* K, const void* V, lu
   g_last_error.clear();
   Problem pb{LUNA_OP_ATTN_CAUSAL, dtype, B, H, n, d, p, chunk};
   Layout lay;
-  luna_status st = plan(pb, &lay);
+  luna_status st = plan(pb, &lay, ws_bytes);
   if (st != LUNA_OK) return st;
   if (!Q || !K || !V || !out) return fail(LUNA_ERR_INVALID_ARG, "Q, K, V or out is NULL");
   if (!finite_nonneg(eps)) return fail(LUNA_ERR_INVALID_ARG, "eps must be finite and >= 0");
@@ -1093,7 +1120,7 @@ luna_status luna_attn_fwd_causal_noalloc(const void* Q, const void* K, const voi
   g_last_error.clear();
   Problem pb{LUNA_OP_ATTN_CAUSAL, dtype, B, H, n, d, p, chunk};
   Layout lay;
-  luna_status st = plan(pb, &lay);
+  luna_status st = plan(pb, &lay, kScratchBytes);
   if (st != LUNA_OK) return st;
   if (lay.total > kScratchBytes) {
     char buf[160];
@@ -1114,7 +1141,7 @@ luna_status luna_attn_state(const void* K, const void* V, luna_dtype dtype, int6
   g_last_error.clear();
   Problem pb{LUNA_OP_STATE, dtype, B, H, n, d, p, 0};
   Layout lay;
-  luna_status st = plan(pb, &lay);
+  luna_status st = plan(pb, &lay, ws_bytes);
   if (st != LUNA_OK) return st;
   if (!K || !V || !S || !z) return fail(LUNA_ERR_INVALID_ARG, "K, V, S or z is NULL");
   if (accumulate != 0 && accumulate != 1) return fail(LUNA_ERR_INVALID_ARG, "accumulate must be 0 or 1");
@@ -1178,7 +1205,7 @@ luna_status luna_attn_causal_step(const void* Q, const void* K, const void* V, l
   g_last_error.clear();
   Problem pb{LUNA_OP_CAUSAL_STEP, dtype, B, H, m, d, p, 0};
   Layout lay;
-  luna_status st = plan(pb, &lay);
+  luna_status st = plan(pb, &lay, ws_bytes);
   if (st != LUNA_OK) return st;
   if (!Q || !K || !V || !S || !z || !out) return fail(LUNA_ERR_INVALID_ARG, "Q, K, V, S, z or out is NULL");
   if (((uintptr_t)S & 15) != 0) return fail(LUNA_ERR_INVALID_ARG, "S must be 16-byte aligned");
@@ -1237,7 +1264,7 @@ luna_status luna_attn_bwd(const void* Q, const void* K, const void* V, const voi
   if (causal != 0 && causal != 1) return fail(LUNA_ERR_INVALID_ARG, "causal must be 0 or 1");
   Problem pb{causal ? LUNA_OP_ATTN_CAUSAL_BWD : LUNA_OP_ATTN_BWD, dtype, B, H, n, d, p, 64};
   Layout lay;
-  luna_status st = plan(pb, &lay);
+  luna_status st = plan(pb, &lay, ws_bytes);
   if (st != LUNA_OK) return st;
   if (!Q || !K || !V || !dO || !dQ || !dK || !dV) return fail(LUNA_ERR_INVALID_ARG, "an input or output is NULL");
   if (grads && (!grads->W || !grads->b || !grads->fc1_w || !grads->fc1_b || !grads->fc2_w || !grads->fc2_b))
@@ -1287,7 +1314,7 @@ luna_status luna_distill(const void* Q, const void* K, luna_dtype dtype, int64_t
   if (causal != 0 && causal != 1) return fail(LUNA_ERR_INVALID_ARG, "causal must be 0 or 1");
   Problem pb{grads ? kOpDistillGrads : kOpDistill, dtype, B, H, n, d, p, 64};
   Layout lay;
-  luna_status st = plan(pb, &lay);
+  luna_status st = plan(pb, &lay, ws_bytes);
   if (st != LUNA_OK) return st;
   if (!Q || !K || !row_loss) return fail(LUNA_ERR_INVALID_ARG, "Q, K or row_loss is NULL");
   if (grads && (!grads->W || !grads->b || !grads->fc1_w || !grads->fc1_b || !grads->fc2_w || !grads->fc2_b))

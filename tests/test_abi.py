@@ -284,3 +284,66 @@ def test_distill_planning_and_rejects(lib):
     assert st(n=0) == luna.LUNA_ERR_INVALID_ARG
     assert st(p=_params(M=12, L=8)) == luna.LUNA_ERR_UNSUPPORTED
     assert st(ws=256) == luna.LUNA_ERR_WORKSPACE
+
+
+# (op, dtype, heads, n, d, M, L): bytes that the call has to do with, fewer than it asks for
+SMALL_WORKSPACES = [
+    (luna.OP_ATTN_CAUSAL, luna.LUNA_BF16, 64, 192, 128, 32, 8, 104960),
+    (luna.OP_ATTN_CAUSAL, luna.LUNA_BF16, 16, 1024, 128, 32, 8, 17013248),
+    (luna.OP_ATTN_CAUSAL, luna.LUNA_BF16, 8, 1999, 128, 256, 1, 32332288),
+    (luna.OP_ATTN_CAUSAL, luna.LUNA_F32, 3, 321, 64, 16, 8, 304640),
+    (luna.OP_ATTN, luna.LUNA_F32, 1, 256, 32, 8, 8, 146432),
+    (luna.OP_ATTN, luna.LUNA_F32, 12, 1999, 128, 32, 8, 80328704),
+    (luna.OP_ATTN, luna.LUNA_BF16, 1, 600, 128, 256, 1, 2217472),
+    (luna.OP_STATE, luna.LUNA_BF16, 4, 1000, 64, 16, 8, 637440),
+    (luna.OP_STATE, luna.LUNA_F32, 1, 16384, 128, 32, 8, 29563392),
+    (luna.OP_ATTN_BWD, luna.LUNA_F32, 12, 1999, 128, 32, 8, 190023680),
+]
+
+
+@pytest.mark.parametrize("op,dt,heads,n,d,M,L,few", SMALL_WORKSPACES)
+def test_small_workspaces(lib, op, dt, heads, n, d, M, L, few):
+    """A workspace that holds the statistics in few pieces (the cut of a causal head in two,
+    512 tokens, token ranges of 256) is accepted although the call asks for more; one that
+    holds no table is refused.  (The size is checked before the pointer, which is
+    misaligned, so that nothing is enqueued.)"""
+    p = _params(M=M, L=L)
+    assert lib.luna_workspace_bytes(op, dt, 1, heads, n, d, ctypes.byref(p), 64) > few
+    g = luna.PhiGradsC(*[FAKE] * 6)
+
+    def call(nb):
+        head = (FAKE, FAKE, FAKE)
+        shape = (dt, 1, heads, n, d, ctypes.byref(p))
+        tail = (FAKE + 8, nb, None)
+        if op == luna.OP_ATTN:
+            return lib.luna_attn_fwd(*head, *shape, 1e-6, FAKE, *tail)
+        if op == luna.OP_ATTN_CAUSAL:
+            return lib.luna_attn_fwd_causal(*head, *shape, 64, 1e-6, FAKE, *tail)
+        if op == luna.OP_STATE:
+            return lib.luna_attn_state(*head[:2], *shape, 0, FAKE, FAKE, *tail)
+        return lib.luna_attn_bwd(*head, FAKE, *shape, 0, 1e-6, FAKE, FAKE, FAKE, ctypes.byref(g), *tail)
+
+    assert call(few) == luna.LUNA_ERR_INVALID_ARG and b"aligned" in lib.luna_last_error()
+    assert call(1 << 16) == luna.LUNA_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("heads,n", [(8, 4992), (3, 13376), (17, 2432), (42, 1024)])
+def test_noalloc_scratch_holds_fewer_pieces(lib, heads, n):
+    """One channel per projection with 256 features at d = 128 holds its features in the
+    workspace too; the static scratch is enough for these shapes with the states of a cut in
+    two, though not for those of equal parts."""
+    p = _params(M=256, L=1)
+    cap = lib.luna_noalloc_scratch_bytes()
+    assert lib.luna_workspace_bytes(luna.OP_ATTN_CAUSAL, luna.LUNA_BF16, 1, heads, n, 128, ctypes.byref(p), 64) > cap
+    assert lib.luna_attn_fwd_causal(FAKE, FAKE, FAKE, luna.LUNA_BF16, 1, heads, n, 128, ctypes.byref(p), 64, 1e-6, FAKE,
+                                    FAKE + 8, cap, None) == luna.LUNA_ERR_INVALID_ARG
+    assert b"aligned" in lib.luna_last_error()
+
+
+def test_features_without_workspace(lib):
+    """Short causal calls on the scan kernel do without any workspace."""
+    st = lib.luna_attn_fwd_features(FAKE, FAKE, luna.LUNA_BF16, FAKE, luna.LUNA_BF16, 1, 1, 255, 64, 128, 1, 64, -1.0,
+                                    FAKE, None, 0, None)
+    assert st == luna.LUNA_ERR_INVALID_ARG and b"eps" in lib.luna_last_error()
+    assert lib.luna_attn_fwd_features(FAKE, FAKE, luna.LUNA_BF16, FAKE, luna.LUNA_BF16, 1, 1, 256, 64, 128, 1, 64, 1e-6,
+                                      FAKE, None, 0, None) == luna.LUNA_ERR_WORKSPACE

@@ -584,3 +584,43 @@ def test_attn_out_in_v(dtype, d, M, L, B, H, n, causal):
     ref = f(Qt, Kt, Vt, pt, eps=w.eps)
     f(Qt, Kt, Vt, pt, eps=w.eps, out=Vt)
     assert torch.equal(Vt, ref)
+
+
+@pytest.mark.parametrize("op,dtype,d,M,L,H,n,few", [
+    ("causal", "bf16", 128, 32, 8, 64, 192, 104960), ("causal", "bf16", 128, 32, 8, 16, 1024, 17013248),
+    ("causal", "bf16", 128, 256, 1, 8, 1999, 32332288), ("causal", "f32", 64, 16, 8, 3, 321, 304640),
+    ("forward", "f32", 32, 8, 8, 1, 256, 146432), ("forward", "f32", 128, 32, 8, 12, 1999, 80328704),
+    ("state", "bf16", 64, 16, 8, 4, 1000, 637440), ("state", "f32", 128, 32, 8, 1, 2000, 4000000)])
+def test_small_workspaces(op, dtype, d, M, L, H, n, few):
+    """A call on a workspace that holds its statistics in few pieces only (one or two parts of
+    a causal head, pieces of 512 tokens, token ranges of 256) against the oracle."""
+    import ctypes
+    import torch
+    w = small_workload(dtype, B=1, H=H, n=n, d=d, M=M, L=L, causal=op == "causal")
+    say(f"small workspace {op} {w.name} H={H}: {few} bytes")
+    Q, K, V, p = inputs(w, seed=95)
+    (Qt, Kt, Vt), pt = upload(w, [Q, K, V], p)
+    lib, dt, pc = luna.load_library(), luna._dt(Qt), pt.c()
+    code = {"causal": luna.OP_ATTN_CAUSAL, "forward": luna.OP_ATTN, "state": luna.OP_STATE}[op]
+    shape = (dt, 1, H, n, d, ctypes.byref(pc))
+    assert lib.luna_workspace_bytes(code, *shape, 64) > few
+    ws = torch.empty(few, dtype=torch.uint8, device="cuda")
+    tail = (ws.data_ptr(), few, torch.cuda.current_stream().cuda_stream)
+    out = torch.empty_like(Qt)
+    q, k, v, o = (t.data_ptr() for t in (Qt, Kt, Vt, out))
+    if op == "state":
+        S = torch.empty((1, H, M * L, d), device="cuda")
+        z = torch.empty((1, H, M * L), device="cuda")
+        assert lib.luna_attn_state(k, v, *shape, 0, S.data_ptr(), z.data_ptr(), *tail) == luna.LUNA_OK
+        rS, rz = oracle.sufficient_statistics(oracle.featuremap(K, p), V)
+        assert_close(to_np(S), rS, dtype, "S")
+        assert_close(to_np(z)[..., None], rz[..., None], dtype, "z")
+        return
+    if op == "causal":
+        st = lib.luna_attn_fwd_causal(q, k, v, *shape, 64, w.eps, o, *tail)
+    else:
+        st = lib.luna_attn_fwd(q, k, v, *shape, w.eps, o, *tail)
+    assert st == luna.LUNA_OK
+    hs = sorted({0, H // 2, H - 1})
+    ref = (oracle.attn_causal if op == "causal" else oracle.attn_noncausal)(Q[:, hs], K[:, hs], V[:, hs], p, eps=w.eps)
+    assert_close_rows(to_np(out)[:, hs], ref, dtype, "out")

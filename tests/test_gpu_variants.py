@@ -280,3 +280,19 @@ def test_attn_features_largest_values(pdt, dt, D, n, causal):
         ref = V.double()
     got = luna.attn_fwd_features(fq, fk, V, causal=causal, eps=0.0)
     assert_close(to_np(got), ref.expand(got.shape).cpu().numpy(), dt, "out")
+
+
+def test_attn_features_without_workspace():
+    """A short causal call on the scan kernel with no workspace at all: one part a head."""
+    import torch
+    rng = np.random.default_rng(48)
+    n, d, D = 255, 64, 128
+    say(f"features without workspace n={n}")
+    (fq, rq), (fk, rk) = (_upload_rounded(_positive_features(rng, (2, 3, n, D)), "bf16") for _ in range(2))
+    V, rv = _upload_rounded(rng.standard_normal((2, 3, n, d)), "bf16")
+    out = torch.empty_like(V)
+    st = luna.load_library().luna_attn_fwd_features(fq.data_ptr(), fk.data_ptr(), luna.LUNA_BF16, V.data_ptr(),
+                                                    luna.LUNA_BF16, 2, 3, n, d, D, 1, 64, 1e-6, out.data_ptr(), None, 0,
+                                                    torch.cuda.current_stream().cuda_stream)
+    assert st == luna.LUNA_OK
+    assert_close_rows(to_np(out), VAR.attn_from_features(rq, rk, rv, causal=True), "bf16", "out")

@@ -61,3 +61,26 @@ def test_noalloc_refuses_problems_beyond_the_scratch():
     assert e.value.status == luna.LUNA_ERR_WORKSPACE
     torch.cuda.synchronize()
     assert not out.any()
+
+
+def test_noalloc_with_fewer_pieces():
+    """A shape whose features and equal parts' states exceed the scratch runs with the states
+    of a cut in two, bitwise as with a workspace of the scratch's size."""
+    import torch
+    cap = luna.noalloc_scratch_bytes()
+    w = small_workload("bf16", B=1, H=8, n=4992, d=128, M=256, L=1, causal=True)
+    say(f"noalloc with fewer pieces: {w.name}")
+    Q, K, V, p = inputs(w, seed=53)
+    (Qt, Kt, Vt), pt = upload(w, [Q, K, V], p)
+    lib, pc = luna.load_library(), pt.c()
+    assert lib.luna_workspace_bytes(luna.OP_ATTN_CAUSAL, luna.LUNA_BF16, 1, 8, 4992, 128, pc, 64) > cap
+    out = torch.full_like(Qt, float("nan"))
+    luna.attn_fwd_causal_noalloc(Qt, Kt, Vt, pt, chunk=64, eps=w.eps, out=out)
+    ws, ref = torch.empty(cap, dtype=torch.uint8, device="cuda"), torch.empty_like(Qt)
+    assert lib.luna_attn_fwd_causal(Qt.data_ptr(), Kt.data_ptr(), Vt.data_ptr(), luna.LUNA_BF16, 1, 8, 4992, 128, pc, 64,
+                                    w.eps, ref.data_ptr(), ws.data_ptr(), cap,
+                                    torch.cuda.current_stream().cuda_stream) == luna.LUNA_OK
+    assert torch.equal(out, ref)
+    full = luna.attn_fwd_causal(Qt, Kt, Vt, pt, chunk=64, eps=w.eps)
+    a, b = out.float(), full.float()  # (states summed in other parts, then rounded to bf16 operands)
+    assert ((a - b).abs().amax(-1) <= 2e-2 * b.abs().amax(-1)).all()
