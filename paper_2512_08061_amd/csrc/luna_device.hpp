@@ -50,6 +50,14 @@ __device__ __forceinline__ int wave_id() {
   return __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
 }
 
+// Between LDS accesses of one wave's lanes to each other's elements: none moves across it.  (The
+// LDS executes a wave's instructions in order; the fence keeps the compiler from moving them,
+// which a wave barrier alone, no memory access to it, does not.)
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // ---------------------------------------------------------------------------
 // piecewise-linear tables (layout shared with the host and luna_prepare.hip)
 // ---------------------------------------------------------------------------

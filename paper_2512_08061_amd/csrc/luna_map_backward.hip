@@ -336,7 +336,7 @@ __global__ __launch_bounds__(256) void map_dw_kernel(MapBwd a) {
       const int c = lane + i * kWave, k = c / (DH / V), q = c % (DH / V);
       *reinterpret_cast<uint4*>(xs + k * LD + q * V) = xv[i];
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_fence();
     Operand<float, T> w[2];
 #pragma unroll
     for (int x = 0; x < 2; ++x) {
@@ -353,7 +353,7 @@ __global__ __launch_bounds__(256) void map_dw_kernel(MapBwd a) {
       for (int x = 0; x < 2; ++x)
         if (pb + 16 * x < M) mma(acc[x][cb], w[x], xf);  // (uniform)
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_fence();
   }
   // db: the four lane groups hold different rows of projection r
 #pragma unroll

@@ -1,0 +1,21 @@
+"""Rules that the kernel sources keep, checked without a GPU."""
+import os
+import re
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2512_08061_amd", "csrc")
+
+
+def sources():
+    return {f: open(os.path.join(CSRC, f)).read() for f in sorted(os.listdir(CSRC))}
+
+
+def test_wave_barriers_are_fences():
+    """Lanes that exchange data through LDS without a workgroup barrier do so over a fence: a
+    bare wave barrier orders no memory access."""
+    for name, text in sources().items():
+        helper = re.search(r"void wave_lds_fence\(\) \{.*?\n\}", text, re.S)
+        rest = text.replace(helper.group(0), "") if helper else text
+        assert "__builtin_amdgcn_wave_barrier" not in rest, name
+        if helper:
+            assert "__builtin_amdgcn_fence(__ATOMIC_ACQ_REL" in helper.group(0)
+    assert "wave_lds_fence()" in sources()["luna_map_backward.hip"]
