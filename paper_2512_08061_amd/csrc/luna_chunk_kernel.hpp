@@ -39,12 +39,7 @@ constexpr int kPassQuery = 0, kPassKey = 1;
 // Everything is read through range-checked buffers that end with the operand's last row, so
 // that rows past it read as 0: a test per load would put a branch around each (measured: the
 // kernel takes twice the time).
-using Buf = __amdgpu_buffer_rsrc_t;
-__device__ __forceinline__ Buf buffer(const void* p, int bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, __builtin_amdgcn_readfirstlane(bytes),
-                                           kBufferFlags);
-}
-constexpr int kPastEnd = 0x7ffffff0;  // an offset no buffer reaches
+
 // 8 floats of row t of a [.][len] array at k0, 0 past the row's end (vec: len is a multiple of 8)
 __device__ __forceinline__ void row8(float (&o)[8], Buf b, int t, int k0, int len, bool vec) {
   const int off = (t * len + k0) * 4;

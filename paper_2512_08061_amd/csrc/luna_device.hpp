@@ -748,6 +748,13 @@ __device__ __forceinline__ f32x4 zero4() { return f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 // dropped, with no per-lane tests; accesses are always issued, so the waits for them
 // count the same loads on every path.
 constexpr int kBufferFlags = 0x00020000;  // raw 32-bit buffer, range-checked
+using Buf = __amdgpu_buffer_rsrc_t;
+__device__ __forceinline__ Buf buffer(const void* p, int bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, __builtin_amdgcn_readfirstlane(bytes),
+                                           kBufferFlags);
+}
+// an offset that no buffer reaches, nor one of the 16-byte pieces of a load there
+constexpr int kPastEnd = 0x7fffff00;
 // s_waitcnt immediate: vector memory counter 0, the others left at their maximum
 constexpr int kWaitVmcnt0 = 0x0F70;
 

@@ -23,12 +23,6 @@ namespace {
 
 // Features, values and statistics are read through range-checked buffers that end with their
 // last row, so that rows past it read as 0: a test per load puts a branch around each.
-using Buf = __amdgpu_buffer_rsrc_t;
-__device__ __forceinline__ Buf buffer(const void* p, int bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, __builtin_amdgcn_readfirstlane(bytes),
-                                           kBufferFlags);
-}
-constexpr int kPastEnd = 0x7ffffff0;  // an offset no buffer reaches
 __device__ __forceinline__ uint4 piece16(Buf b, int off) {
   return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(b, off, 0, 0));
 }
