@@ -520,10 +520,8 @@ template <typename T, int DH, int KB, int PASS>
 hipError_t chunk_launch(const ChunkArgs& a, hipStream_t s) {
   using C = CkCfg<T, DH, KB>;
   static_assert(C::lds(true, true) <= (160u << 10), "LDS of a compute unit");
-  static const hipError_t set = hipFuncSetAttribute(reinterpret_cast<const void*>(chunk_kernel<T, DH, KB, PASS>),
-                                                    hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                    (int)C::lds(true, true));
-  if (set != hipSuccess) return set;
+  const hipError_t e = allow_lds<chunk_kernel<T, DH, KB, PASS>>((int)C::lds(true, true));
+  if (e != hipSuccess) return e;
   const int64_t tiles = (a.n + kChunkTile - 1) / kChunkTile;
   const int64_t blocks = a.heads * ((tiles - a.first + a.step - 1) / a.step);
   hipLaunchKernelGGL((chunk_kernel<T, DH, KB, PASS>), dim3((unsigned)blocks), dim3(kCkThreads),

@@ -344,9 +344,8 @@ hipError_t state_launch(const FeatArgs& a, hipStream_t s) {
 template <auto Kernel>
 hipError_t readout_launch_k(dim3 grid, size_t lds, const FeatArgs& a, hipStream_t s) {
   if (lds > (64u << 10)) {
-    static const hipError_t set = hipFuncSetAttribute(reinterpret_cast<const void*>(Kernel),
-                                                      hipFuncAttributeMaxDynamicSharedMemorySize, 160 << 10);
-    if (set != hipSuccess) return set;
+    const hipError_t e = allow_lds<Kernel>(160 << 10);
+    if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL(Kernel, grid, dim3(kFrThreads), lds, s, a);
   return hipGetLastError();

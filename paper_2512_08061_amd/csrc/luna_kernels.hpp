@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <atomic>
+
 namespace luna {
 
 // piecewise-linear tables of the channel MLPs (built by luna_prepare.hip)
@@ -258,6 +260,22 @@ hipError_t by_heads(int64_t heads, int64_t threads_per_head, F f) {
   }
   return hipSuccess;
 }
+
+// Lets a kernel take up to `bytes` of dynamic LDS on the current device: asked of every device
+// once, and again where it failed.
+template <auto Kernel>
+hipError_t allow_lds(int bytes) {
+  static std::atomic<uint64_t> allowed{0};  // a bit per device (those past 64 are asked each time)
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const uint64_t bit = dev < 64 ? (uint64_t)1 << dev : 0;
+  if (allowed.load(std::memory_order_relaxed) & bit) return hipSuccess;
+  e = hipFuncSetAttribute(reinterpret_cast<const void*>(Kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if (e == hipSuccess) allowed.fetch_or(bit, std::memory_order_relaxed);
+  return e;
+}
+
 inline const void* advance(const void* p, int64_t bytes) { return p ? static_cast<const char*>(p) + bytes : nullptr; }
 inline void* advance(void* p, int64_t bytes) { return p ? static_cast<char*>(p) + bytes : nullptr; }
 

@@ -1,6 +1,7 @@
 """Rules that the kernel sources keep, checked without a GPU."""
 import os
 import re
+import subprocess
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2512_08061_amd", "csrc")
 
@@ -31,3 +32,48 @@ def test_past_end_offset_leaves_room():
     (name, value), = values
     assert name == "luna_device.hpp" and f"constexpr int kPastEnd = {value};" in sources()[name]
     assert int(value, 16) + 64 < 2 ** 31
+
+
+ALLOW_LDS = r"""
+#include "luna_kernels.hpp"
+#include <cstdio>
+static int device = 0, calls = 0, fails = 0;
+extern "C" hipError_t hipGetDevice(int* d) { *d = device; return hipSuccess; }
+extern "C" hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) {
+  ++calls;
+  return fails-- > 0 ? hipErrorInvalidValue : hipSuccess;
+}
+static void one() {}
+static void two() {}
+int main() {
+  int bad = 0;
+  auto expect = [&](hipError_t e, hipError_t want, int n) {
+    if (e != want || calls != n) printf("status %d calls %d, wanted %d and %d\n", e, calls, want, n), ++bad;
+  };
+  fails = 1;
+  expect(luna::allow_lds<one>(1 << 17), hipErrorInvalidValue, 1);  // a failure is not kept
+  expect(luna::allow_lds<one>(1 << 17), hipSuccess, 2);
+  expect(luna::allow_lds<one>(1 << 17), hipSuccess, 2);  // a success is
+  expect(luna::allow_lds<two>(1 << 17), hipSuccess, 3);  // for each kernel
+  device = 3;
+  expect(luna::allow_lds<one>(1 << 17), hipSuccess, 4);  // and each device
+  expect(luna::allow_lds<one>(1 << 17), hipSuccess, 4);
+  device = 64;
+  expect(luna::allow_lds<one>(1 << 17), hipSuccess, 5);
+  expect(luna::allow_lds<one>(1 << 17), hipSuccess, 6);
+  return bad;
+}
+"""
+
+
+def test_dynamic_lds_is_asked_of_every_device(tmp_path):
+    """The attribute that lets a kernel take more than 64 KiB of dynamic LDS, against stand-ins
+    for the two runtime calls; no launcher sets it by itself."""
+    for name, text in sources().items():
+        assert "hipFuncSetAttribute" not in text or name == "luna_kernels.hpp", name
+    src, exe = tmp_path / "allow_lds.cpp", tmp_path / "allow_lds"
+    src.write_text(ALLOW_LDS)
+    subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I", CSRC, "-I", "/opt/rocm/include", str(src), "-o",
+                    str(exe)], check=True)
+    p = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert p.returncode == 0, p.stdout
