@@ -115,15 +115,20 @@ ATTN_CASES = [  # (feature dtype, value dtype, d, D, n, causal)
     ("f32", "f32", 64, 64, 97, False), ("f32", "f32", 64, 100, 333, True), ("bf16", "bf16", 128, 256, 700, False),
     ("bf16", "bf16", 128, 256, 1000, True), ("bf16", "bf16", 64, 128, 333, True), ("bf16", "f32", 32, 48, 129, True),
     ("f32", "bf16", 128, 256, 65, True),
+    # widths that only the fp32 GEMM path takes, over several chunks and 512-token pieces
+    ("f32", "f32", 48, 100, 130, True), ("bf16", "f32", 48, 100, 1100, False), ("bf16", "bf16", 64, 300, 700, True),
+    ("f32", "bf16", 64, 300, 1025, False), ("f32", "f32", 256, 512, 200, True), ("bf16", "bf16", 256, 512, 600, False),
+    ("f32", "f32", 9, 1, 65, True), ("f32", "f32", 33, 512, 513, False), ("bf16", "bf16", 48, 257, 64, True),
 ]
 
 
 @pytest.mark.parametrize("fdt,vdt,d,D,n,causal", ATTN_CASES)
 def test_attn_from_features(fdt, vdt, d, D, n, causal):
     """Positive random features (exp of a Gaussian projection), so that denominators
-    stay away from 0; the bf16 causal cases with (d, D) = (128, 256) and (64, 128) run
-    on the causal scan kernel (with state pieces at n >= 256), the others on the fp32
-    GEMM path."""
+    stay away from 0.  The bf16 causal cases with (d, D) = (128, 256) and (64, 128) run on
+    the causal scan kernel; d in {32, 64, 128} with D <= 256 otherwise on the kernels that
+    read the features as they are (non-causal) or the fp32 chunk kernels (causal); all other
+    widths on fp32 GEMMs."""
     say(f"attention from features {fdt}/{vdt} d={d} D={D} n={n} causal={causal}")
     rng = np.random.default_rng(42 + n)
     B, H = 2, 3
@@ -296,3 +301,20 @@ def test_attn_features_without_workspace():
                                                     torch.cuda.current_stream().cuda_stream)
     assert st == luna.LUNA_OK
     assert_close_rows(to_np(out), VAR.attn_from_features(rq, rk, rv, causal=True), "bf16", "out")
+
+
+@pytest.mark.parametrize("causal", [False, True])
+def test_attn_features_more_heads_than_one_launch(causal):
+    """8.4 million heads and more, of one or two tokens: the launches of every kernel are cut
+    at 2^31 threads."""
+    import torch
+    heads, n, d, eps = (1 << 23) + 1001, 2 if causal else 1, 32, 1e-3
+    say(f"features, {heads} heads causal={causal}")
+    g = torch.Generator(device="cuda").manual_seed(47)
+    fq, fk = (torch.rand((1, heads, n, 1), generator=g, device="cuda") + 0.5 for _ in range(2))
+    V = torch.randn((1, heads, n, d), generator=g, device="cuda").to(torch.bfloat16)
+    out = luna.attn_fwd_features(fq, fk, V, causal=causal, eps=eps)
+    num = (torch.cumsum(fk * V.float(), 2) if causal else fk * V.float()) * fq
+    den = (torch.cumsum(fk, 2) if causal else fk) * fq + eps
+    # (the only rounding beyond fp32 sums of at most two terms is the output's own to bf16)
+    assert ((out.float() - num / den).abs() <= 2.0 ** -8 * (num / den).abs() + 1e-6).all()
