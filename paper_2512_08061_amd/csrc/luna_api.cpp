@@ -144,12 +144,13 @@ luna_status plan_f32_forward(const Problem& pb, bool causal, bool queries, Layou
   return plan_f32_buffers(pb.B * pb.H, pb.n, (int)pb.d, pb.p->M * pb.p->L, causal, queries, true, lay, off);
 }
 
-// The causal kernel's split.  Too few heads to fill the device: up to 85 heads in equal parts,
-// with 97 to 128 heads the staged form below (two scan launches); otherwise cut every head in
-// two at a chunk boundary x near n/2, where a state launch first sums the state of [0, x) in
-// pieces (one workgroup per head and piece, enough pieces to fill the device) and part 1 of
-// the scan launch starts from the sum of the pieces.
-void plan_causal_parts(int64_t heads, int64_t n, size_t state_floats, Layout* lay, size_t* off, bool staged_ok) {
+// The causal kernel's split.  Too few heads to fill the device: up to 85 heads in equal parts
+// (short sequences in one), with 97 to 128 heads the staged form below (two scan launches);
+// otherwise cut every head in two at a chunk boundary x near n/2, where a state launch first
+// sums the state of [0, x) in pieces (one workgroup per head and piece, enough pieces to fill
+// the device) and part 1 of the scan launch starts from the sum of the pieces.
+void plan_causal_parts(luna::Dt dt, int64_t heads, int64_t n, size_t state_floats, Layout* lay, size_t* off,
+                       bool staged_ok) {
   const int64_t nch = (n + 63) / 64;
   lay->state_floats = state_floats;
   // the cut in two: chunks before it, chunks of a piece, pieces
@@ -160,10 +161,16 @@ void plan_causal_parts(int64_t heads, int64_t n, size_t state_floats, Layout* la
     pc = (cx + pieces - 1) / pieces;
     pieces = (cx + pc - 1) / pc;  // every piece non-empty
   }
-  if (heads <= 85 && nch >= 3) {
+  if (heads <= 85) {
     // Equal parts: a state launch over all but the last, their running sums, one scan
-    // launch.  One scanned part in place of a two-part cut's n / 2 tokens: 16 heads of 1999
-    // tokens, d = 128, 32 projections: 48 us instead of 215.
+    // launch, for a chain of one part in place of a cut's n / 2 tokens (16 heads of 32 chunks,
+    // d = 128, 32 projections in bf16: 61 us a call, 222 cut in two).  The two further
+    // launches and the states cost what some chunks of a chain do, the more the more heads.
+    // One part against equal parts, the same map: 1 head 39 / 38 us at 6 chunks, 31 / 38 at 4;
+    // 16 heads 39 / 47 at 6, 47 / 51 at 8, 56 / 52 at 10; 64 heads 56 / 63 at 10, 80 / 69 at
+    // 16.  In fp32 a chunk takes twice the time: d = 64, 16 projections, 1 head 39 / 37 at 3
+    // chunks, 64 heads 39 / 42 at 3 and 47 / 44 at 4.
+    if (nch < (dt == luna::Dt::BF16 ? 6 + heads / 12 : 3 + heads / 40)) return;
     // With a small workspace no more states than the cut in two would hold.
     int64_t parts = std::min(256 / heads, nch);
     if (lay->few) parts = std::min(parts, pieces + 1);
@@ -319,7 +326,7 @@ luna_status plan_pieces(const Problem& pb, Layout* lay) {
       lay->total = off;
       return LUNA_OK;
     }
-    plan_causal_parts(heads, pb.n, state_floats, lay, &off, !lay->given);
+    plan_causal_parts(dt, heads, pb.n, state_floats, lay, &off, !lay->given);
   } else if (pb.op == LUNA_OP_STATE) {
     luna::NoncausalPlan np;
     if (luna::noncausal_supported(dt, d, L, M, &np)) {
@@ -711,7 +718,7 @@ luna_status plan_features_pieces(luna_dtype phi_dtype, luna_dtype dtype, int64_t
   size_t off = 0;
   if (causal && phi_dtype == LUNA_BF16 && dtype == LUNA_BF16 && luna::causal_given_supported(luna::Dt::BF16, (int)d, (int)D)) {
     lay->given = 1;
-    plan_causal_parts(heads, n, luna::causal_given_state_floats((int)d, (int)D), lay, &off, false);
+    plan_causal_parts(luna::Dt::BF16, heads, n, luna::causal_given_state_floats((int)d, (int)D), lay, &off, false);
   } else if (!causal && luna::feat_supported((int)d, (int)D)) {
     // the features in their own type: statistics of pieces only
     lay->feat = 1;

@@ -16,10 +16,10 @@
 //    of [A, A + B), both writing their final states; the second scans [A, A + B) and
 //    [A + B, nch) from those states (A = nch / 5, B = 2 nch / 5: a state-only chunk
 //    costs about half a scanned one, so both launches are balanced);
-//  - up to 85 heads: every head in three or more equal parts, as many as fill the device.
-//    The state launch (a separate instantiation, ST) sums the state of every part but the
-//    last, causal_prefix_kernel their running sums, and the scan launch starts each part
-//    from the state before it;
+//  - up to 85 heads and more than a few chunks: every head in equal parts, as many as fill
+//    the device.  The state launch (a separate instantiation, ST) sums the state of every
+//    part but the last, causal_prefix_kernel their running sums, and the scan launch starts
+//    each part from the state before it;
 //  - otherwise each head is cut at a chunk boundary x near n/2: the state launch (a
 //    separate instantiation, ST) sums the state of [0, x) in pieces, one workgroup per
 //    (head, piece), and writes them in fp32; the scan launch then runs part 0 over

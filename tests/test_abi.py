@@ -288,7 +288,6 @@ def test_distill_planning_and_rejects(lib):
 
 # (op, dtype, heads, n, d, M, L): bytes that the call has to do with, fewer than it asks for
 SMALL_WORKSPACES = [
-    (luna.OP_ATTN_CAUSAL, luna.LUNA_BF16, 64, 192, 128, 32, 8, 104960),
     (luna.OP_ATTN_CAUSAL, luna.LUNA_BF16, 16, 1024, 128, 32, 8, 17013248),
     (luna.OP_ATTN_CAUSAL, luna.LUNA_BF16, 8, 1999, 128, 256, 1, 32332288),
     (luna.OP_ATTN_CAUSAL, luna.LUNA_F32, 3, 321, 64, 16, 8, 304640),
@@ -341,9 +340,11 @@ def test_noalloc_scratch_holds_fewer_pieces(lib, heads, n):
 
 
 def test_features_without_workspace(lib):
-    """Short causal calls on the scan kernel do without any workspace."""
+    """Short causal calls on the scan kernel do without any workspace (it is asked for from
+    the length on where states come in)."""
+    assert lib.luna_attn_features_workspace_bytes(luna.LUNA_BF16, luna.LUNA_BF16, 1, 1, 255, 64, 128, 1, 64) == 0
     st = lib.luna_attn_fwd_features(FAKE, FAKE, luna.LUNA_BF16, FAKE, luna.LUNA_BF16, 1, 1, 255, 64, 128, 1, 64, -1.0,
                                     FAKE, None, 0, None)
     assert st == luna.LUNA_ERR_INVALID_ARG and b"eps" in lib.luna_last_error()
-    assert lib.luna_attn_fwd_features(FAKE, FAKE, luna.LUNA_BF16, FAKE, luna.LUNA_BF16, 1, 1, 256, 64, 128, 1, 64, 1e-6,
+    assert lib.luna_attn_fwd_features(FAKE, FAKE, luna.LUNA_BF16, FAKE, luna.LUNA_BF16, 1, 1, 400, 64, 128, 1, 64, 1e-6,
                                       FAKE, None, 0, None) == luna.LUNA_ERR_WORKSPACE

@@ -347,10 +347,17 @@ def test_attn_causal_staged(dtype, d, M, B, H, n):
 @pytest.mark.parametrize("dtype,d,M,L,B,H,n", [
     ("bf16", 128, 32, 8, 1, 1, 129), ("bf16", 128, 32, 8, 1, 85, 193), ("bf16", 64, 16, 8, 5, 17, 641),
     ("f32", 64, 16, 8, 2, 30, 321), ("bf16", 32, 8, 8, 1, 7, 1999), ("bf16", 128, 256, 1, 1, 43, 449),
-    ("bf16", 64, 16, 8, 1, 86, 200)])
+    # the longest of one part and the shortest of equal ones, for few and for many heads
+    ("bf16", 128, 32, 8, 1, 1, 320), ("bf16", 128, 32, 8, 1, 1, 321), ("bf16", 64, 16, 8, 5, 17, 768),
+    ("bf16", 64, 16, 8, 1, 85, 769), ("bf16", 64, 128, 1, 1, 24, 449), ("f32", 64, 16, 8, 1, 39, 128),
+    ("f32", 64, 16, 8, 1, 39, 129), ("f32", 32, 8, 8, 1, 80, 257),
+    ("f32", 64, 16, 8, 7, 10, 200),  # three parts asked for, two of two chunks taken
+    # past it: one part; the cut in two with three and two state pieces
+    ("bf16", 64, 16, 8, 1, 86, 200), ("bf16", 128, 32, 8, 1, 86, 650), ("f32", 64, 16, 8, 2, 48, 449)])
 def test_attn_causal_equal_parts(dtype, d, M, L, B, H, n):
     """Up to 85 heads: equal parts from the running sums of the states before them, with one
-    to several chunks a part, ragged last parts and chunks, and the first head count past it."""
+    to several chunks a part, ragged last parts and chunks, one part below the length where
+    they pay, and the head counts past it."""
     w = small_workload(dtype, B=B, H=H, n=n, d=d, M=M, L=L, causal=True)
     say(f"causal equal parts {dtype} d={d} M={M} L={L} B={B} H={H} n={n}")
     Q, K, V, p = inputs(w, seed=71)
@@ -587,7 +594,7 @@ def test_attn_out_in_v(dtype, d, M, L, B, H, n, causal):
 
 
 @pytest.mark.parametrize("op,dtype,d,M,L,H,n,few", [
-    ("causal", "bf16", 128, 32, 8, 64, 192, 104960), ("causal", "bf16", 128, 32, 8, 16, 1024, 17013248),
+    ("causal", "bf16", 128, 32, 8, 16, 1024, 17013248),
     ("causal", "bf16", 128, 256, 1, 8, 1999, 32332288), ("causal", "f32", 64, 16, 8, 3, 321, 304640),
     ("forward", "f32", 32, 8, 8, 1, 256, 146432), ("forward", "f32", 128, 32, 8, 12, 1999, 80328704),
     ("state", "bf16", 64, 16, 8, 4, 1000, 637440), ("state", "f32", 128, 32, 8, 1, 2000, 4000000)])

@@ -288,7 +288,7 @@ def test_attn_features_largest_values(pdt, dt, D, n, causal):
 
 
 def test_attn_features_without_workspace():
-    """A short causal call on the scan kernel with no workspace at all: one part a head."""
+    """A short causal call on the scan kernel, for which no workspace is asked: one part a head."""
     import torch
     rng = np.random.default_rng(48)
     n, d, D = 255, 64, 128
