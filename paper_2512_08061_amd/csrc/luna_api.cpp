@@ -96,13 +96,27 @@ struct Layout {
   int given = 0;    // causal: features mapped beforehand (bf16, in phiq / phik), then the scan kernel
 };
 
-// Tokens per piece of the statistics of a whole sequence: 512, or the fewer (64 at least) that
-// put a piece on every compute unit.  A piece is a serial chain of 32-token steps, 16 of them
-// 40 us at d = 128 and 256 features.
-int state_piece(int64_t heads, int64_t n, bool few) {
-  int piece = 512;
-  while (!few && piece > 64 && heads * ((n + piece - 1) / piece) < 256) piece /= 2;
-  return piece;
+// Tokens per piece of the statistics of a whole sequence: 512, or fewer (64 at least) while
+// there are not enough pieces for the compute units.  A piece is a serial chain of 32-token
+// steps (fp32 features and values: 4.9 us a step at 256 features in one workgroup and d = 128,
+// 1.5 at 128 and 64, 0.6 at 64 and 32; both in bf16 a third of it, the two mixed half).  Cut, it
+// takes a launch that adds up the pieces (3 us) and every piece's state written and read.
+// 256 features, d = 128, one piece of the whole against pieces of 64, us a call: fp32, 1 head of
+// 512 tokens 44 / 28; bf16 23.4 / 21.6; 64 bf16 heads of 100 tokens 17 / 33, 128 fp32 heads of
+// 100 tokens 36 / 51.
+int state_piece(luna::Dt fdt, luna::Dt vdt, int64_t heads, int64_t n, int d, int D, bool few) {
+  const int64_t elems = luna::feat_elems(d, D);
+  const int64_t step = fdt != vdt ? 28 : fdt == luna::Dt::BF16 ? 19 : 56;  // in states written and read
+  auto cost = [&](int64_t piece) {
+    const int64_t pieces = (n + piece - 1) / piece;
+    const int each = luna::feat_state_features(D, heads * pieces);
+    return step * std::min(D, each) / D * ((std::min(n, piece) + 31) / 32) + heads * pieces +
+           (pieces > 1 ? 1100000 / elems : 0);
+  };
+  int best = 512;
+  for (int piece = 256; !few && piece >= 64 && heads * ((n + 2 * piece - 1) / (2 * piece)) < 256; piece /= 2)
+    if (cost(piece) < cost(best)) best = piece;
+  return best;
 }
 
 // Buffers of the forward pass in fp32 (the forward of shapes without a fused kernel, and
@@ -112,14 +126,15 @@ int state_piece(int64_t heads, int64_t n, bool few) {
 // Widths that only given features have take fp32 GEMMs over 64-token chunks: [V | 1],
 // [num | den - eps] and the per-chunk states, plus P for the causal form.
 // (features: the buffers for fp32 features, or none when the caller's are used)
-luna_status plan_f32_buffers(int64_t heads, int64_t n, int d, int D, bool causal, bool queries, bool features,
-                             Layout* lay, size_t* off) {
+luna_status plan_f32_buffers(luna::Dt vdt, int64_t heads, int64_t n, int d, int D, bool causal, bool queries,
+                             bool features, Layout* lay, size_t* off) {
   lay->chunk = causal ? 64 : 512;
   int64_t nch = (n + lay->chunk - 1) / lay->chunk;
   if (nch > 65535) return fail(LUNA_ERR_UNSUPPORTED, causal ? "n must be <= 65535 * 64" : "n must be <= 65535 * 512");
   lay->chunked = luna::chunk_supported(d, D);
   if (lay->chunked) {
-    lay->chunk = causal ? luna::kChunkPiece : state_piece(heads, n, lay->few);
+    lay->chunk = causal ? luna::kChunkPiece
+                        : state_piece(luna::Dt::F32, vdt, heads, n, d, D, lay->few);
     nch = (n + lay->chunk - 1) / lay->chunk;
   }
   lay->nch = (int)nch;
@@ -141,7 +156,8 @@ luna_status plan_f32_buffers(int64_t heads, int64_t n, int d, int D, bool causal
   return LUNA_OK;
 }
 luna_status plan_f32_forward(const Problem& pb, bool causal, bool queries, Layout* lay, size_t* off) {
-  return plan_f32_buffers(pb.B * pb.H, pb.n, (int)pb.d, pb.p->M * pb.p->L, causal, queries, true, lay, off);
+  return plan_f32_buffers(pb.dt == LUNA_BF16 ? luna::Dt::BF16 : luna::Dt::F32, pb.B * pb.H, pb.n, (int)pb.d,
+                          pb.p->M * pb.p->L, causal, queries, true, lay, off);
 }
 
 // The causal kernel's split.  Too few heads to fill the device: up to 85 heads in equal parts
@@ -715,6 +731,7 @@ luna_status plan_features_pieces(luna_dtype phi_dtype, luna_dtype dtype, int64_t
   if (causal != 0 && causal != 1) return fail(LUNA_ERR_INVALID_ARG, "causal must be 0 or 1");
   if (causal && chunk != 64) return fail(LUNA_ERR_UNSUPPORTED, "chunk must be 64");
   const int64_t heads = B * H;
+  const luna::Dt vdt = dtype == LUNA_BF16 ? luna::Dt::BF16 : luna::Dt::F32;
   size_t off = 0;
   if (causal && phi_dtype == LUNA_BF16 && dtype == LUNA_BF16 && luna::causal_given_supported(luna::Dt::BF16, (int)d, (int)D)) {
     lay->given = 1;
@@ -723,14 +740,16 @@ luna_status plan_features_pieces(luna_dtype phi_dtype, luna_dtype dtype, int64_t
     // the features in their own type: statistics of pieces only
     lay->feat = 1;
     if ((n + 511) / 512 > 65535) return fail(LUNA_ERR_UNSUPPORTED, "n must be <= 65535 * 512");
-    lay->chunk = state_piece(heads, n, lay->few);
+    lay->chunk = state_piece(phi_dtype == LUNA_BF16 ? luna::Dt::BF16 : luna::Dt::F32, vdt, heads, n, (int)d, (int)D,
+                             lay->few);
     const int64_t pieces = (n + lay->chunk - 1) / lay->chunk;
     lay->nch = (int)pieces;
     lay->sx = off;
     off = align256(off + (size_t)heads * lay->nch * (size_t)luna::feat_elems(d, D) * 4);
   } else {
     lay->generic = 1;
-    luna_status st = plan_f32_buffers(heads, n, (int)d, (int)D, causal != 0, true, phi_dtype == LUNA_BF16, lay, &off);
+    luna_status st =
+        plan_f32_buffers(vdt, heads, n, (int)d, (int)D, causal != 0, true, phi_dtype == LUNA_BF16, lay, &off);
     if (st != LUNA_OK) return st;
   }
   lay->total = off;

@@ -32,7 +32,10 @@ __device__ __forceinline__ uint4 piece16(Buf b, int off) {
 // and values in LDS (the next 32 in registers meanwhile) and read both transposed, the
 // tokens being the k dimension; wave w forms the 16-feature blocks w, w + 4, ... and all
 // value columns.  Bound by the read of the features and values: pieces are short enough
-// that a few hundred workgroups share the device.
+// that a few hundred workgroups share the device; where they are few all the same, a step is
+// bound by its products (4.9 us for 256 fp32 features beside d = 128), and a piece's features
+// go to two or four workgroups that each read its values (a call on 1 head of 512 tokens 38 ->
+// 28 us).
 // ---------------------------------------------------------------------------
 constexpr int kFsTok = 32;
 
@@ -51,6 +54,7 @@ __global__ __launch_bounds__(256) void feat_state_kernel(FeatArgs a) {
   const int rows = (int)min((int64_t)a.piece, a.n - first);
   const int D = a.D, tid = threadIdx.x, lane = tid % kWave, wave = wave_id();
   const int g = lane / 16, r = lane % 16;
+  const int from = blockIdx.y * DPM;  // this workgroup's first feature
   const TF* phi = reinterpret_cast<const TF*>(a.phik) + (head * a.n + first) * D;
   const T* V = reinterpret_cast<const T*>(a.v) + (head * a.n + first) * DH;
   const bool vec = D % VF == 0;  // (uniform) feature rows are whole 16-byte pieces
@@ -68,7 +72,7 @@ __global__ __launch_bounds__(256) void feat_state_kernel(FeatArgs a) {
     if (vec)
 #pragma unroll
       for (int i = 0; i < NP; ++i) {
-        const int c = tid + 256 * i, q = c % (DPM / VF) * VF;
+        const int c = tid + 256 * i, q = from + c % (DPM / VF) * VF;
         pr[i] = piece16(bphi, q < D ? ((t0 + c / (DPM / VF)) * D + q) * (int)sizeof(TF) : kPastEnd);
       }
 #pragma unroll
@@ -85,8 +89,8 @@ __global__ __launch_bounds__(256) void feat_state_kernel(FeatArgs a) {
       }
     } else {
       for (int i = tid; i < kFsTok * DPM; i += 256) {
-        const int k = i / DPM, f = i % DPM;
-        ps[k * LDP + f] = t0 + k < rows && f < D ? phi[(int64_t)(t0 + k) * D + f] : (TF)0.0f;
+        const int k = i / DPM, f = from + i % DPM;
+        ps[k * LDP + i % DPM] = t0 + k < rows && f < D ? phi[(int64_t)(t0 + k) * D + f] : (TF)0.0f;
       }
     }
 #pragma unroll
@@ -128,12 +132,12 @@ __global__ __launch_bounds__(256) void feat_state_kernel(FeatArgs a) {
       set_operand(bf, y);
 #pragma unroll
       for (int f = 0; f < FBW; ++f)
-        if (f == 0 || 16 * (wave + 4 * f) < D) mma(acc[f][cb], af[f], bf);  // (uniform)
+        if (f == 0 || from + 16 * (wave + 4 * f) < D) mma(acc[f][cb], af[f], bf);  // (uniform)
     }
   }
   float* S = a.state + blockIdx.x * a.elems;
   auto store = [&](const f32x4& c, int f, int cb) {
-    const int f0 = 16 * (wave + 4 * f) + 4 * g;
+    const int f0 = from + 16 * (wave + 4 * f) + 4 * g;
 #pragma unroll
     for (int j = 0; j < 4; ++j)
       if (f0 + j < D) S[(f0 + j) * DH + 16 * cb + r] = c[j];
@@ -143,7 +147,7 @@ __global__ __launch_bounds__(256) void feat_state_kernel(FeatArgs a) {
   for (int f = 0; f < FBW; ++f) {
     z[f] += __shfl_xor(z[f], 16, kWave);
     z[f] += __shfl_xor(z[f], 32, kWave);
-    const int f0 = 16 * (wave + 4 * f);
+    const int f0 = from + 16 * (wave + 4 * f);
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb) {
       const f32x4 c = acc[f][cb];
@@ -171,7 +175,7 @@ __global__ __launch_bounds__(256) void feat_state_kernel(FeatArgs a) {
             const float w = WGT && t < rows ? reinterpret_cast<const float2*>(a.w)[head * a.n + first + t].x : 1.0f;
 #pragma unroll
             for (int f = 0; f < FBW; ++f) {
-              const int k = 16 * (wave + 4 * f) + r;
+              const int k = from + 16 * (wave + 4 * f) + r;
               x[f].v[e] = w * __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
                                   bphi, k < D ? (t * D + k) * (int)sizeof(TF) : kPastEnd, 0, 0));
             }
@@ -328,9 +332,10 @@ __global__ __launch_bounds__(256) void feat_export_kernel(const float* __restric
 
 template <typename TF, typename T, int DH, bool WGT>
 hipError_t state_launch_w(const FeatArgs& a, hipStream_t s) {
-  const dim3 grid((unsigned)(a.heads * a.pieces)), block(256);
-  if (a.D <= 64) hipLaunchKernelGGL((feat_state_kernel<TF, T, DH, 1, WGT>), grid, block, 0, s, a);
-  else if (a.D <= 128) hipLaunchKernelGGL((feat_state_kernel<TF, T, DH, 2, WGT>), grid, block, 0, s, a);
+  const int each = feat_state_features(a.D, a.heads * a.pieces);
+  const dim3 grid((unsigned)(a.heads * a.pieces), (unsigned)((a.D + each - 1) / each)), block(256);
+  if (each == 64) hipLaunchKernelGGL((feat_state_kernel<TF, T, DH, 1, WGT>), grid, block, 0, s, a);
+  else if (each == 128) hipLaunchKernelGGL((feat_state_kernel<TF, T, DH, 2, WGT>), grid, block, 0, s, a);
   else hipLaunchKernelGGL((feat_state_kernel<TF, T, DH, 4, WGT>), grid, block, 0, s, a);
   return hipGetLastError();
 }

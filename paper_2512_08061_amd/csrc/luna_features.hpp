@@ -23,6 +23,13 @@ struct FeatArgs {
 bool feat_supported(int d, int D);
 // floats from one piece's statistics to the next's: whole 16-byte rows of S
 constexpr int64_t feat_elems(int64_t d, int64_t D) { return (D * (d + 1) + 3) / 4 * 4; }
+// features per workgroup of the state kernel: all of them in blocks of 64, or half or a quarter
+// while the pieces' workgroups still find a compute unit each
+constexpr int feat_state_features(int D, int64_t pieces) {
+  int each = D <= 64 ? 64 : D <= 128 ? 128 : 256;
+  while (each > 64 && pieces * ((D + each / 2 - 1) / (each / 2)) <= 256) each /= 2;
+  return each;
+}
 // per piece: S = phi(K)^T V, z = phi(K)^T 1
 hipError_t launch_feat_state(Dt fdt, Dt vdt, int d, const FeatArgs& a, hipStream_t s);
 // the pieces of every head summed into its first (in order)

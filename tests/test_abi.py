@@ -292,11 +292,11 @@ SMALL_WORKSPACES = [
     (luna.OP_ATTN_CAUSAL, luna.LUNA_BF16, 8, 1999, 128, 256, 1, 32332288),
     (luna.OP_ATTN_CAUSAL, luna.LUNA_F32, 3, 321, 64, 16, 8, 304640),
     (luna.OP_ATTN, luna.LUNA_F32, 1, 256, 32, 8, 8, 146432),
-    (luna.OP_ATTN, luna.LUNA_F32, 12, 1999, 128, 32, 8, 80328704),
+    (luna.OP_ATTN, luna.LUNA_F32, 1, 1999, 128, 32, 8, 6790656),
     (luna.OP_ATTN, luna.LUNA_BF16, 1, 600, 128, 256, 1, 2217472),
     (luna.OP_STATE, luna.LUNA_BF16, 4, 1000, 64, 16, 8, 637440),
-    (luna.OP_STATE, luna.LUNA_F32, 1, 16384, 128, 32, 8, 29563392),
-    (luna.OP_ATTN_BWD, luna.LUNA_F32, 12, 1999, 128, 32, 8, 190023680),
+    (luna.OP_STATE, luna.LUNA_F32, 1, 2000, 128, 32, 8, 3713536),
+    (luna.OP_ATTN_BWD, luna.LUNA_F32, 1, 1999, 128, 32, 8, 10601984),
 ]
 
 
@@ -348,3 +348,12 @@ def test_features_without_workspace(lib):
     assert st == luna.LUNA_ERR_INVALID_ARG and b"eps" in lib.luna_last_error()
     assert lib.luna_attn_fwd_features(FAKE, FAKE, luna.LUNA_BF16, FAKE, luna.LUNA_BF16, 1, 1, 400, 64, 128, 1, 64, 1e-6,
                                       FAKE, None, 0, None) == luna.LUNA_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("dt,heads,n,pieces", [
+    (luna.LUNA_F32, 1, 100, 1), (luna.LUNA_F32, 1, 512, 8), (luna.LUNA_F32, 128, 100, 1), (luna.LUNA_F32, 300, 1024, 2),
+    (luna.LUNA_BF16, 1, 100, 1), (luna.LUNA_BF16, 64, 512, 1), (luna.LUNA_BF16, 1, 512, 8)])
+def test_state_pieces(lib, dt, heads, n, pieces):
+    """Non-causal calls on 256 given features cut their tokens only where the pieces pay."""
+    nb = lib.luna_attn_features_workspace_bytes(dt, dt, 1, heads, n, 128, 256, 0, 64)
+    assert nb == heads * pieces * 256 * 129 * 4

@@ -318,3 +318,17 @@ def test_attn_features_more_heads_than_one_launch(causal):
     den = (torch.cumsum(fk, 2) if causal else fk) * fq + eps
     # (the only rounding beyond fp32 sums of at most two terms is the output's own to bf16)
     assert ((out.float() - num / den).abs() <= 2.0 ** -8 * (num / den).abs() + 1e-6).all()
+
+
+@pytest.mark.parametrize("pdt,dt,d,D,B,H,n", [
+    ("f32", "f32", 128, 256, 1, 150, 70), ("f32", "bf16", 128, 200, 2, 65, 33), ("bf16", "bf16", 64, 256, 1, 129, 64),
+    ("f32", "f32", 64, 128, 1, 257, 45), ("bf16", "f32", 32, 256, 1, 100, 40), ("bf16", "bf16", 128, 72, 1, 140, 97)])
+def test_attn_features_many_heads(pdt, dt, d, D, B, H, n):
+    """Non-causal attention from features with as many pieces as the state kernel gives all, or
+    half, of their features to one workgroup (few pieces give a quarter)."""
+    say(f"features many heads phi={pdt} {dt} d={d} D={D} B={B} H={H} n={n}")
+    rng = np.random.default_rng(2000 * D + n)
+    fq, fqr = _upload_rounded(np.abs(rng.standard_normal((B, H, n, D))), pdt)
+    fk, fkr = _upload_rounded(np.abs(rng.standard_normal((B, H, n, D))), pdt)
+    V, Vr = _upload_rounded(rng.standard_normal((B, H, n, d)), dt)
+    assert_close(to_np(luna.attn_fwd_features(fq, fk, V)), VAR.attn_from_features(fqr, fkr, Vr), dt, "out")
