@@ -142,7 +142,7 @@ __global__ __launch_bounds__(256) void feat_state_kernel(FeatArgs a) {
     for (int j = 0; j < 4; ++j)
       if (f0 + j < D) S[(f0 + j) * DH + 16 * cb + r] = c[j];
   };
-  bool nan = false;
+  float nan = 0.0f;  // until a sum is NaN (or infinite)
 #pragma unroll
   for (int f = 0; f < FBW; ++f) {
     z[f] += __shfl_xor(z[f], 16, kWave);
@@ -152,7 +152,7 @@ __global__ __launch_bounds__(256) void feat_state_kernel(FeatArgs a) {
     for (int cb = 0; cb < CB; ++cb) {
       const f32x4 c = acc[f][cb];
       store(c, f, cb);
-      nan = nan || __builtin_isunordered(c[0], c[1]) || __builtin_isunordered(c[2], c[3]);
+      nan = fmaf(c[0] + c[1], 0.0f, fmaf(c[2] + c[3], 0.0f, nan));
     }
     if (g == 0 && f0 + r < D) S[D * DH + f0 + r] = z[f];
   }
@@ -160,7 +160,7 @@ __global__ __launch_bounds__(256) void feat_state_kernel(FeatArgs a) {
   // one, has met parts of either sign, and such sums end as NaN.  They are formed again as fp32
   // products, each wave's from memory.
   if constexpr (sizeof(TF) > sizeof(T))
-    if (__any(nan)) {  // (uniform)
+    if (__any(nan != 0.0f)) {  // (uniform)
 #pragma unroll 1
       for (int cb = 0; cb < CB; ++cb) {
         f32x4 c[FBW];
