@@ -47,7 +47,14 @@ KERNEL_SOURCES = {
     "causal_kernel": ["luna_causal.hip", "luna_device.hpp", "luna_kernels.hpp"],
     "nc_fused_kernel": ["luna_noncausal.hip", "luna_device.hpp", "luna_kernels.hpp"],
     "featuremap_kernel": ["luna_featuremap.hip", "luna_device.hpp", "luna_kernels.hpp"],
+    "chunk_kernel": ["luna_chunk_kernel.hpp", "luna_chunk.hpp", "luna_split.hpp", "luna_device.hpp",
+                     "luna_kernels.hpp"],
+    "feat_state_kernel": ["luna_features.hip", "luna_features.hpp", "luna_split.hpp", "luna_device.hpp",
+                          "luna_kernels.hpp"],
+    "map_bwd_kernel": ["luna_map_backward.hip", "luna_grad.hpp", "luna_split.hpp", "luna_device.hpp",
+                       "luna_kernels.hpp"],
 }
+# the kernels whose HBM traffic is recorded, with their workloads
 KERNEL_WORKLOAD = {"causal_kernel": "long_causal", "nc_fused_kernel": "long_noncausal",
                    "featuremap_kernel": "featuremap_long_noncausal"}
 # launches of the kernel per ABI call on these workloads: the causal call (128 heads)
@@ -122,11 +129,11 @@ def traffic_from(fetch_csv: str, write_csv: str, command: str) -> int:
         if not copies:
             log(f"{path}: no 1 GiB copy dispatch found (run bench.py with --copy-calibration)")
             return 1
-        if not any(f"{len(k)}{k}" in nm for k in KERNEL_SOURCES for nm in names.values()):
+        if not any(f"{len(k)}{k}" in nm for k in KERNEL_WORKLOAD for nm in names.values()):
             log(f"{path}: none of the measured kernels")
             return 1
         factor = COPY_BYTES / (sum(copies) / len(copies))
-        for kern in KERNEL_SOURCES:
+        for kern in KERNEL_WORKLOAD:
             ds = [d for d in vals if f"{len(kern)}{kern}" in names[d]]
             if ds:
                 rec = out.setdefault(kern, {})
@@ -416,10 +423,15 @@ COUNTER_UTIL = [
 ]
 COUNTER_KERNELS = {  # kernel-name pattern (mangled or not) -> (file tag, workload, kernel whose sources are hashed)
     r"nc_fused_kernel(<|I)": ("nc_fused_kernel", "long_noncausal", "nc_fused_kernel"),
-    r"(13causal_kernelI.*Lb1ELb0EE|\bcausal_kernel<.*true, false>)": ("causal_kernel_state_launch", "long_causal",
-                                                                         "causal_kernel"),
-    r"(13causal_kernelI.*Lb0ELb0EE|\bcausal_kernel<.*false, false>)": ("causal_kernel_scan_launch", "long_causal",
-                                                                          "causal_kernel"),
+    r"(13causal_kernelI.*Lb1ELb0ELb0EE|\bcausal_kernel<.*true, false, false>)": ("causal_kernel_state_launch",
+                                                                                "long_causal", "causal_kernel"),
+    r"(13causal_kernelI.*Lb0ELb0ELb0EE|\bcausal_kernel<.*false, false, false>)": ("causal_kernel_scan_launch",
+                                                                                 "long_causal", "causal_kernel"),
+    r"12chunk_kernelIDF16bLi128ELi8ELi0EE": ("chunk_kernel_query_pass", "backward_long_causal", "chunk_kernel"),
+    r"12chunk_kernelIDF16bLi128ELi8ELi1EE": ("chunk_kernel_key_pass", "backward_long_causal", "chunk_kernel"),
+    r"17feat_state_kernelIfDF16bLi128ELi4ELb[01]EE": ("feat_state_kernel", "backward_long_causal",
+                                                      "feat_state_kernel"),
+    r"14map_bwd_kernelIDF16bLi128ELi8ELb0EE": ("map_bwd_kernel", "backward_long_causal", "map_bwd_kernel"),
     r"pwl_prepare_kernel": ("pwl_prepare_kernel", "bench_step", None),
     r"featuremap_kernel(<|I)": ("featuremap_kernel", "featuremap_long_noncausal", None),
 }
@@ -678,13 +690,13 @@ def configs_bench(args) -> int:
         mfma_peak = MFMA_BF16_PEAK_TFLOPS if w.dtype == "bf16" else MFMA_F32_PEAK_TFLOPS
         t_hbm, t_mfma = gb / HBM_PEAK_GBS, tf / mfma_peak
         # the path, from the workspace beyond the tables (a feature-map call's workspace):
-        # the fp32 GEMM path holds fp32 features of the queries and keys (8 M L bytes per
-        # token and head), the causal kernel with the features given bf16 ones (4 M L),
-        # the attention kernels at most small partial statistics
+        # the fp32 path holds fp32 features of the queries and keys (8 M L bytes per token
+        # and head), the causal kernel with the features given bf16 ones (4 M L), the
+        # attention kernels at most small partial statistics
         ws_tables = luna.workspace_bytes(luna.OP_FEATUREMAP, luna.LUNA_BF16 if w.dtype == "bf16" else luna.LUNA_F32,
                                          w.B, w.H, w.n, w.d, pt)
         fb = (plan.ws_bytes - ws_tables) / (w.M * w.L * th)
-        path = "fp32 GEMM" if fb >= 8 else "features mapped, then scan" if fb >= 4 else "attention kernels"
+        path = "fp32 kernels" if fb >= 8 else "features mapped, then scan" if fb >= 4 else "attention kernels"
         rec.update({
             "status": "ok",
             "path": path,
@@ -723,8 +735,8 @@ def configs_bench(args) -> int:
                      "algorithmic bytes (read Q, K, V, write out) at 8 TB/s and the MFMA time at the dtype's "
                      "dense peak. path: the attention kernels (fused, or the split state / reduce / readout kernels "
                      "below 192 heads), the features mapped first and then the causal scan kernel, or the fp32 "
-                     "GEMM path of the shapes that have neither (features in the workspace, all arithmetic "
-                     "fp32).\n\n")
+                     "kernels of the shapes that have neither (features in the workspace in fp32, then chunk or "
+                     "readout kernels on them).\n\n")
             cores = next((r["oracle"]["cores"] for r in rows if r["status"] == "ok"), 0)
             fh.write(f"oracle: the float64 CPU oracle (the linear form non-causal, the token recurrence causal) "
                      f"timed in the same run on {cores} host cores over whole heads of the same inputs, added "
@@ -878,7 +890,8 @@ def variants_bench(args) -> int:
         t_hbm = nbytes / (HBM_PEAK_GBS * 1e9)
         rec = {"case": label, "shape": {"B": B, "H": H, "n": n, "d": d, "D": D, "causal": causal,
                                         "features": "bf16" if fb == 2 else "f32", "values": "bf16"},
-               "path": "causal scan kernel" if (causal and fb == 2) else "fp32 GEMM",
+               "path": "state and readout kernels" if not causal else
+                       "causal scan kernel" if fb == 2 else "fp32 chunk kernels",
                "ms_median": round(ms, 5), "ms_p10": round(p10, 5), "ms_p90": round(p90, 5),
                "tokens_per_s": B * n / (ms * 1e-3), "hbm_gbs": nbytes / (ms * 1e-3) / 1e9,
                "bound": "hbm", "floor_us": 1e6 * t_hbm, "roofline_frac": t_hbm / (ms * 1e-3)}

@@ -45,11 +45,12 @@
  *  - Every problem with d in {32, 64, 128}, L in {1, 2, 4, 8, 16} and M*L <= 256
  *    runs on the GPU.  The shapes below have fused attention kernels (Q, K and V
  *    read once, out written once); the others (one channel per projection with
- *    M = 128 or 256, fp32 at d = 128, ...) take a path of fp32 matrix-core GEMMs
- *    and scans over 64-token chunks (causal) or 512-token pieces (non-causal) with
- *    the features in the workspace: the same results to fp32 rounding, slower, and
- *    about 4 (2 M L + 2 (d + 1)) bytes of workspace per token and head plus
- *    4 M L (d + 1) per chunk or piece (and 16 KiB per causal chunk).
+ *    M = 128 or 256, fp32 at d = 128, ...) write the features to the workspace and
+ *    run fp32 kernels on them, over the statistics of 128-token pieces (causal) or
+ *    of pieces of 64 to 512 tokens (non-causal): the same results to fp32 rounding,
+ *    slower, with 8 M L bytes of workspace per token and head (bf16 at d = 128,
+ *    causal, with M L = 256, and at d = 64 with 128: 4 M L, and the scan kernel) plus
+ *    4 M L (d + 1) per piece.
  *      non-causal, (dtype, d, L, M): (f32, 32, 8 or 2, <= 16), (f32, 64, 8, <= 16),
  *        (bf16, 32, 8, <= 16), (bf16, 64, 8, <= 32), (bf16, 64, 4, <= 16),
  *        (bf16, 64, 1, 49..64 or 113..128), (bf16, 128, 8, <= 16);
@@ -262,9 +263,9 @@ typedef struct luna_phi_grads {
  * channel functions through their exact piecewise-linear form, whose slopes give
  * dpsi/du).  Supported: d in {32, 64, 128}, L in {1, 2, 4, 8, 16}, M*L <= 256 and
  * H <= 65535.  The workspace (LUNA_OP_ATTN_BWD / LUNA_OP_ATTN_CAUSAL_BWD in
- * luna_workspace_bytes) holds the features, the per-chunk states and the partial
- * parameter sums: about 4 (2 M L + 3 (d + 1)) bytes per token and head, plus
- * 2 x 4 M L (d + 1) per chunk of 64 tokens for the causal form.
+ * luna_workspace_bytes) holds the features and their gradients, the pieces' states and
+ * the partial parameter sums: about 4 (4 M L + 2 M + 2) bytes per token and head, plus
+ * 2 x 4 M L (d + 1) per piece (of 128 tokens for the causal form).
  */
 luna_status luna_attn_bwd(const void* Q, const void* K, const void* V, const void* dO, luna_dtype dtype,
                           int64_t B, int64_t H, int64_t n, int64_t d, const luna_phi_params* p,

@@ -29,7 +29,12 @@ struct ChunkArgs {
 // Tokens per piece of the causal form.  Every piece's state is written once, scanned in place
 // and read twice or more, while a tile also meets the other tiles of its piece.  Backward of
 // 2 x 16 heads of 2048 tokens, d = 128, D = 256: states and scans take 210 us at one tile a
-// piece and 139 us at two, the query and key passes 350 and 401 us.
+// piece and 139 us at two, the query and key passes 350 and 401 us.  Calls with one, two and
+// four tiles a piece, 32 heads of 1024 tokens: that backward 415 / 404 / 462 us, with D = 128
+// 263 / 273 / 330, in fp32 497 / 497 / 584 and 327 / 339 / 410; d = 64, D = 128 193 / 204 / 246;
+// the fp32 forward with D = 256 166 / 158 / 177, with 128 106 / 104 / 118.  4 heads of 333
+// tokens: 186 / 206 / 252 and 57 / 64 / 83.  (Two suit the largest maps and the forward, one
+// the smaller maps' backward and short calls.)
 constexpr int kChunkPiece = 128;
 
 bool chunk_supported(int d, int D);

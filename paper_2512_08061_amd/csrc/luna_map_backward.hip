@@ -53,8 +53,9 @@ constexpr int wt_blocks() { return (256 / L + 31) / 32; }  // 32-projection bloc
 
 // Threads per workgroup: 16 waves where a lane's fragments, dx sums and feature gradients
 // nearly fit the 128 registers that leaves it, 8 where they would spill for real (at
-// d = 64, L = 8 in bf16, 16 waves with 24 spilled bytes take 71 us for 2 x 151,296 rows
-// and 16 projections, 8 waves 80 us).
+// d = 64, L = 8 in bf16, 16 waves spill 24 bytes: the backward call on 768 heads of 197 rows
+// with 16 projections takes 464 us, with 32 projections 830; with 8 waves 467 and 841; without
+// dx, in the distillation call, the kernel takes 85 and 82.5 us).
 template <typename T, int DH, int L, bool PACK>
 constexpr int map_threads() {
   constexpr int NT = PACK ? 2 : 1;
@@ -78,7 +79,7 @@ constexpr int map_threads() {
 // The moments are LDS atomics in fp64: an fp32 LDS atomic takes 195 cycles per wave
 // instruction here (a probe with one workgroup of 8 waves per CU; 3 cycles a lane whatever
 // the addresses), an fp64 one 9 to 21.  With fp32 moments they bound this kernel: 170 us
-// for 2 x 12 x 32 heads of 512 rows, 8 projections and 8 channels, now 80, of which the
+// for 2 x 12 x 32 heads of 512 rows, 8 projections and 8 channels, now 68, of which the
 // 200 MB of x, dphi and dx are 41 at the rate of a copy.  With the table they fill most
 // of a CU's LDS, so one workgroup runs per CU.
 template <typename T, int DH, int L, bool PACK>
