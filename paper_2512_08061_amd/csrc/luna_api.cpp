@@ -97,21 +97,21 @@ struct Layout {
 };
 
 // Tokens per piece of the statistics of a whole sequence: 512, or fewer (64 at least) while
-// there are not enough pieces for the compute units.  A piece is a serial chain of 32-token
-// steps (fp32 features and values: 4.9 us a step at 256 features in one workgroup and d = 128,
-// 1.5 at 128 and 64, 0.6 at 64 and 32; both in bf16 a third of it, the two mixed half).  Cut, it
-// takes a launch that adds up the pieces (3 us) and every piece's state written and read.
-// 256 features, d = 128, one piece of the whole against pieces of 64, us a call: fp32, 1 head of
-// 512 tokens 44 / 28; bf16 23.4 / 21.6; 64 bf16 heads of 100 tokens 17 / 33, 128 fp32 heads of
-// 100 tokens 36 / 51.
+// there are not enough pieces for the compute units and the shorter chain pays.  A piece is a
+// serial chain of 32-token steps: with fp32 features and values 4.9 us a step at 256 features in
+// one workgroup and d = 128, 1.5 at 128 and 64, 0.6 at 64 and 32; in bf16 1.4, 0.55 and 0.3; the
+// two mixed in between.  Cut, it takes a launch that adds up the pieces (3 us) and every piece's
+// state written and read (5.8 TB/s).  256 features, d = 128, one piece of the whole against
+// pieces of 64, us a call: fp32, 1 head of 512 tokens 44 / 28, bf16 23.4 / 21.6; 64 bf16 heads of
+// 100 tokens 17 / 33, 128 fp32 heads of 100 tokens 36 / 51.
 int state_piece(luna::Dt fdt, luna::Dt vdt, int64_t heads, int64_t n, int d, int D, bool few) {
-  const int64_t elems = luna::feat_elems(d, D);
-  const int64_t step = fdt != vdt ? 28 : fdt == luna::Dt::BF16 ? 19 : 56;  // in states written and read
-  auto cost = [&](int64_t piece) {
-    const int64_t pieces = (n + piece - 1) / piece;
-    const int each = luna::feat_state_features(D, heads * pieces);
-    return step * std::min(D, each) / D * ((std::min(n, piece) + 31) / 32) + heads * pieces +
-           (pieces > 1 ? 1100000 / elems : 0);
+  const double elems = (double)luna::feat_elems(d, D);
+  const bool mixed = fdt != vdt, bf16 = fdt == luna::Dt::BF16;
+  const double each_step = mixed ? 0.25 : bf16 ? 0.22 : 0.3, each_elem = mixed ? 7e-5 : bf16 ? 3.6e-5 : 1.4e-4;
+  auto cost = [&](int64_t piece) {  // us
+    const int64_t pieces = (n + piece - 1) / piece, steps = (std::min(n, piece) + 31) / 32;
+    const double part = std::min(1.0, (double)luna::feat_state_features(D, heads * pieces) / D);
+    return steps * (each_step + each_elem * elems * part) + (pieces > 1 ? 3.0 + 1.4e-6 * elems * heads * pieces : 0.0);
   };
   int best = 512;
   for (int piece = 256; !few && piece >= 64 && heads * ((n + 2 * piece - 1) / (2 * piece)) < 256; piece /= 2)

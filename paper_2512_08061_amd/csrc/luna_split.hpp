@@ -26,14 +26,15 @@ __device__ __forceinline__ void split3(Split3& s, const float (&x)[8]) {
   float r[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) r[e] = x[e];
+  float most = kBf16Max;
+  asm("" : "+s"(most));  // (one scalar register for both bounds: two constants take vector registers)
 #pragma unroll
   for (int k = 0; k < 3; ++k)
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       if (e % 2 == 0) {
         if (ALL && k == 0)
-          s.p[k].set2(e, __builtin_amdgcn_fmed3f(r[e], -kBf16Max, kBf16Max),
-                      __builtin_amdgcn_fmed3f(r[e + 1], -kBf16Max, kBf16Max));
+          s.p[k].set2(e, __builtin_amdgcn_fmed3f(r[e], -most, most), __builtin_amdgcn_fmed3f(r[e + 1], -most, most));
         else s.p[k].set2(e, r[e], r[e + 1]);
       }
       const float h = s.p[k].get(e);
