@@ -303,35 +303,23 @@ __global__ __launch_bounds__(kCkThreads, KB <= 4 ? 4 : 2) void chunk_kernel(Chun
       load8(p, ps + k * PP + (16 * (rb1 + b) + r) * LDP + 32 * ks + 8 * g);
       return p;
     };
-    bool rest = true;  // (the parts gather as in mma_value)
-    if constexpr (sizeof(T) == 2)
-      if (__any(not_finite(va[0]) || not_finite(va[1]))) {  // (uniform) the first parts, then the others by 1
-        rest = false;
+    if constexpr (sizeof(T) == 2) {  // (the parts gather as in mma_value)
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
+      for (int ks = 0; ks < 2; ++ks) {
 #pragma unroll
-          for (int b = 0; b < R1; ++b) mma(num[b], va[ks], p_of(ks, b, 0));
-          to_ones(va[ks]);
+        for (int b = 0; b < R1; ++b) mma(num[b], va[ks], p_of(ks, b, 0));
+        if (__any(not_finite(va[ks]))) to_ones(va[ks]);  // (uniform)
 #pragma unroll
-          for (int b = 0; b < R1; ++b) {
-            mma(lo1[b], va[ks], p_of(ks, b, 2));
-            mma(lo1[b], va[ks], p_of(ks, b, 1));
-          }
+        for (int b = 0; b < R1; ++b) {
+          mma(lo1[b], va[ks], p_of(ks, b, 2));
+          mma(lo1[b], va[ks], p_of(ks, b, 1));
         }
       }
-    if (rest) {
+    } else {
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-        for (int b = 0; b < R1; ++b) {
-          if constexpr (sizeof(T) == 2) {
-            mma(lo1[b], va[ks], p_of(ks, b, 2));
-            mma(lo1[b], va[ks], p_of(ks, b, 1));
-            mma(num[b], va[ks], p_of(ks, b, 0));
-          } else {
-            mma(lo1[b], va[ks], p_of(ks, b, 0));
-          }
-        }
+        for (int b = 0; b < R1; ++b) mma(lo1[b], va[ks], p_of(ks, b, 0));
     }
   }
 #pragma unroll
