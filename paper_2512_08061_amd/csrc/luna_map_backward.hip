@@ -53,7 +53,7 @@ constexpr int wt_blocks() { return (256 / L + 31) / 32; }  // 32-projection bloc
 
 // Threads per workgroup: 16 waves where a lane's fragments, dx sums and feature gradients
 // nearly fit the 128 registers that leaves it, 8 where they would spill for real (at
-// d = 64, L = 8 in bf16, 16 waves spill 24 bytes: the backward call on 768 heads of 197 rows
+// d = 64, L = 8 in bf16, 16 waves spill 16 bytes: the backward call on 768 heads of 197 rows
 // with 16 projections takes 464 us, with 32 projections 830; with 8 waves 467 and 841; without
 // dx, in the distillation call, the kernel takes 85 and 82.5 us).
 template <typename T, int DH, int L, bool PACK>
